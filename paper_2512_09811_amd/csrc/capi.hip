@@ -790,10 +790,14 @@ pp_status ppint_syev(int32_t n, const double* A, double* w, double* Z) {
 
 pp_status ppint_cholesky(int32_t n, const double* A, double* L) {
   g_setup_error.clear();
-  return guarded(&g_setup_error, [&] {
-    ppw::small_cholesky(n, A, L, nullptr, nullptr);
+  double* scr = nullptr;
+  pp_status st = guarded(&g_setup_error, [&] {
+    if (n > 64 && n <= 512) PPW_HIP(hipMalloc(&scr, sizeof(double) * n * n));
+    ppw::small_cholesky(n, A, L, nullptr, scr, nullptr);
     PPW_HIP(hipDeviceSynchronize());
   });
+  if (scr) (void)hipFree(scr);
+  return st;
 }
 
 pp_status ppint_riesz_filter(pp_handle* h, double center, double radius, int32_t nodes, double tol, int32_t maxit,

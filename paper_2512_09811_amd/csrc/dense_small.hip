@@ -256,112 +256,92 @@ __global__ __launch_bounds__(NT) void syev_kernel(int n, const double* __restric
   }
 }
 
-__global__ __launch_bounds__(kT) void cholesky_kernel(int n, const double* __restrict__ A, double* __restrict__ L,
-                                                      int* __restrict__ info) {
-  __shared__ int bad;
-  const int tid = threadIdx.x;
-  const long nn = (long)n * n;
-  for (long i = tid; i < nn; i += kT) {
-    const long r = i / n, c = i % n;
-    L[i] = c <= r ? A[i] : 0.0;
+// Panel of the blocked Cholesky: columns j0..j0+jb-1 (jb <= 64) of the lower factor, read from
+// W and written to L (row-major n x n, zeros above the diagonal); the update of the trailing
+// columns is a GEMM issued by the host.  info (nullable): 0 on success, j+1 for the first
+// non-positive pivot j (later panels then stop).
+//
+// The panel is a chain of jb columns, so its time is the latency of one column.  Every
+// workgroup factors the 64-row diagonal block itself and then owns 128 of the rows below it,
+// which removes all exchange between workgroups; a thread keeps one row, its part of the panel
+// in LDS (column-major: the lanes of a wave read consecutive words, and the pivot row's entry is
+// one broadcast), subtracts the earlier columns in order and finds the pivot by itself, so a
+// column costs one barrier of three waves.  Measured at n = 480: 8 panels of 0.30 ms in one
+// workgroup that updated the whole panel in global memory per column; now 0.03 ms each.
+constexpr int kCholNB = 64, kCholRows = 128;
+__global__ __launch_bounds__(kCholNB + kCholRows) void chol_panel_kernel(int n, int j0, int jb,
+                                                                         const double* __restrict__ W,
+                                                                         double* __restrict__ L,
+                                                                         int* __restrict__ info) {
+  __shared__ double Ds[kCholNB][kCholNB];    // [column][row] of the diagonal block
+  __shared__ double Os[kCholNB][kCholRows];  // [column][row] of this workgroup's rows below it
+  __shared__ double dg[kCholNB];
+  const int tid = threadIdx.x, nt = kCholNB + kCholRows;
+  if (info && j0 > 0 && *info != 0) return;
+  const int j1 = j0 + jb, r0 = j1 + (int)blockIdx.x * kCholRows;
+  const int nown = max(0, min(kCholRows, n - r0));
+  for (int i = tid; i < jb * jb; i += nt) {
+    const int r = i / jb, k = i % jb;
+    Ds[k][r] = W[(long)(j0 + r) * n + j0 + k];
   }
-  if (tid == 0) bad = 0;
+  for (int i = tid; i < nown * jb; i += nt) {
+    const int r = i / jb, k = i % jb;
+    Os[k][r] = W[(long)(r0 + r) * n + j0 + k];
+  }
   __syncthreads();
-  for (int j = 0; j < n; ++j) {
-    const double djj = L[(long)j * n + j];
-    if (!(djj > 0.0)) {
-      if (tid == 0) bad = j + 1;
-      __syncthreads();
+  const bool diag = tid < kCholNB;
+  const int row = diag ? tid : tid - kCholNB;
+  const bool live = diag ? row < jb : row < nown;
+  double* mine = diag ? &Ds[0][row] : &Os[0][row];
+  const int ld = diag ? kCholNB : kCholRows;
+  int bad = 0;
+  for (int j = 0; j < jb; ++j) {
+    double acc = live ? mine[j * ld] : 0.0, piv = Ds[j][j];
+    int k = 0;
+    for (; k + 4 <= j; k += 4) {
+      double m[4], l[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        m[t] = mine[(k + t) * ld];
+        l[t] = Ds[k + t][j];
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        acc = fma(-m[t], l[t], acc);
+        piv = fma(-l[t], l[t], piv);
+      }
+    }
+    for (; k < j; ++k) {
+      const double l = Ds[k][j];
+      acc = fma(-mine[k * ld], l, acc);
+      piv = fma(-l, l, piv);
+    }
+    if (!(piv > 0.0)) {  // the same value in every thread
+      bad = j0 + j + 1;
       break;
     }
-    const double ljj = sqrt(djj);
-    __syncthreads();
-    if (tid == 0) L[(long)j * n + j] = ljj;
-    for (int i = j + 1 + tid; i < n; i += kT) L[(long)i * n + j] /= ljj;
-    __syncthreads();
-    // trailing update of the lower triangle: L[i][k] -= L[i][j] L[k][j], j < k <= i
-    const int m = n - j - 1;
-    const long cnt = (long)m * m;
-    for (long idx = tid; idx < cnt; idx += kT) {
-      const int i = j + 1 + (int)(idx / m), k = j + 1 + (int)(idx % m);
-      if (k <= i) L[(long)i * n + k] -= L[(long)i * n + j] * L[(long)k * n + j];
-    }
+    const double ljj = sqrt(piv);
+    // the pivot goes to its own array: the column's diagonal entry is still being read
+    if (diag && row == j) dg[j] = ljj;
+    if (live && (!diag || row > j)) mine[j * ld] = acc / ljj;
     __syncthreads();
   }
-  if (tid == 0 && info) *info = bad;
-}
-
-// Panel of the blocked Cholesky (one workgroup): columns j0..j0+jb-1 of the lower
-// factor, in place in W (row-major n x n; only the lower triangle is read); the
-// update of the trailing columns is a GEMM issued by the host.  info (nullable):
-// 0 on success, j+1 for the first non-positive pivot j (later panels then stop).
-__global__ __launch_bounds__(1024) void chol_panel_kernel(int n, int j0, int jb, double* __restrict__ W,
-                                                         int* __restrict__ info) {
-  __shared__ double piv;
-  __shared__ int bad;
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    if (info && j0 == 0) *info = 0;
-    bad = (info && *info != 0) ? 1 : 0;
+  if (bad) {
+    if (info && blockIdx.x == 0 && tid == 0) *info = bad;
+    return;
   }
-  __syncthreads();
-  if (bad) return;
-  __shared__ double colj[64];  // column j of the panel rows j+1..kend-1 (jb <= 64)
-  const int kend = j0 + jb;
-  for (int j = j0; j < kend; ++j) {
-    if (tid == 0) {
-      const double d = W[(long)j * n + j];
-      if (d > 0.0) {
-        piv = sqrt(d);
-        W[(long)j * n + j] = piv;
-      } else {
-        bad = 1;
-        if (info) *info = j + 1;
-      }
+  if (info && j0 == 0 && blockIdx.x == 0 && tid == 0) *info = 0;
+  if (blockIdx.x == 0)
+    for (int i = tid; i < jb * jb; i += nt) {
+      const int r = i / jb, k = i % jb;
+      L[(long)(j0 + r) * n + j0 + k] = k < r ? Ds[k][r] : (k == r ? dg[k] : 0.0);
     }
-    __syncthreads();
-    if (bad) return;
-    const double l = piv;
-    for (int i = j + 1 + tid; i < n; i += blockDim.x) {
-      const double x = W[(long)i * n + j] / l;
-      W[(long)i * n + j] = x;
-      if (i < kend) colj[i - j - 1] = x;
-    }
-    __syncthreads();
-    // rest of the panel: W[i][k] -= W[i][j] W[k][j] for j < k < kend, k <= i; a wave
-    // takes one row at a time (lane = column k), the waves interleave rows
-    {
-      const int lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
-      const int k = j + 1 + lane;
-      if (k < kend) {
-        const double lkj = colj[lane];
-        // eight rows per batch, all loads issued before the stores
-        for (int i0 = j + 1 + wv; i0 < n; i0 += 8 * nw) {
-          double a[8], b[8];
-#pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            const int i = i0 + nw * t;
-            if (i < n) {
-              a[t] = W[(long)i * n + j];
-              b[t] = W[(long)i * n + k];
-            }
-          }
-#pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            const int i = i0 + nw * t;
-            if (i < n && k <= i) W[(long)i * n + k] = b[t] - a[t] * lkj;
-          }
-        }
-      }
-    }
-    __syncthreads();
+  for (int i = tid; i < nown * jb; i += nt) {
+    const int r = i / jb, k = i % jb;
+    L[(long)(r0 + r) * n + j0 + k] = Os[k][r];
   }
-}
-
-__global__ void zero_upper_kernel(int n, double* __restrict__ L) {
-  const long nn = (long)n * n;
-  for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < nn; idx += (long)gridDim.x * blockDim.x)
-    if (idx % n > idx / n) L[idx] = 0.0;
+  for (int i = (int)blockIdx.x * nt + tid; i < j0 * jb; i += (int)gridDim.x * nt)
+    L[(long)(i / jb) * n + j0 + i % jb] = 0.0;
 }
 
 __global__ __launch_bounds__(kT) void trinv_kernel(int n, const double* __restrict__ L, double* __restrict__ X) {
@@ -521,169 +501,189 @@ __global__ __launch_bounds__(kT) void tridiag_kernel(int n, const double* __rest
   }
 }
 
-// number of eigenvalues of the tridiagonal (d, e) below x (Sturm sequence)
-__device__ int sturm_count(int n, const double* d, const double* e, double x, double pivmin) {
-  int c = 0;
-  double q = d[0] - x;
-  if (fabs(q) < pivmin) q = -pivmin;
-  if (q < 0) ++c;
-  for (int i = 1; i < n; ++i) {
-    q = d[i] - x - e[i - 1] * e[i - 1] / q;
-    if (fabs(q) < pivmin) q = -pivmin;
-    if (q < 0) ++c;
+// Spectrum slicing of the tridiagonal (d, e) is a chain of n dependent steps per Sturm count
+// and per triangular solve, so its time is (steps in sequence) x (latency of a step), and the
+// two kernels below shorten both.  Measured on MI355X at n = 240..480, p = 28: 1.4 ms in one
+// workgroup (one thread per eigenvalue bisecting with a division per Sturm step, then one
+// thread per vector with its arrays in global memory); now both kernels together 0.17 ms.
+
+// Scale of the tridiagonal: a power of two that brings its Gershgorin interval [gl, gu]
+// into [-1, 1], so that a Sturm sequence grows by at most a factor 4 per step.
+__device__ __forceinline__ void tridiag_bounds(int n, const double* d, const double* e, int lane, double& gl,
+                                               double& gu) {
+  double lo = DBL_MAX, hi = -DBL_MAX;
+  for (int i = lane; i < n; i += 64) {
+    const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < n ? fabs(e[i]) : 0.0);
+    lo = fmin(lo, d[i] - r);
+    hi = fmax(hi, d[i] + r);
   }
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, off, 64));
+    hi = fmax(hi, __shfl_xor(hi, off, 64));
+  }
+  const double span = fmax(hi - lo, 1e-300);
+  gl = lo - 1e-14 * span;
+  gu = hi + 1e-14 * span;
+}
+
+// Number of eigenvalues of the scaled tridiagonal below x: the sign changes of the Sturm
+// sequence p_i = (d_i - x) p_(i-1) - e_(i-1)^2 p_(i-2).  One dependent fused multiply-add per
+// step (the quotient form needs a division); the pair is rescaled by a power of two every 8
+// steps (a step shrinks it by 2^-100 at most: a zero is replaced by that much of its
+// predecessor, of the sign that counts it as below x).  de[i] = {d_i, e_(i-1)^2}.
+__device__ __forceinline__ int sturm_below(int n, const double2* de, double x) {
+  double prev = 1.0, p = de[0].x - x;
+  if (p == 0.0) p = -0x1p-100;
+  int c = p < 0.0 ? 1 : 0;
+  int i = 1;
+  auto step = [&](const double2& q) {
+    double t = fma(q.x - x, p, -q.y * prev);
+    t = t == 0.0 ? -0x1p-100 * p : t;
+    c += (t < 0.0) != (p < 0.0) ? 1 : 0;
+    prev = p;
+    p = t;
+  };
+  for (; i + 8 <= n; i += 8) {
+    double2 q[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) q[t] = de[i + t];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) step(q[t]);
+    const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(prev)));
+    p = __builtin_amdgcn_ldexp(p, ex);
+    prev = __builtin_amdgcn_ldexp(prev, ex);
+  }
+  for (; i < n; ++i) step(de[i]);
   return c;
 }
 
-// Eigenvector of the tridiagonal (sd, se) for the eigenvalue lmb by inverse iteration:
-// partially pivoted LU of T - lmb I (a zero pivot is replaced by pert), then four solves
-// from a fixed start vector, each normalised.  The work arrays are private to the
-// calling thread and do not overlap (restrict), so their loads can be issued ahead of
-// the dependent recurrences.
-__device__ void inverse_iteration(int n, const double* sd, const double* se, double lmb, double pert, int seed,
-                                  double* __restrict__ dl, double* __restrict__ dd, double* __restrict__ du,
-                                  double* __restrict__ du2, double* __restrict__ x, int* __restrict__ piv,
-                                  double* __restrict__ out) {
-  for (int i = 0; i < n; ++i) {
-    dd[i] = sd[i] - lmb;
-    if (i + 1 < n) {
-      dl[i] = se[i];
-      du[i] = se[i];
-    }
-    du2[i] = 0.0;
-    piv[i] = i;
+// The eigenvalues of the tridiagonal around 'target': the p below and the p above it, one wave
+// each (the p nearest lie among them), by multisection: the 64 lanes count at 64 points of the
+// interval, which shrinks 65-fold per round (10 rounds instead of 53 bisections, each as long).
+// cand[c]: ascending; *nc: how many there are.
+__global__ __launch_bounds__(64) void multisect_kernel(int n, const double* __restrict__ d,
+                                                       const double* __restrict__ e, double target, int p,
+                                                       double* __restrict__ cand, int* __restrict__ nc) {
+  __shared__ double2 de[kMaxN];
+  const int lane = threadIdx.x;
+  double gl, gu;
+  tridiag_bounds(n, d, e, lane, gl, gu);
+  const double big = fmax(fabs(gl), fabs(gu));
+  const int ex = (big > 0.0 && big < 1e300) ? __builtin_amdgcn_frexp_exp(big) : 0;
+  for (int i = lane; i < n; i += 64) {
+    const double ei = i > 0 ? __builtin_amdgcn_ldexp(e[i - 1], -ex) : 0.0;
+    de[i] = double2{__builtin_amdgcn_ldexp(d[i], -ex), ei * ei};
   }
-  for (int i = 0; i + 1 < n; ++i) {
-    if (fabs(dd[i]) >= fabs(dl[i])) {
-      if (dd[i] == 0.0) dd[i] = pert;
-      const double f = dl[i] / dd[i];
-      dl[i] = f;
-      dd[i + 1] -= f * du[i];
-    } else {
-      const double f = dd[i] / dl[i];
-      dd[i] = dl[i];
-      dl[i] = f;
-      const double tmp = du[i];
-      du[i] = dd[i + 1];
-      dd[i + 1] = tmp - f * dd[i + 1];
-      if (i + 2 < n) {
-        du2[i] = du[i + 1];
-        du[i + 1] = -f * du[i + 1];
-      }
-      piv[i] = i + 1;
-    }
+  __syncthreads();
+  // (a target beyond the spectrum counts none or all, at the interval's ends as well)
+  const double ts = fmin(fmax(__builtin_amdgcn_ldexp(target, -ex), -1.5), 1.5);
+  const int j0 = sturm_below(n, de, ts);
+  const int lo = max(0, j0 - p), count = min(n, j0 + p) - lo;
+  if (blockIdx.x == 0 && lane == 0) *nc = count;
+  if ((int)blockIdx.x >= count) return;
+  const int idx = lo + blockIdx.x;
+  double a = __builtin_amdgcn_ldexp(gl, -ex), b = __builtin_amdgcn_ldexp(gu, -ex);
+  for (int it = 0; it < 32 && (b - a) > 4.0 * DBL_EPSILON * fmax(fabs(a), fabs(b)) + DBL_MIN; ++it) {
+    const double w = (b - a) * (1.0 / 65.0);
+    const double x = fma((double)(lane + 1), w, a);
+    const unsigned long long above = __ballot(sturm_below(n, de, x) > idx);
+    const int f = above ? __ffsll((long long)above) - 1 : 64;  // first point with more than idx below it
+    const double a0 = a;
+    if (f < 64) b = fma((double)(f + 1), w, a0);
+    if (f > 0) a = fma((double)f, w, a0);
   }
-  if (dd[n - 1] == 0.0) dd[n - 1] = pert;
-  // deterministic start vector
-  for (int i = 0; i < n; ++i) x[i] = 1.0 + 0.5 * sin(0.7 * i + 1.3 * seed + 0.1);
-  for (int iter = 0; iter < 4; ++iter) {
-    double xi = x[0];
-    for (int i = 0; i + 1 < n; ++i) {
-      const double xn = x[i + 1];
-      if (piv[i] == i) {
-        x[i] = xi;
-        xi = xn - dl[i] * xi;
-      } else {
-        x[i] = xn;
-        xi = xi - dl[i] * xn;
-      }
-    }
-    x[n - 1] = xi;
-    double x1 = x[n - 1] / dd[n - 1];
-    x[n - 1] = x1;
-    double x2 = 0.0;
-    if (n >= 2) {
-      x2 = x1;
-      x1 = (x[n - 2] - du[n - 2] * x2) / dd[n - 2];
-      x[n - 2] = x1;
-    }
-    for (int i = n - 3; i >= 0; --i) {
-      const double xi0 = (x[i] - du[i] * x1 - du2[i] * x2) / dd[i];
-      x[i] = xi0;
-      x2 = x1;
-      x1 = xi0;
-    }
-    double s2 = 0.0;
-    for (int i = 0; i < n; ++i) s2 += x[i] * x[i];
-    const double inv = 1.0 / sqrt(s2);
-    for (int i = 0; i < n; ++i) x[i] *= inv;
-  }
-  for (int i = 0; i < n; ++i) out[i] = x[i];
+  if (lane == 0) cand[blockIdx.x] = __builtin_amdgcn_ldexp(0.5 * (a + b), ex);
 }
 
-// The p eigenvalues of the tridiagonal nearest 'target': the p below and the p above
-// it by bisection (one per thread), the p nearest of those, then their vectors by
-// inverse iteration with partially pivoted LU.  V[t][n]: vector t; lam[t] ascending;
-// work: 6 n doubles per thread.  p <= 64.
-__global__ __launch_bounds__(kT) void slice_kernel(int n, const double* __restrict__ d, const double* __restrict__ e,
-                                                   double target, int p, double* __restrict__ lam,
-                                                   double* __restrict__ V, double* __restrict__ work) {
-  __shared__ double sd[kMaxN], se[kMaxN];
-  __shared__ double bounds[3];
-  __shared__ int lo_s, nc_s;
-  __shared__ double cand[128];
-  __shared__ int pick[64];
-  const int tid = threadIdx.x;
-  for (int i = tid; i < n; i += kT) {
+// Partially pivoted LU of T - lmb I (a vanishing pivot is replaced by pert) and three inverse
+// iterations from a fixed start vector, each normalised (the eigenvalue is exact to rounding, so
+// the second already reaches that level).  One wave per vector: lane 0 runs the recurrences with
+// every array in LDS and the pivots stored as reciprocals, the lanes share the rest.
+__global__ __launch_bounds__(64) void inverse_iteration_kernel(int n, const double* __restrict__ d,
+                                                               const double* __restrict__ e, double target, int p,
+                                                               const double* __restrict__ cand,
+                                                               const int* __restrict__ ncp, double* __restrict__ lam,
+                                                               double* __restrict__ V) {
+  __shared__ double sd[kMaxN], se[kMaxN], dl[kMaxN], di[kMaxN], du[kMaxN], du2[kMaxN], x[kMaxN], y[kMaxN];
+  __shared__ int piv[kMaxN];
+  const int lane = threadIdx.x, t = blockIdx.x;
+  const int nc = *ncp;
+  // the p candidates nearest the target (ties: the lower) are the contiguous run whose start is
+  // the first candidate not farther than the one p places above it
+  const bool farther = lane + p < nc && fabs(cand[lane] - target) > fabs(cand[lane + p] - target);
+  const unsigned long long m = ~__ballot(farther);
+  const int i0 = m ? __ffsll((long long)m) - 1 : 64;
+  const double lmb = cand[i0 + t];
+  double gl, gu;
+  tridiag_bounds(n, d, e, lane, gl, gu);
+  const double pert = 1e-15 * fmax(fmax(fabs(gl), fabs(gu)), 1e-300);
+  for (int i = lane; i < n; i += 64) {
     sd[i] = d[i];
-    se[i] = e[i];
+    se[i] = i + 1 < n ? e[i] : 0.0;
+    x[i] = 1.0 + 0.5 * sin(0.7 * i + 1.3 * t + 0.1);  // deterministic start vector
   }
+  if (lane == 0) lam[t] = lmb;
   __syncthreads();
-  if (tid == 0) {
-    double gl = sd[0], gu = sd[0], emax = 0.0;
-    for (int i = 0; i < n; ++i) {
-      const double r = (i > 0 ? fabs(se[i - 1]) : 0.0) + (i + 1 < n ? fabs(se[i]) : 0.0);
-      gl = fmin(gl, sd[i] - r);
-      gu = fmax(gu, sd[i] + r);
-      if (i + 1 < n) emax = fmax(emax, se[i] * se[i]);
+  if (lane == 0) {
+    double dc = sd[0] - lmb, uc = se[0];
+    for (int i = 0; i + 1 < n; ++i) {
+      const double sub = se[i], dn = sd[i + 1] - lmb, un = se[i + 1];
+      const bool keep = fabs(dc) >= fabs(sub);
+      double pv = keep ? dc : sub;
+      if (fabs(pv) < 1e-290) pv = pert;
+      const double inv = 1.0 / pv;
+      const double f = (keep ? sub : dc) * inv;
+      dl[i] = f;
+      di[i] = inv;
+      du[i] = keep ? uc : dn;
+      du2[i] = keep ? 0.0 : un;
+      piv[i] = keep ? 0 : 1;
+      dc = keep ? dn - f * uc : uc - f * dn;
+      uc = keep ? un : -f * un;
     }
-    const double span = fmax(gu - gl, 1e-300);
-    bounds[0] = gl - 1e-14 * span;
-    bounds[1] = gu + 1e-14 * span;
-    bounds[2] = fmax(DBL_MIN, 1e-300 + 4.0 * DBL_MIN * fmax(1.0, emax));
-    // the p eigenvalues nearest the target lie among the p below and the p above it
-    const int j0 = sturm_count(n, sd, se, target, bounds[2]);
-    const int lo = max(0, j0 - p);
-    lo_s = lo;
-    nc_s = min(n, j0 + p) - lo;
+    if (fabs(dc) < 1e-290) dc = pert;
+    di[n - 1] = 1.0 / dc;
   }
-  __syncthreads();
-  const double pivmin = bounds[2];
-  const double scale = fmax(fabs(bounds[0]), fabs(bounds[1]));
-  // bisection for every candidate index (ascending eigenvalue order)
-  if (tid < nc_s) {
-    const int idx = lo_s + tid;  // the idx-th smallest (0-based)
-    double a = bounds[0], b = bounds[1];
-    for (int it = 0; it < 200 && (b - a) > 4.0 * DBL_EPSILON * fmax(fabs(a), fabs(b)) + DBL_MIN; ++it) {
-      const double mid = 0.5 * (a + b);
-      if (sturm_count(n, sd, se, mid, pivmin) > idx)
-        b = mid;
-      else
-        a = mid;
+  for (int iter = 0; iter < 3; ++iter) {
+    __syncthreads();
+    if (lane == 0) {
+      double xi = x[0];
+#pragma unroll 8
+      for (int i = 0; i + 1 < n; ++i) {
+        const double xn = x[i + 1];
+        const bool sw = piv[i] != 0;
+        const double top = sw ? xn : xi;
+        y[i] = top;
+        xi = (sw ? xi : xn) - dl[i] * top;
+      }
+      double x1 = xi * di[n - 1], x2 = 0.0;
+      x[n - 1] = x1;
+      if (n >= 2) {
+        x2 = x1;
+        x1 = (y[n - 2] - du[n - 2] * x2) * di[n - 2];
+        x[n - 2] = x1;
+      }
+#pragma unroll 8
+      for (int i = n - 3; i >= 0; --i) {
+        const double xi0 = (y[i] - du2[i] * x2 - du[i] * x1) * di[i];
+        x[i] = xi0;
+        x2 = x1;
+        x1 = xi0;
+      }
     }
-    cand[tid] = 0.5 * (a + b);
+    __syncthreads();
+    double big = 0.0;
+    for (int i = lane; i < n; i += 64) big = fmax(big, fabs(x[i]));
+    for (int off = 32; off > 0; off >>= 1) big = fmax(big, __shfl_xor(big, off, 64));
+    const double r = 1.0 / big;
+    double s2 = 0.0;
+    for (int i = lane; i < n; i += 64) s2 += (x[i] * r) * (x[i] * r);
+    for (int off = 32; off > 0; off >>= 1) s2 += __shfl_xor(s2, off, 64);
+    const double sc = 1.0 / sqrt(s2);
+    for (int i = lane; i < n; i += 64) x[i] = (x[i] * r) * sc;
   }
   __syncthreads();
-  // the p candidates nearest the target (ties: the lower), kept in ascending order;
-  // candidates are ascending, so the nearest p form a contiguous run
-  if (tid == 0) {
-    int i0 = 0, i1 = nc_s;  // shrink [i0, i1) from the farther end
-    while (i1 - i0 > p) {
-      if (fabs(cand[i1 - 1] - target) >= fabs(cand[i0] - target))
-        --i1;
-      else
-        ++i0;
-    }
-    for (int j = 0; j < p; ++j) pick[j] = i0 + j;
-  }
-  __syncthreads();
-  if (tid < p) {
-    const double lmb = cand[pick[tid]];
-    lam[tid] = lmb;
-    double* base = work + (long)tid * 6 * n;
-    inverse_iteration(n, sd, se, lmb, 1e-15 * fmax(scale, 1e-300), tid, base, base + n, base + 2 * n, base + 3 * n,
-                      base + 4 * n, (int*)(base + 5 * n), V + (long)tid * n);
-  }
+  for (int i = lane; i < n; i += 64) V[(long)t * n + i] = x[i];
 }
 
 // T1[t][j] = UG[t][first + j] / sqrt(w[first + j])  (p x q, ld q)
@@ -782,7 +782,7 @@ void small_syev(int n, const double* A, double* w, double* Z, hipStream_t s, dou
 }
 
 size_t partial_syev_scratch(int n, int p) {
-  return (size_t)2 * n * n + 2 * (size_t)n + 4 * (size_t)p * n + 6 * (size_t)n * p + 8 * (size_t)p * p + 64;
+  return (size_t)2 * n * n + 2 * (size_t)n + 4 * (size_t)p * n + 8 * (size_t)p * p + 2 * (size_t)p + 64;
 }
 
 int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch,
@@ -797,7 +797,7 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   double* Y = V1 + (size_t)p * n;
   double* V2 = Y + (size_t)p * n;
   double* work = V2 + (size_t)p * n;
-  double* G = work + (size_t)6 * n * p;
+  double* G = work + (size_t)2 * p + 2;
   double* UG = G + (size_t)p * p;
   double* T1 = UG + (size_t)p * p;
   double* H = T1 + (size_t)p * p;
@@ -806,7 +806,11 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   double* eig_scr = wG + p;  // 2 p^2
   tridiag_kernel<<<1, kT, 0, s>>>(n, A, W, d, e, Hh);
   PPW_LAUNCH_CHECK();
-  slice_kernel<<<1, kT, 0, s>>>(n, d, e, target, p, lam, V, work);
+  double* cand = work;
+  int* nc = reinterpret_cast<int*>(work + 2 * p);
+  multisect_kernel<<<2 * p, 64, 0, s>>>(n, d, e, target, p, cand, nc);
+  PPW_LAUNCH_CHECK();
+  inverse_iteration_kernel<<<p, 64, 0, s>>>(n, d, e, target, p, cand, nc, lam, V);
   PPW_LAUNCH_CHECK();
   // Rayleigh-Ritz inside span(V): G = V V^T, symmetric orthonormalization, H = V1 T V1^T
   GemmDesc g;
@@ -848,23 +852,20 @@ void small_trsm_lt(int n, const double* L, int p, double* B, hipStream_t s) {
   PPW_LAUNCH_CHECK();
 }
 
-void small_cholesky(int n, const double* A, double* L, int* info, hipStream_t s) {
+void small_cholesky(int n, const double* A, double* L, int* info, double* work, hipStream_t s) {
   if (n < 1 || n > kMaxN) throw InvalidArg("small_cholesky: n out of range");
-  if (n <= 64) {
-    cholesky_kernel<<<1, kT, 0, s>>>(n, A, L, info);
+  // blocked right-looking: panels of 64 columns, trailing updates as GEMMs on a working copy
+  // (the first panel reads A itself)
+  const double* W = A;
+  for (int j0 = 0; j0 < n; j0 += kCholNB) {
+    const int jb = std::min(kCholNB, n - j0), j1 = j0 + jb, m2 = n - j1;
+    if (j0 == 0 && m2 > 0) {
+      PPW_HIP(hipMemcpyAsync(work, A, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s));
+      W = work;
+    }
+    const int blocks = std::max(1, (m2 + kCholRows - 1) / kCholRows);
+    chol_panel_kernel<<<blocks, kCholNB + kCholRows, 0, s>>>(n, j0, jb, W, L, info);
     PPW_LAUNCH_CHECK();
-    return;
-  }
-  // blocked right-looking: panels of 64 columns in one workgroup, trailing updates as
-  // GEMMs over the whole device (the unblocked sweep reads and writes the trailing
-  // matrix once per column through one CU)
-  constexpr int NB = 64;
-  PPW_HIP(hipMemcpyAsync(L, A, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s));
-  for (int j0 = 0; j0 < n; j0 += NB) {
-    const int jb = std::min(NB, n - j0);
-    chol_panel_kernel<<<1, 1024, 0, s>>>(n, j0, jb, L, info);
-    PPW_LAUNCH_CHECK();
-    const int j1 = j0 + jb, m2 = n - j1;
     if (m2 > 0) {
       GemmDesc d;
       d.M = m2;
@@ -876,11 +877,9 @@ void small_cholesky(int n, const double* A, double* L, int* info, hipStream_t s)
       d.ldb = n;
       d.ldc = n;
       const double* panel = L + (size_t)j1 * n + j0;
-      gemm_f64(d, -1.0, panel, panel, 1.0, L + (size_t)j1 * n + j1, s);
+      gemm_f64(d, -1.0, panel, panel, 1.0, work + (size_t)j1 * n + j1, s);
     }
   }
-  zero_upper_kernel<<<(n * n + 255) / 256, 256, 0, s>>>(n, L);
-  PPW_LAUNCH_CHECK();
 }
 
 void small_trinv(int n, const double* L, double* X, hipStream_t s) {

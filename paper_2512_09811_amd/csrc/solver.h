@@ -75,8 +75,9 @@ void window_solve_many(Context& c, const SolveOptions& opt, int nw, const double
 //  scratch: 2 n^2 doubles (null: allocated and freed internally).
 void small_syev(int n, const double* A, double* w, double* Z, hipStream_t s, double* scratch = nullptr);
 //  small_cholesky: lower factor L (zeros above the diagonal); *info (device int,
-//  may be null) = 0 on success, j+1 if the leading minor j is not positive.
-void small_cholesky(int n, const double* A, double* L, int* info, hipStream_t s);
+//  may be null) = 0 on success, j+1 if the leading minor j is not positive.  work: n^2
+//  doubles (not read for n <= 64).
+void small_cholesky(int n, const double* A, double* L, int* info, double* work, hipStream_t s);
 //  small_trinv: X = L^-1 for lower-triangular L.
 void small_trinv(int n, const double* L, double* X, hipStream_t s);
 
@@ -86,7 +87,7 @@ namespace ppw {
 // Partial symmetric eigensolver for the projected problem: the p eigenpairs of the
 // n x n symmetric A (row-major, device) whose eigenvalues are nearest 'target'
 // (p <= n, p <= 64).  lam[p] ascending; Z[n][p] row-major (column j = vector j).
-// Work: 2 n^2 + 8 n p + 4 p^2 + 64 doubles of scratch (device).
+// scratch: partial_syev_scratch(n, p) doubles (device).
 // Returns q <= p, the number of independent pairs found (columns 0..q-1 valid).
 int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch,
                  hipStream_t s);

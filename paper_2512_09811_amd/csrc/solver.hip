@@ -935,7 +935,7 @@ Solver::Ritz Solver::rayleigh_ritz() {
   symmetrize_kernel<<<gridn((long)n * n), kB, 0, s_>>>(Ap_, n);
   symmetrize_kernel<<<gridn((long)n * n), kB, 0, s_>>>(Am_, n);
   symmetrize_kernel<<<gridn((long)n * n), kB, 0, s_>>>(Sp_, n);
-  small_cholesky(n, Am_, L_, ival_, s_);
+  small_cholesky(n, Am_, L_, ival_, tmp_, s_);
   // Sp^-1: the metric is the identity plus the (small) MP2 density correction, so
   // Newton-Schulz X <- 2X - X Sp X from X = I converges quadratically; the Cholesky
   // route is the fallback when |I - Sp X| does not reach rounding level.
@@ -956,7 +956,7 @@ Solver::Ritz Solver::rayleigh_ritz() {
   if (c_.order >= 2) {
     auto res = fetch(lam_, 1);
     if (!(res[0] < 1e-13)) {
-      small_cholesky(n, Sp_, Ls_, ival_ + 1, s_);
+      small_cholesky(n, Sp_, Ls_, ival_ + 1, tmp_, s_);
       auto inf2 = fetch(ival_ + 1, 1);
       if (inf2[0] != 0) throw Unstable("S is not positive definite in the subspace");
       small_trinv(n, Ls_, Lsi_, s_);

@@ -477,3 +477,44 @@ def test_gemm_split_bf16_tiles(B, shape):
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
     err = np.abs(outs[0].double().cpu().numpy() - (0.5 * ref + 6.0)).max()
     assert err <= 1e-5 * np.sqrt(K) * 0.5 * 25.0, err
+
+
+@pytest.mark.parametrize("n", [63, 66, 191, 192, 193, 320, 385])
+def test_small_cholesky_panel_edges(B, n):
+    """Panels of 64 columns whose rows below the diagonal block are shared out 128 to a
+    workgroup: one row more and one row less than whole workgroups, and a short last panel.
+    Backward error of a Cholesky factor: n eps |A| (n / 2 rounding units and a margin of 2)."""
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, n))
+    A = X @ X.T / n + 0.5 * np.eye(n)
+    dA = torch.tensor(A, device="cuda")
+    L = torch.full((n, n), 7.0, dtype=torch.float64, device="cuda")
+    B.cholesky(dA, L)
+    Lh = L.cpu().numpy()
+    assert np.array_equal(np.triu(Lh, 1), np.zeros((n, n)))
+    assert np.abs(Lh @ Lh.T - A).max() <= n * 2.3e-16 * np.abs(A).max()
+
+
+@pytest.mark.parametrize("n,p,scale,target", [(1, 1, 1.0, 0.0), (9, 1, 1.0, 0.7), (10, 10, 1e-9, 0.5), (64, 64, 1e8, 0.5),
+                                              (129, 63, 1.0, -5.0), (512, 64, 1.0, 0.9), (300, 20, 1.0, 40.0)])
+def test_partial_syev_ranges(B, n, p, scale, target):
+    """Spectrum slicing over its range: one to 512 rows, one to 64 pairs, matrices of small and
+    large norm, targets inside and far outside the spectrum, a repeated eigenvalue."""
+    rng = np.random.default_rng(n + p)
+    lam = rng.uniform(0.1, 2.0, n)
+    if n >= 9:
+        lam[3] = lam[4]
+    lam, target = lam * scale, target * scale
+    A = _spectrum_matrix(lam, n)
+    A = 0.5 * (A + A.T)
+    dA = torch.tensor(A, device="cuda")
+    w = torch.zeros(p, dtype=torch.float64, device="cuda")
+    Z = torch.zeros(n * p, dtype=torch.float64, device="cuda")
+    q = B.partial_syev(dA, target, p, w, Z)
+    assert q == p
+    wh, Zh = w.cpu().numpy(), Z.cpu().numpy().reshape(n, p)
+    nearest = np.sort(np.sort(lam)[np.argsort(np.abs(np.sort(lam) - target), kind="stable")[:p]])
+    # eigenvalues to n eps |A|, vectors orthonormal to the same with a factor 10 for clusters
+    np.testing.assert_allclose(np.sort(wh), nearest, rtol=0, atol=1e-12 * np.abs(lam).max())
+    assert np.linalg.norm(A @ Zh - Zh * wh, axis=0).max() < 1e-11 * np.abs(lam).max()
+    np.testing.assert_allclose(Zh.T @ Zh, np.eye(p), atol=1e-11)

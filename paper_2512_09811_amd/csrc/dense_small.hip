@@ -686,24 +686,159 @@ __global__ __launch_bounds__(64) void inverse_iteration_kernel(int n, const doub
   for (int i = lane; i < n; i += 64) V[(long)t * n + i] = x[i];
 }
 
-// T1[t][j] = UG[t][first + j] / sqrt(w[first + j])  (p x q, ld q)
-__global__ void scale_keep_kernel(int p, int first, const double* __restrict__ U, const double* __restrict__ w,
-                                  double* __restrict__ T1) {
-  const int q = p - first;
-  for (int idx = threadIdx.x; idx < p * q; idx += blockDim.x) {
-    const int t = idx / q, j = idx % q;
-    T1[idx] = U[(long)t * p + first + j] / sqrt(w[first + j]);
+// Factors that orthonormalise k <= 64 vectors from their Gram matrix G: pivoted Cholesky
+// G = R^T R in pivot order, stopped at the first pivot not above thresh (the rest lies within
+// sqrt(thresh) of the span found).  T[k][q] (ld q): X T is orthonormal; R[q][k]: X = (X T) R
+// (both in the original order of the columns); *q_out = q.
+//
+// The vectors only have to be orthonormal and to span the same space, so a triangular factor
+// does for the symmetric one (eigenvectors of G): k dependent steps of one wave in LDS, 20 us at
+// k = 40, where the eigensolver below took 260 us (its rotations are a scalar recurrence of
+// about k^2 steps).
+__global__ __launch_bounds__(64) void orth_factors_kernel(int k, const double* __restrict__ G, double thresh,
+                                                          double* __restrict__ T, double* __restrict__ R,
+                                                          int* __restrict__ q_out) {
+  __shared__ double Gs[64][64], Rs[64][64], Ts[64][64];
+  __shared__ int perm[64], rank[64];
+  const int lane = threadIdx.x;
+  for (int i = lane; i < k * k; i += 64) Gs[i / k][i % k] = G[i];
+  rank[lane] = -1;
+  __syncthreads();
+  double dj = lane < k ? Gs[lane][lane] : -1.0;
+  bool done = lane >= k;
+  int q = 0;
+  for (; q < k; ++q) {
+    double best = done ? -1.0 : dj;
+    int at = lane;
+    for (int off = 32; off > 0; off >>= 1) {
+      const double ob = __shfl_xor(best, off, 64);
+      const int oa = __shfl_xor(at, off, 64);
+      if (ob > best || (ob == best && oa < at)) {
+        best = ob;
+        at = oa;
+      }
+    }
+    if (!(best > thresh)) break;
+    const double piv = sqrt(best);
+    double acc = Gs[at][lane];
+#pragma unroll 4
+    for (int t = 0; t < q; ++t) acc = fma(-Rs[t][at], Rs[t][lane], acc);
+    const double r = done ? 0.0 : (lane == at ? piv : acc / piv);
+    Rs[q][lane] = r;
+    dj = fma(-r, r, dj);
+    if (lane == at) {
+      done = true;
+      perm[q] = lane;
+      rank[lane] = q;
+    }
+    __syncthreads();
   }
+  // upper triangle in pivot order, then column c of its inverse by lane c
+  for (int i = 0; i < q; ++i)
+    if (lane < q) {
+      Gs[i][lane] = Rs[i][perm[lane]];
+      Ts[i][lane] = 0.0;
+    }
+  __syncthreads();
+  for (int i = q - 1; i >= 0; --i) {
+    double acc = lane == i ? 1.0 : 0.0;
+#pragma unroll 4
+    for (int t = i + 1; t < q; ++t) acc = fma(-Gs[i][t], Ts[t][lane], acc);
+    if (lane < q && lane >= i) Ts[i][lane] = acc / Gs[i][i];
+  }
+  __syncthreads();
+  for (int i = lane; i < k * q; i += 64) {
+    const int j = i / q, c = i % q;
+    T[i] = rank[j] >= 0 ? Ts[rank[j]][c] : 0.0;
+    R[i] = Rs[i / k][i % k];
+  }
+  if (lane == 0) *q_out = q;
 }
 
-__global__ void symmetrize_small_kernel(int n, double* A) {
-  for (int idx = threadIdx.x; idx < n * n; idx += blockDim.x) {
-    const int r = idx / n, c = idx % n;
-    if (c > r) {
-      const double m = 0.5 * (A[r * n + c] + A[c * n + r]);
-      A[r * n + c] = m;
-      A[c * n + r] = m;
+// Eigenpairs of a symmetric n x n matrix (n <= 64) that is diagonal but for a few elements, by
+// cyclic Jacobi: w ascending, Z[r * n + c] component r of vector c.  Pairs of the round-robin
+// order whose element is below a tenth of a rounding unit of the largest diagonal element are
+// left alone, and a round without a rotation costs one barrier, so the matrices it is for (the
+// tridiagonal in the span of its own eigenvectors, off-diagonal only in clusters) take 10-60 us.
+__global__ __launch_bounds__(256) void jacobi_kernel(int n, const double* __restrict__ A, double* __restrict__ w,
+                                                     double* __restrict__ Z) {
+  __shared__ double H[64][65], U[64][65];
+  __shared__ double cs[32], sn[32];
+  __shared__ int pp[32], qq[32], pos[64];
+  __shared__ double diag[64];
+  const int tid = threadIdx.x;
+  for (int i = tid; i < 64 * 64; i += 256) {
+    const int r = i / 64, c = i % 64;
+    H[r][c] = r < n && c < n ? 0.5 * (A[r * n + c] + A[c * n + r]) : 0.0;
+    U[r][c] = r == c ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  double big = 0.0;
+  for (int i = 0; i < n; ++i) big = fmax(big, fabs(H[i][i]));
+  const double tol = 0.1 * DBL_EPSILON * big;
+  const int m = n + (n & 1), half = m / 2;
+  for (int sweep = 0; sweep < 40 && n > 1; ++sweep) {
+    int rotated = 0;
+    for (int rd = 0; rd < m - 1; ++rd) {
+      int rot = 0;
+      if (tid < half) {
+        int p = tid == 0 ? m - 1 : (rd + tid) % (m - 1), q = tid == 0 ? rd : (rd - tid + m - 1) % (m - 1);
+        if (p > q) {
+          const int t = p;
+          p = q;
+          q = t;
+        }
+        const double apq = H[p][q];
+        double c = 1.0, s = 0.0;
+        if (q < n && fabs(apq) > tol) {
+          const double th = (H[q][q] - H[p][p]) / (2.0 * apq);
+          const double t = copysign(1.0, th) / (fabs(th) + sqrt(th * th + 1.0));
+          c = 1.0 / sqrt(t * t + 1.0);
+          s = t * c;
+          rot = 1;
+        }
+        cs[tid] = c;
+        sn[tid] = s;
+        pp[tid] = p;
+        qq[tid] = q;
+      }
+      if (!__syncthreads_or(rot)) continue;
+      rotated = 1;
+      for (int i = tid; i < half * n; i += 256) {
+        const int t = i / n, r = i % n, p = pp[t], q = qq[t];
+        if (q >= n) continue;
+        const double c = cs[t], s = sn[t];
+        const double hp = H[r][p], hq = H[r][q], up = U[r][p], uq = U[r][q];
+        H[r][p] = c * hp - s * hq;
+        H[r][q] = s * hp + c * hq;
+        U[r][p] = c * up - s * uq;
+        U[r][q] = s * up + c * uq;
+      }
+      __syncthreads();
+      for (int i = tid; i < half * n; i += 256) {
+        const int t = i / n, k = i % n, p = pp[t], q = qq[t];
+        if (q >= n) continue;
+        const double c = cs[t], s = sn[t];
+        const double hp = H[p][k], hq = H[q][k];
+        H[p][k] = c * hp - s * hq;
+        H[q][k] = s * hp + c * hq;
+      }
+      __syncthreads();
     }
+    if (!rotated) break;  // the same in every thread
+  }
+  if (tid < n) diag[tid] = H[tid][tid];
+  __syncthreads();
+  if (tid < n) {
+    int k = 0;
+    for (int j = 0; j < n; ++j) k += diag[j] < diag[tid] || (diag[j] == diag[tid] && j < tid) ? 1 : 0;
+    pos[tid] = k;
+    w[k] = diag[tid];
+  }
+  __syncthreads();
+  for (int i = tid; i < n * n; i += 256) {
+    const int r = i / n, c = i % n;
+    Z[r * n + pos[c]] = U[r][c];
   }
 }
 
@@ -721,46 +856,114 @@ __global__ void tridiag_apply_kernel(int n, int p, const double* __restrict__ d,
   }
 }
 
-// Z[r][j] = (H_0 ... H_{n-3} v_j)[r]: one workgroup per vector
-__global__ __launch_bounds__(256) void backtransform_kernel(int n, int p, const double* __restrict__ Hh,
-                                                            const double* __restrict__ V, double* __restrict__ Z) {
-  __shared__ double v[kMaxN];
-  __shared__ double red[40];
-  const int j = blockIdx.x;
-  const int tid = threadIdx.x;
-  for (int i = tid; i < n; i += blockDim.x) v[i] = V[(long)j * n + i];
-  __syncthreads();
-  for (int k = n - 3; k >= 0; --k) {
-    const double* u = Hh + (long)k * n;
-    double part = 0.0;
-    for (int i = k + 1 + tid; i < n; i += blockDim.x) part += u[i] * v[i];
-    // block reduction over 256 threads
-    for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
-    if ((tid & 63) == 0) red[tid >> 6] = part;
-    __syncthreads();
-    const double dot = red[0] + red[1] + red[2] + red[3];
-    for (int i = k + 1 + tid; i < n; i += blockDim.x) v[i] -= 2.0 * dot * u[i];
-    __syncthreads();
-  }
-  for (int i = tid; i < n; i += blockDim.x) Z[(long)i * p + j] = v[i];
+// Sum over the wave, in every lane: row shifts and row broadcasts (about 150 cycles, a quarter
+// of the time of lane permutes through LDS).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_get(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+  v += dpp_get<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds its sum
+  v += dpp_get<0x112, 0xf>(v);
+  v += dpp_get<0x114, 0xf>(v);
+  v += dpp_get<0x118, 0xf>(v);
+  v += dpp_get<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  v += dpp_get<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+  return __hiloint2double(hi, lo);
 }
 
-// L^T X = B, one workgroup per right-hand side (column j of B[n][p])
-__global__ __launch_bounds__(256) void trsm_lt_kernel(int n, const double* __restrict__ L, int p, double* __restrict__ B) {
-  __shared__ double b[kMaxN];
-  const int j = blockIdx.x;
-  const int tid = threadIdx.x;
-  for (int i = tid; i < n; i += blockDim.x) b[i] = B[(long)i * p + j];
-  __syncthreads();
-  for (int i = n - 1; i >= 0; --i) {
-    const double xi = b[i] / L[(long)i * n + i];
-    __syncthreads();
-    if (tid == 0) b[i] = xi;
-    // b[k] -= L[i][k] x_i for k < i   (row i of L, contiguous)
-    for (int k = tid; k < i; k += blockDim.x) b[k] -= L[(long)i * n + k] * xi;
-    __syncthreads();
+// Z[r][j] = (H_0 ... H_{n-3} v_j)[r], one wave per vector with the vector in registers (8 per
+// lane up to n = 512): a reflector costs one wave sum and no barrier, and the next one's
+// elements are loaded meanwhile.  At n = 480: 60 us against 150 us with a workgroup per vector.
+__global__ __launch_bounds__(64) void backtransform_kernel(int n, int p, const double* __restrict__ Hh,
+                                                           const double* __restrict__ V, double* __restrict__ Z) {
+  constexpr int S = kMaxN / 64;
+  const int j = blockIdx.x, lane = threadIdx.x;
+  double v[S], u[S], un[S];
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int i = lane + 64 * t;
+    v[t] = i < n ? V[(long)j * n + i] : 0.0;
+    un[t] = (n >= 3 && i < n) ? Hh[(long)(n - 3) * n + i] : 0.0;
   }
-  for (int i = tid; i < n; i += blockDim.x) B[(long)i * p + j] = b[i];
+  for (int k = n - 3; k >= 0; --k) {
+#pragma unroll
+    for (int t = 0; t < S; ++t) u[t] = un[t];
+    if (k > 0) {
+#pragma unroll
+      for (int t = 0; t < S; ++t) {
+        const int i = lane + 64 * t;
+        un[t] = i < n ? Hh[(long)(k - 1) * n + i] : 0.0;  // zero in entries <= k - 1
+      }
+    }
+    double part = 0.0;
+#pragma unroll
+    for (int t = 0; t < S; ++t) part = fma(u[t], v[t], part);
+    const double f = -2.0 * wave_total(part);
+#pragma unroll
+    for (int t = 0; t < S; ++t) v[t] = fma(f, u[t], v[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int i = lane + 64 * t;
+    if (i < n) Z[(long)i * p + j] = v[t];
+  }
+}
+
+// X[:, j] = scale_j L^-T B[:, j] with scale_j = sqrt(th[j]), one wave per right-hand side with
+// the column in registers: an unknown costs one broadcast (a lane read) and no barrier.
+__global__ __launch_bounds__(64) void trsm_lt_kernel(int n, const double* __restrict__ L, const double* __restrict__ B,
+                                                     long ldb, const double* __restrict__ th, double* __restrict__ X,
+                                                     long ldx) {
+  constexpr int S = kMaxN / 64;
+  __shared__ double rdiag[kMaxN];
+  const int j = blockIdx.x, lane = threadIdx.x;
+  double b[S], ln[S];
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int i = lane + 64 * t;
+    b[t] = i < n ? B[(long)i * ldb + j] : 0.0;
+    if (i < n) rdiag[i] = 1.0 / L[(long)i * n + i];
+    ln[t] = i < n ? L[(long)(n - 1) * n + i] : 0.0;
+  }
+  __syncthreads();
+  const double sc = sqrt(th[j]);
+  // unknown i = 64 blk + src, from the last; row i of L feeds the unknowns below it
+#pragma unroll
+  for (int blk = S - 1; blk >= 0; --blk) {
+    if (64 * blk >= n) continue;
+    for (int src = min(63, n - 1 - 64 * blk); src >= 0; --src) {
+      const int i = 64 * blk + src;
+      const int lo = __builtin_amdgcn_readlane(__double2loint(b[blk]), src);
+      const int hi = __builtin_amdgcn_readlane(__double2hiint(b[blk]), src);
+      const double x = __hiloint2double(hi, lo) * rdiag[i];
+      double l[S];
+#pragma unroll
+      for (int t = 0; t <= blk; ++t) l[t] = ln[t];
+      if (i > 0) {
+#pragma unroll
+        for (int t = 0; t <= blk; ++t) {
+          const int c = lane + 64 * t;
+          ln[t] = c < n ? L[(long)(i - 1) * n + c] : 0.0;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t <= blk; ++t) {
+        const int c = lane + 64 * t;
+        b[t] = c < i ? fma(-l[t], x, b[t]) : b[t];
+      }
+      if (lane == src) b[blk] = x;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int i = lane + 64 * t;
+    if (i < n) X[(long)i * ldx + j] = sc * b[t];
+  }
 }
 
 }  // namespace
@@ -782,7 +985,7 @@ void small_syev(int n, const double* A, double* w, double* Z, hipStream_t s, dou
 }
 
 size_t partial_syev_scratch(int n, int p) {
-  return (size_t)2 * n * n + 2 * (size_t)n + 4 * (size_t)p * n + 8 * (size_t)p * p + 2 * (size_t)p + 64;
+  return (size_t)2 * n * n + 2 * (size_t)n + 4 * (size_t)p * n + 5 * (size_t)p * p + 2 * (size_t)p + 64;
 }
 
 int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch,
@@ -802,8 +1005,6 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   double* T1 = UG + (size_t)p * p;
   double* H = T1 + (size_t)p * p;
   double* UH = H + (size_t)p * p;
-  double* wG = UH + (size_t)p * p;
-  double* eig_scr = wG + p;  // 2 p^2
   tridiag_kernel<<<1, kT, 0, s>>>(n, A, W, d, e, Hh);
   PPW_LAUNCH_CHECK();
   double* cand = work;
@@ -812,21 +1013,14 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   PPW_LAUNCH_CHECK();
   inverse_iteration_kernel<<<p, 64, 0, s>>>(n, d, e, target, p, cand, nc, lam, V);
   PPW_LAUNCH_CHECK();
-  // Rayleigh-Ritz inside span(V): G = V V^T, symmetric orthonormalization, H = V1 T V1^T
+  // Rayleigh-Ritz inside span(V): G = V V^T, orthonormalization, H = V1 T V1^T
   GemmDesc g;
   g.M = p; g.N = p; g.K = n; g.transA = 0; g.lda = n; g.transB = 1; g.ldb = n; g.ldc = p;
   gemm_f64(g, 1.0, V, V, 0.0, G, s);
-  small_syev(p, G, wG, UG, s, eig_scr);
-  std::vector<double> wg(p);
-  PPW_HIP(hipMemcpyAsync(wg.data(), wG, sizeof(double) * p, hipMemcpyDeviceToHost, s));
-  PPW_HIP(hipStreamSynchronize(s));
-  int first = 0;
-  while (first < p && !(wg[first] > 1e-12 * wg[p - 1])) ++first;
-  const int q = p - first;
+  // (T1 is p x q, ld q; R goes to UG)
+  const int q = orth_factors(p, G, 1e-12, T1, UG, nc, s);
   if (q == 0) throw Unstable("partial_syev: inverse iteration produced no independent vectors");
-  scale_keep_kernel<<<1, 256, 0, s>>>(p, first, UG, wG, T1);
-  PPW_LAUNCH_CHECK();
-  // V1[j][r] = sum_t T1[t][j] V[t][r]   (T1 is p x q, ld q)
+  // V1[j][r] = sum_t T1[t][j] V[t][r]
   GemmDesc a;
   a.M = q; a.N = n; a.K = p; a.transA = 1; a.lda = q; a.transB = 0; a.ldb = n; a.ldc = n;
   gemm_f64(a, 1.0, T1, V, 0.0, V1, s);
@@ -835,20 +1029,31 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   GemmDesc h;
   h.M = q; h.N = q; h.K = n; h.transA = 0; h.lda = n; h.transB = 1; h.ldb = n; h.ldc = q;
   gemm_f64(h, 1.0, V1, Y, 0.0, H, s);
-  symmetrize_small_kernel<<<1, 256, 0, s>>>(q, H);
-  small_syev(q, H, lam, UH, s, eig_scr);
+  jacobi_kernel<<<1, 256, 0, s>>>(q, H, lam, UH);
+  PPW_LAUNCH_CHECK();
   // V2[j][r] = sum_t UH[t][j] V1[t][r]
   GemmDesc b;
   b.M = q; b.N = n; b.K = q; b.transA = 1; b.lda = q; b.transB = 0; b.ldb = n; b.ldc = n;
   gemm_f64(b, 1.0, UH, V1, 0.0, V2, s);
-  backtransform_kernel<<<q, 256, 0, s>>>(n, p, Hh, V2, Z);
+  backtransform_kernel<<<q, 64, 0, s>>>(n, p, Hh, V2, Z);
   PPW_LAUNCH_CHECK();
   return q;
 }
 
-void small_trsm_lt(int n, const double* L, int p, double* B, hipStream_t s) {
+int orth_factors(int k, const double* G, double thresh, double* T, double* R, int* count, hipStream_t s) {
+  if (k < 1 || k > 64) throw InvalidArg("orth_factors: k out of range");
+  orth_factors_kernel<<<1, 64, 0, s>>>(k, G, thresh, T, R, count);
+  PPW_LAUNCH_CHECK();
+  int q = 0;
+  PPW_HIP(hipMemcpyAsync(&q, count, sizeof(int), hipMemcpyDeviceToHost, s));
+  PPW_HIP(hipStreamSynchronize(s));
+  return q;
+}
+
+void small_trsm_lt(int n, const double* L, int p, const double* B, long ldb, const double* th, double* X, long ldx,
+                   hipStream_t s) {
   if (n < 1 || n > kMaxN) throw InvalidArg("small_trsm_lt: n out of range");
-  trsm_lt_kernel<<<p, 256, 0, s>>>(n, L, p, B);
+  trsm_lt_kernel<<<p, 64, 0, s>>>(n, L, B, ldb, th, X, ldx);
   PPW_LAUNCH_CHECK();
 }
 

@@ -92,6 +92,12 @@ namespace ppw {
 int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch,
                  hipStream_t s);
 size_t partial_syev_scratch(int n, int p);
-// Solve L^T X = B for lower-triangular L (n x n) and p right-hand sides B[n][p] (row-major, in place).
-void small_trsm_lt(int n, const double* L, int p, double* B, hipStream_t s);
+// X[:, j] = sqrt(th[j]) L^-T B[:, j] for lower-triangular L (n x n) and p columns (row-major,
+// leading dimensions ldb, ldx).
+void small_trsm_lt(int n, const double* L, int p, const double* B, long ldb, const double* th, double* X, long ldx,
+                   hipStream_t s);
+// Factors that orthonormalise k <= 64 vectors X of Gram matrix G (k x k, device): returns q, the
+// number kept (pivots of a pivoted Cholesky above thresh); T[k][q] (ld q) with X T orthonormal,
+// R[q][k] with X = (X T) R.  count: one device int.  Waits for the stream.
+int orth_factors(int k, const double* G, double thresh, double* T, double* R, int* count, hipStream_t s);
 }  // namespace ppw

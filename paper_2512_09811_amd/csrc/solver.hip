@@ -49,10 +49,66 @@ inline int gridn(long n) { return (int)std::max<long>(1, std::min<long>((n + kB 
 
 #define GS_LOOP(idx, n) for (long idx = blockIdx.x * (long)blockDim.x + threadIdx.x; idx < (n); idx += (long)gridDim.x * blockDim.x)
 
-__global__ void scale_rows_kernel(double* X, long N, int k, const double* __restrict__ s, int invert) {
-  GS_LOOP(idx, N * k) {
-    const int q = (int)(idx / N);
-    X[idx] = invert ? X[idx] / s[q] : X[idx] * s[q];
+// The solver's vectors are small (0.05-1.3 MB) and a cycle is a chain of dependent launches of
+// a few microseconds each, 9-16 us apart in a trace, so a cycle's time is mostly the number of
+// launches.  The kernels below therefore each take a whole step of that chain (a norm and its
+// scaling, a product's three combinations, all coefficients of a block, the six sums, alpha and
+// the update of a Jacobi step): 8/24/64 first order 180 -> 100 launches and 50 -> 12 copies a cycle.
+
+// rows X[q][N] to unit length, their norms (1 for a zero row) in nrm; one workgroup per row
+__global__ __launch_bounds__(kB) void unit_rows_kernel(double* __restrict__ X, long N, double* __restrict__ nrm) {
+  __shared__ double red[kB / 64];
+  double* x = X + (long)blockIdx.x * N;
+  double a = 0.0;
+  for (long i = threadIdx.x; i < N; i += kB) a += x[i] * x[i];
+  for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+  __syncthreads();
+  double s = 0.0;
+  for (int w = 0; w < kB / 64; ++w) s += red[w];
+  s = sqrt(s);
+  if (!(s > 0.0)) s = 1.0;
+  for (long i = threadIdx.x; i < N; i += kB) x[i] = x[i] / s;
+  if (threadIdx.x == 0) nrm[blockIdx.x] = s;
+}
+
+// P0 = A + B, P1 = A - B, PS = S
+__global__ void store_products_kernel(long n, const double* __restrict__ A, const double* __restrict__ B,
+                                      const double* __restrict__ S, double* __restrict__ P0, double* __restrict__ P1,
+                                      double* __restrict__ PS) {
+  GS_LOOP(i, n) {
+    const double a = A[i], b = B[i];
+    P0[i] = a + b;
+    P1[i] = a - b;
+    PS[i] = S[i];
+  }
+}
+
+// Coefficients of the input vectors of an extension in the extended basis, C[rows][ld]:
+// rows below nb0: (C1 + C2 R1) nrm, the n2 rows of the new vectors: (R2 R1) nrm, zero elsewhere.
+__global__ void coeffs_kernel(int rows, long ld, int nb0, int kk, int n1, int n2, const double* __restrict__ C1,
+                              const double* __restrict__ C2, const double* __restrict__ R1,
+                              const double* __restrict__ R2, const double* __restrict__ nrm, double* __restrict__ C) {
+  GS_LOOP(idx, (long)rows * ld) {
+    const int p = (int)(idx / ld), j = (int)(idx % ld);
+    double v = 0.0;
+    if (j < kk && p < nb0 + n2) {
+      const double* c = p < nb0 ? C2 + (long)p * n1 : R2 + (long)(p - nb0) * n1;
+      for (int t = 0; t < n1; ++t) v = fma(c[t], R1[(long)t * kk + j], v);
+      if (p < nb0) v += C1[(long)p * kk + j];
+      v *= nrm[j];
+    }
+    C[idx] = v;
+  }
+}
+
+// coefficient halves of [X | Y] columns: U = X + Y, W = X - Y ([2][rows][k])
+__global__ void pair_coeffs_kernel(int rows, int k, long ld, const double* __restrict__ C, double* __restrict__ UW) {
+  GS_LOOP(idx, (long)rows * k) {
+    const int p = (int)(idx / k), q = (int)(idx % k);
+    const double x = C[(long)p * ld + q], y = C[(long)p * ld + k + q];
+    UW[idx] = x + y;
+    UW[(long)rows * k + idx] = x - y;
   }
 }
 
@@ -65,10 +121,6 @@ __global__ void scale_cols_kernel(double* C, int rows, int cols, long ld, const 
   }
 }
 
-__global__ void sqrt_kernel(double* x, int n) {
-  GS_LOOP(i, n) x[i] = sqrt(x[i]);
-}
-
 __global__ void symmetrize_kernel(double* A, int n) {
   GS_LOOP(idx, (long)n * n) {
     const int r = (int)(idx / n), c = (int)(idx % n);
@@ -78,6 +130,36 @@ __global__ void symmetrize_kernel(double* A, int n) {
       A[(long)c * n + r] = m;
     }
   }
+}
+
+// Projected matrices A[0..2] (n x n, stride apart) symmetrized; with E: E = I - A[2] and
+// X = I + E, the start of the inverse of the projected metric.
+__global__ void projected_kernel(double* A, long stride, int n, double* __restrict__ E, double* __restrict__ X) {
+  GS_LOOP(idx, 3L * n * n) {
+    const int b = (int)(idx / ((long)n * n)), r = (int)(idx / n % n), c = (int)(idx % n);
+    if (c < r) continue;
+    double* a = A + b * stride;
+    const double m = 0.5 * (a[(long)r * n + c] + a[(long)c * n + r]);
+    a[(long)r * n + c] = m;
+    a[(long)c * n + r] = m;
+    if (b == 2 && E) {
+      const double d = r == c ? 1.0 : 0.0, e = d - m;
+      E[(long)r * n + c] = e;
+      E[(long)c * n + r] = e;
+      X[(long)r * n + c] = d + e;
+      X[(long)c * n + r] = d + e;
+    }
+  }
+}
+
+// y += x
+__global__ void add_kernel(long n, const double* __restrict__ x, double* __restrict__ y) {
+  GS_LOOP(i, n) y[i] += x[i];
+}
+
+// th = sqrt(th2); th2 <= 0 gives NaN
+__global__ void theta_kernel(int n, const double* __restrict__ th2, double* __restrict__ th) {
+  GS_LOOP(i, n) th[i] = th2[i] > 0.0 ? sqrt(th2[i]) : __longlong_as_double(0x7ff8000000000000LL);
 }
 
 // T[j][jj] = U[j][keep[jj]] / sqrt(lam[keep[jj]]),  R[jj][j] = sqrt(lam[keep[jj]]) U[j][keep[jj]]
@@ -121,17 +203,14 @@ __global__ void jacobi_dir_kernel(long N, int k, double w0, double clampv, const
   }
 }
 
-// alpha per column from the folded-quotient coefficients (see module comment)
-__global__ void alpha_kernel(int k, const double* __restrict__ st, double* __restrict__ alpha) {
-  // st layout: [6][k]: |Zt|^2+|Zb|^2 (rho nz^2), Z.Zd, |Zd|^2, c.cd, |cd|^2, |c|^2
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= k) return;
-  const double nz2 = st[5 * k + q];
-  const double rho = st[0 * k + q] / nz2;
-  const double a1 = 2.0 * st[1 * k + q] / nz2;
-  const double a2 = st[2 * k + q] / nz2;
-  const double b1 = 2.0 * st[3 * k + q] / nz2;
-  const double b2 = st[4 * k + q] / nz2;
+// Step length from the folded-quotient coefficients (see module comment): rho nz^2 = |Z z|^2,
+// a1 nz^2 / 2 = Zz.Zd, a2 nz^2 = |Zd|^2, b1 nz^2 / 2 = z.d, b2 nz^2 = |d|^2, nz^2 = |z|^2.
+__device__ double folded_alpha(double zz, double zd, double dd, double cd, double d2, double nz2) {
+  const double rho = zz / nz2;
+  const double a1 = 2.0 * zd / nz2;
+  const double a2 = dd / nz2;
+  const double b1 = 2.0 * cd / nz2;
+  const double b2 = d2 / nz2;
   const double qa = a2 * b1 - a1 * b2, qb = 2.0 * (a2 - rho * b2), qc = a1 - rho * b1;
   double cand[2];
   int nc = 0;
@@ -164,15 +243,51 @@ __global__ void alpha_kernel(int k, const double* __restrict__ st, double* __res
       have = true;
     }
   }
-  alpha[q] = best;
+  return best;
 }
 
-// C[:, q] += alpha[q] D[:, q] for coefficient matrices with ld
-__global__ void axpy_cols_kernel(int rows, int k, long ld, const double* __restrict__ alpha, const double* __restrict__ D,
-                                 long ldd, double* __restrict__ C) {
-  GS_LOOP(idx, (long)rows * k) {
-    const int p = (int)(idx / k), q = (int)(idx % k);
-    C[(long)p * ld + q] += alpha[q] * D[(long)p * ldd + q];
+// One Jacobi step's line search, one workgroup per column q: the sums over the vectors Zz =
+// [Zt; Zb] and Zd ([2k][N] each: X rows, then Y rows) and over the coefficients z, d ([rows][ld],
+// columns q and k + q), alpha from them, and z += alpha d.
+__global__ __launch_bounds__(kB) void jacobi_step_kernel(long N, int k, int rows, long ld,
+                                                         const double* __restrict__ Zz, const double* __restrict__ Zd,
+                                                         double* __restrict__ cz, const double* __restrict__ cd) {
+  __shared__ double red[6][kB / 64];
+  __shared__ double alpha;
+  const int q = blockIdx.x;
+  const long bx = (long)q * N, by = (long)(k + q) * N;
+  double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (long i = threadIdx.x; i < N; i += kB) {
+    const double zt = Zz[bx + i], zb = Zz[by + i], dt = Zd[bx + i], db = Zd[by + i];
+    s[0] += zt * zt + zb * zb;
+    s[1] += zt * dt + zb * db;
+    s[2] += dt * dt + db * db;
+  }
+  for (int p = threadIdx.x; p < rows; p += kB) {
+    const double x = cz[p * ld + q], y = cz[p * ld + k + q], dx = cd[p * ld + q], dy = cd[p * ld + k + q];
+    s[3] += x * dx + y * dy;
+    s[4] += dx * dx + dy * dy;
+    s[5] += x * x + y * y;
+  }
+#pragma unroll
+  for (int t = 0; t < 6; ++t) {
+    for (int off = 32; off > 0; off >>= 1) s[t] += __shfl_down(s[t], off, 64);
+    if ((threadIdx.x & 63) == 0) red[t][threadIdx.x >> 6] = s[t];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double v[6];
+    for (int t = 0; t < 6; ++t) {
+      v[t] = 0.0;
+      for (int w = 0; w < kB / 64; ++w) v[t] += red[t][w];
+    }
+    alpha = folded_alpha(v[0], v[1], v[2], v[3], v[4], v[5]);
+  }
+  __syncthreads();
+  const double a = alpha;
+  for (int p = threadIdx.x; p < rows; p += kB) {
+    cz[p * ld + q] += a * cd[p * ld + q];
+    cz[p * ld + k + q] += a * cd[p * ld + k + q];
   }
 }
 
@@ -278,64 +393,27 @@ __global__ void start_block_kernel(long N, int m, const int* __restrict__ pos, c
   }
 }
 
-// out[q] = A1[q].A2[q] + B1[q].B2[q] for vector sets [k][N] (one block per column)
-__global__ void two_dots_kernel(const double* __restrict__ A1, const double* __restrict__ B1,
-                                const double* __restrict__ A2, const double* __restrict__ B2, long N,
-                                double* __restrict__ out) {
-  __shared__ double red[kB / 64];
-  const int q = blockIdx.x;
-  const long base = (long)q * N;
-  double a = 0.0;
-  for (long i = threadIdx.x; i < N; i += blockDim.x) a += A1[base + i] * A2[base + i] + B1[base + i] * B2[base + i];
-  for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+// out[0] = max |I - T| for an n x n matrix T
+__global__ __launch_bounds__(1024) void ns_residual_kernel(int n, const double* __restrict__ T,
+                                                           double* __restrict__ out) {
+  __shared__ double red[16];
+  double m = 0.0;
+  bool nan = false;
+  for (int idx = threadIdx.x; idx < n * n; idx += 1024) {
+    const double t = fabs(T[idx] - ((idx / n == idx % n) ? 1.0 : 0.0));
+    nan = nan || !(t == t);
+    m = fmax(m, t);
+  }
+  if (nan) m = INFINITY;
+  for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_down(m, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int w = 0; w < kB / 64; ++w) s += red[w];
-    out[q] = s;
+    for (int w = 1; w < 16; ++w) m = fmax(m, red[w]);
+    out[0] = m;
   }
 }
 
-// out[q] = sum_p (X1[p][q] X2[p][q] + Y1[p][q] Y2[p][q]) over rows p < rows (ld)
-__global__ void coeff_dots_kernel(int rows, int k, long ld, const double* __restrict__ X1,
-                                  const double* __restrict__ Y1, const double* __restrict__ X2,
-                                  const double* __restrict__ Y2, double* __restrict__ out) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= k) return;
-  double s = 0.0;
-  for (int p = 0; p < rows; ++p) s += X1[(long)p * ld + q] * X2[(long)p * ld + q] + Y1[(long)p * ld + q] * Y2[(long)p * ld + q];
-  out[q] = s;
-}
-
-__global__ void identity_kernel(double* X, int n) {
-  GS_LOOP(idx, (long)n * n) X[idx] = (idx / n == idx % n) ? 1.0 : 0.0;
-}
-
-// out[0] = max |I - T| for an n x n matrix T
-__global__ void ns_residual_kernel(int n, const double* __restrict__ T, double* __restrict__ out) {
-  __shared__ double red[256];
-  double m = 0.0;
-  for (long idx = threadIdx.x; idx < (long)n * n; idx += blockDim.x)
-    m = fmax(m, fabs(T[idx] - ((idx / n == idx % n) ? 1.0 : 0.0)));
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = red[0];
-}
-
-__global__ void copy_cols_kernel(int rows, int cols, const double* __restrict__ src, long lds, double* __restrict__ dst,
-                                 long ldd) {
-  GS_LOOP(idx, (long)rows * cols) {
-    const int r = (int)(idx / cols), c = (int)(idx % cols);
-    dst[(long)r * ldd + c] = src[(long)r * lds + c];
-  }
-}
-
-// out[j] = sum_p (U[p][j]^2 + W[p][j]^2)
 // X = (u + w) / 2, Y = (u - w) / 2 for paired halves u = X + Y, w = X - Y ([k][N] each)
 __global__ void halves_kernel(long n, const double* __restrict__ U, const double* __restrict__ W,
                               double* __restrict__ X, double* __restrict__ Y) {
@@ -345,13 +423,14 @@ __global__ void halves_kernel(long n, const double* __restrict__ U, const double
   }
 }
 
-__global__ void coeff_norms_kernel(int rows, int cols, const double* __restrict__ U, const double* __restrict__ W,
-                                   double* __restrict__ out) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= cols) return;
+// out[j] = sum_p (U[p][j]^2 + W[p][j]^2), one wave per column
+__global__ __launch_bounds__(64) void coeff_norms_kernel(int rows, long ld, const double* __restrict__ U,
+                                                         const double* __restrict__ W, double* __restrict__ out) {
+  const int j = blockIdx.x;
   double s = 0.0;
-  for (int p = 0; p < rows; ++p) s += U[(long)p * cols + j] * U[(long)p * cols + j] + W[(long)p * cols + j] * W[(long)p * cols + j];
-  out[j] = s;
+  for (int p = threadIdx.x; p < rows; p += 64) s += U[p * ld + j] * U[p * ld + j] + W[p * ld + j] * W[p * ld + j];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+  if (threadIdx.x == 0) out[j] = s;
 }
 
 GemmDesc gd(int M, int N, int K, int tA, long lda, int tB, long ldb, long ldc) {
@@ -566,13 +645,13 @@ class Solver {
   // basis and products [nbmax][N]
   double *Q_, *P0_, *P1_, *PS_, *Qs_, *P0s_, *P1s_, *PSs_;
   // work vectors [*][N]
-  double *V_, *AV_, *BV_, *SV_, *T1_, *T2_, *T3_, *T4_, *T5_, *T6_;
+  double *V_, *AV_, *BV_, *SV_, *T1_, *T2_, *T3_, *T4_, *T5_;
   // Ritz-space arrays [nbmax][N]
-  double *RU_, *RW_, *RSU_, *RSW_;
+  double *RU_, *RW_, *RS_;
   // small matrices
-  double *c1_, *c2_, *g_, *U_, *lam_, *Tm_, *Rm_, *Ctot_, *Rtot_, *tmp_, *tmp2_, *nrm_;
-  double *cx_, *cy_, *cdx_, *cdy_, *cu_, *cw_, *st_, *alpha_;
-  double *Ap_, *Am_, *Sp_, *L_, *Li_, *Ls_, *Lsi_, *Spi_, *K_, *th2_, *Zk_, *us_, *ws_, *th_, *stats_;
+  double *c1_, *c2_, *g_, *U_, *lam_, *Tm_, *Rm_, *Rtot_, *tmp_, *tmp2_, *nrm_;
+  double *cz_, *cd_, *uw2_;
+  double *Ap_, *Am_, *Sp_, *L_, *Ls_, *Lsi_, *Spi_, *K_, *th2_, *Zk_, *uw_, *us_, *ws_, *th_, *stats_;
   double *eigscr_;
   int *keep_, *ival_, *sel_;
   double* noise_;
@@ -627,8 +706,7 @@ class Solver {
     PSs_ = get<double>(bN, "basis swap");
     RU_ = get<double>(bN, "ritz PU");
     RW_ = get<double>(bN, "ritz MW");
-    RSU_ = get<double>(bN, "ritz SU");
-    RSW_ = get<double>(bN, "ritz SW");
+    RS_ = get<double>(2 * bN, "ritz SU, SW");
     V_ = get<double>(kN, "block V");
     AV_ = get<double>(kN, "block AV");
     BV_ = get<double>(kN, "block BV");
@@ -638,7 +716,6 @@ class Solver {
     T3_ = get<double>(kN, "block tmp");
     T4_ = get<double>(kN, "block tmp");
     T5_ = get<double>(kN, "block tmp");
-    T6_ = get<double>(kN, "block tmp");
     const size_t bk = (size_t)nbmax_ * kmax_;
     const size_t bb = (size_t)nbmax_ * nbmax_;
     const size_t kk = (size_t)kmax_ * kmax_;
@@ -649,34 +726,26 @@ class Solver {
     lam_ = get<double>(nbmax_, "eigval");
     Tm_ = get<double>(std::max(kk, bk), "T");
     Rm_ = get<double>(kk, "R");
-    Ctot_ = get<double>(bk, "C");
     Rtot_ = get<double>(kk, "R tot");
-    tmp_ = get<double>(std::max(bk, bb), "tmp");
-    tmp2_ = get<double>(std::max(bk, bb), "tmp2");
+    tmp_ = get<double>(std::max(bk, 2 * bb), "tmp");
+    tmp2_ = get<double>(std::max(bk, 2 * bb), "tmp2");
     nrm_ = get<double>(std::max(kmax_, 8), "norms");
-    cx_ = get<double>(bk, "cx");
-    cy_ = get<double>(bk, "cy");
-    cdx_ = get<double>(bk, "cdx");
-    cdy_ = get<double>(bk, "cdy");
-    cu_ = get<double>(bk, "cu");
-    cw_ = get<double>(bk, "cw");
-    st_ = get<double>((size_t)8 * kmax_, "stats");
-    alpha_ = get<double>(kmax_, "alpha");
+    cz_ = get<double>(bk, "coefficients z");
+    cd_ = get<double>(bk, "coefficients d");
+    uw2_ = get<double>(bk, "coefficients z+, z-");
     Ap_ = get<double>(bb, "Ap");
     Am_ = get<double>(bb, "Am");
     Sp_ = get<double>(bb, "Sp");
     L_ = get<double>(bb, "L");
-    Li_ = get<double>(bb, "Li");
     Ls_ = get<double>(bb, "Ls");
     Lsi_ = get<double>(bb, "Lsi");
     Spi_ = get<double>(bb, "Spi");
     K_ = get<double>(bb, "K");
     th2_ = get<double>(nbmax_, "theta2");
     Zk_ = get<double>(bb, "Zk");
-    us_ = get<double>(bb, "us");
-    ws_ = get<double>(bb, "ws");
+    uw_ = get<double>(2 * bb, "us, ws");
     th_ = get<double>(nbmax_, "theta");
-    stats_ = get<double>(std::max((size_t)2 * nbmax_, (size_t)3 * 64), "ritz stats");
+    stats_ = get<double>(std::max((size_t)2 * nbmax_, (size_t)4 * 64), "ritz stats");
     eigscr_ = get<double>(std::max((size_t)2 * std::max(bb, kk), partial_syev_scratch(nbmax_, 64)), "eig scratch");
     keep_ = get<int>(std::max(kmax_, nbmax_), "keep");
     ival_ = get<int>(4, "info");
@@ -743,106 +812,80 @@ class Solver {
     products_ += k;
   }
 
-  // symmetric orthonormalization of the kk vectors in X ([kk][N]); keeps eigen-directions of
-  // the Gram matrix above thresh. Returns kept count; X <- X T, R (nk x kk, ld kk) such that
-  // X_old ~= X_new R.
-  int sym_orth(double* X, int kk, double thresh, double* Xout) {
+  // Orthonormalization of the kk vectors in X ([kk][N]), dropping what lies within
+  // sqrt(thresh) of the span of the rest.  Returns the kept count nk; Xout <- X T, R (nk x kk,
+  // ld kk) such that X ~= Xout R.
+  int orthonormalize(double* X, int kk, double thresh, double* Xout, double* R) {
     tn(kk, kk, X, X, g_, kk);
-    symmetrize_kernel<<<gridn((long)kk * kk), kB, 0, s_>>>(g_, kk);
-    small_syev(kk, g_, lam_, U_, s_, eigscr_);
-    auto lam = fetch(lam_, kk);
-    std::vector<int> keep;
-    for (int j = 0; j < kk; ++j)
-      if (lam[j] > thresh) keep.push_back(j);
-    const int nk = (int)keep.size();
-    if (nk == 0) return 0;
-    upload(keep_, keep);
-    symorth_factors_kernel<<<gridn((long)kk * nk), kB, 0, s_>>>(kk, U_, lam_, keep_, nk, Tm_, Rm_);
+    int nk;
+    if (kk <= 64) {
+      nk = orth_factors(kk, g_, thresh, Tm_, R, ival_ + 2, s_);
+      if (nk == 0) return 0;
+    } else {
+      symmetrize_kernel<<<gridn((long)kk * kk), kB, 0, s_>>>(g_, kk);
+      small_syev(kk, g_, lam_, U_, s_, eigscr_);
+      auto lam = fetch(lam_, kk);
+      std::vector<int> keep;
+      for (int j = 0; j < kk; ++j)
+        if (lam[j] > thresh) keep.push_back(j);
+      nk = (int)keep.size();
+      if (nk == 0) return 0;
+      upload(keep_, keep);
+      symorth_factors_kernel<<<gridn((long)kk * nk), kB, 0, s_>>>(kk, U_, lam_, keep_, nk, Tm_, R);
+    }
     // Xout[jj][r] = sum_j T[j][jj] X[j][r]
     expand(nk, kk, Tm_, nk, X, Xout);
     return nk;
   }
 
-  // Add span(X) ([kk][N]) to the basis.  On return the coefficients of the input
-  // vectors in the extended basis are in Ctot_ ([nb_new][kk], ld kk).
-  int extend(double* X, int kk) {
+  // Add span(X) ([kk][N]) to the basis.  C (nullable): on return the coefficients of the input
+  // vectors in the extended basis ([nbmax][kmax], zero outside).
+  int extend(double* X, int kk, double* C) {
     const int nb0 = nb_;
-    column_dots(X, X, N_, kk, nrm_, s_);
-    sqrt_kernel<<<1, kB, 0, s_>>>(nrm_, kk);
-    auto nr = fetch(nrm_, kk);
-    for (double& x : nr)
-      if (!(x > 0)) x = 1.0;
-    upload(nrm_, nr);
-    scale_rows_kernel<<<gridn(N_ * kk), kB, 0, s_>>>(X, N_, kk, nrm_, 1);
+    unit_rows_kernel<<<kk, kB, 0, s_>>>(X, N_, nrm_);
     // pass 1: C1 = Q X^T, X -= C1^T Q
     if (nb0) {
       tn(nb0, kk, Q_, X, c1_, kk);
       expand(kk, nb0, c1_, kk, Q_, X, -1.0, 1.0);
     }
-    int n1 = sym_orth(X, kk, 1e-12, T1_);
-    if (n1 == 0) {
-      // nothing new: coefficients are C1 only
-      small_copy_coeffs(nb0, kk, nb0 ? c1_ : nullptr, nullptr, 0, nr);
-      return 0;
+    const int n1 = orthonormalize(X, kk, 1e-12, T1_, Rtot_);
+    int n2 = 0;
+    if (n1 > 0) {
+      // pass 2
+      if (nb0) {
+        tn(nb0, n1, Q_, T1_, c2_, n1);
+        expand(n1, nb0, c2_, n1, Q_, T1_, -1.0, 1.0);
+      }
+      n2 = orthonormalize(T1_, n1, 0.25, Q_ + (size_t)nb0 * N_, Rm_);
     }
-    // R1 (n1 x kk) saved
-    PPW_HIP(hipMemcpyAsync(Rtot_, Rm_, sizeof(double) * n1 * kk, hipMemcpyDeviceToDevice, s_));
-    // pass 2
-    if (nb0) {
-      tn(nb0, n1, Q_, T1_, c2_, n1);
-      expand(n1, nb0, c2_, n1, Q_, T1_, -1.0, 1.0);
-    }
-    int n2 = sym_orth(T1_, n1, 0.25, Q_ + (size_t)nb0 * N_);
-    // coefficient rows for the new vectors: R = R2 R1 (n2 x kk)
-    if (n2 > 0) small_mm(n2, kk, n1, Rm_, n1, 0, Rtot_, kk, 0, tmp2_, kk);
-    // C = C1 + C2 R1 (nb0 x kk)
-    if (nb0) {
-      PPW_HIP(hipMemcpyAsync(Ctot_, c1_, sizeof(double) * nb0 * kk, hipMemcpyDeviceToDevice, s_));
-      small_mm(nb0, kk, n1, c2_, n1, 0, Rtot_, kk, 0, Ctot_, kk, 1.0, 1.0);
-    }
-    if (n2 > 0) PPW_HIP(hipMemcpyAsync(Ctot_ + (size_t)nb0 * kk, tmp2_, sizeof(double) * n2 * kk,
-                                       hipMemcpyDeviceToDevice, s_));
-    // undo the unit scaling: column j of C times nrm[j]
-    scale_cols_kernel<<<gridn((long)(nb0 + n2) * kk), kB, 0, s_>>>(Ctot_, nb0 + n2, kk, kk, nrm_, 0);
+    // C = C1 + C2 R1 and R2 R1, the unit scaling undone (n1 = 0: nothing new, C1 alone)
+    if (C)
+      coeffs_kernel<<<gridn((long)nbmax_ * kmax_), kB, 0, s_>>>(nbmax_, kmax_, nb0, kk, n1, n2, c1_, c2_, Rtot_, Rm_,
+                                                                nrm_, C);
     // products of the new orthonormal vectors
     if (n2 > 0) {
       products(n2, Q_ + (size_t)nb0 * N_, false);
-      axpby((long)n2 * N_, 1.0, AV_, 0.0, P0_ + (size_t)nb0 * N_, s_);
-      axpby((long)n2 * N_, 1.0, BV_, 1.0, P0_ + (size_t)nb0 * N_, s_);
-      axpby((long)n2 * N_, 1.0, AV_, 0.0, P1_ + (size_t)nb0 * N_, s_);
-      axpby((long)n2 * N_, -1.0, BV_, 1.0, P1_ + (size_t)nb0 * N_, s_);
-      PPW_HIP(hipMemcpyAsync(PS_ + (size_t)nb0 * N_, SV_, sizeof(double) * n2 * N_, hipMemcpyDeviceToDevice, s_));
+      store_products_kernel<<<gridn((long)n2 * N_), kB, 0, s_>>>((long)n2 * N_, AV_, BV_, SV_, P0_ + (size_t)nb0 * N_,
+                                                                P1_ + (size_t)nb0 * N_, PS_ + (size_t)nb0 * N_);
+      PPW_LAUNCH_CHECK();
     }
     nb_ = nb0 + n2;
     return n2;
   }
 
-  void small_copy_coeffs(int nb0, int kk, const double* c1, const double*, int, const std::vector<double>&) {
-    if (nb0) {
-      PPW_HIP(hipMemcpyAsync(Ctot_, c1, sizeof(double) * nb0 * kk, hipMemcpyDeviceToDevice, s_));
-      scale_cols_kernel<<<gridn((long)nb0 * kk), kB, 0, s_>>>(Ctot_, nb0, kk, kk, nrm_, 0);
-    }
-  }
-
-  // Zt, Zb (in T3_, T4_) for block coefficient vectors cx, cy (nb_ x k, ld kmax_)
-  void zprod(int k, const double* cx, const double* cy, double* Zt, double* Zb) {
-    // cu = cx + cy, cw = cx - cy
-    PPW_HIP(hipMemcpyAsync(cu_, cx, sizeof(double) * nbmax_ * kmax_, hipMemcpyDeviceToDevice, s_));
-    PPW_HIP(hipMemcpyAsync(cw_, cx, sizeof(double) * nbmax_ * kmax_, hipMemcpyDeviceToDevice, s_));
-    axpby((long)nbmax_ * kmax_, 1.0, cy, 1.0, cu_, s_);
-    axpby((long)nbmax_ * kmax_, -1.0, cy, 1.0, cw_, s_);
-    expand(k, nb_, cu_, kmax_, P0_, T1_);   // PU
-    expand(k, nb_, cw_, kmax_, P1_, T2_);   // MW
-    expand(k, nb_, cx, kmax_, PS_, T5_);    // SX
-    expand(k, nb_, cy, kmax_, PS_, T6_);    // SY
-    zcombine_kernel<<<gridn(N_ * k), kB, 0, s_>>>(N_ * k, w0_, T1_, T2_, T5_, T6_, Zt, Zb);
-  }
-
-  void two_dots(const double* A1, const double* B1, const double* A2, const double* B2, long N, int k, double* out) {
-    two_dots_kernel<<<k, kB, 0, s_>>>(A1, B1, A2, B2, N, out);
-  }
-  void coeff_dots(int k, const double* X1, const double* Y1, const double* X2, const double* Y2, double* out) {
-    coeff_dots_kernel<<<(k + 63) / 64, 64, 0, s_>>>(nb_, k, kmax_, X1, Y1, X2, Y2, out);
+  // Z z = [Zt; Zb] ([2k][N]) of the vectors with coefficients c ([nbmax][kmax]: columns X, then Y).
+  // Scratch: T1_ (P0 u, P1 w), T2_ (S x, S y).
+  void zprod(int k, const double* c, double* Z) {
+    pair_coeffs_kernel<<<gridn((long)nb_ * k), kB, 0, s_>>>(nb_, k, kmax_, c, uw2_);
+    GemmDesc d = gd(k, (int)N_, nb_, 1, k, 0, N_, N_);
+    d.nb1 = 2;
+    d.sA1 = (long)nb_ * k;
+    d.sB1 = P1_ - P0_;
+    d.sC1 = (long)k * N_;
+    gemm(d, 1.0, uw2_, P0_, 0.0, T1_);
+    expand(2 * k, nb_, c, kmax_, PS_, T2_);
+    const size_t kN = (size_t)k * N_;
+    zcombine_kernel<<<gridn(N_ * k), kB, 0, s_>>>(N_ * k, w0_, T1_, T1_ + kN, T2_, T2_ + kN, Z, Z + kN);
   }
 
   // thick restart: new basis = orthonormal span of the X+Y and X-Y halves of the block's Ritz vectors
@@ -871,11 +914,8 @@ class Solver {
     if (opt_.precision == 1) {
       // mixed precision: the restart block gets FP64 products (refinement)
       products(nk, Qs_, true);
-      axpby((long)nk * N_, 1.0, AV_, 0.0, P0s_, s_);
-      axpby((long)nk * N_, 1.0, BV_, 1.0, P0s_, s_);
-      axpby((long)nk * N_, 1.0, AV_, 0.0, P1s_, s_);
-      axpby((long)nk * N_, -1.0, BV_, 1.0, P1s_, s_);
-      PPW_HIP(hipMemcpyAsync(PSs_, SV_, sizeof(double) * nk * N_, hipMemcpyDeviceToDevice, s_));
+      store_products_kernel<<<gridn((long)nk * N_), kB, 0, s_>>>((long)nk * N_, AV_, BV_, SV_, P0s_, P1s_, PSs_);
+      PPW_LAUNCH_CHECK();
     } else {
       expand(nk, n, tmp2_, nk, P0_, P0s_);
       expand(nk, n, tmp2_, nk, P1_, P1s_);
@@ -929,33 +969,51 @@ class Solver {
 
 Solver::Ritz Solver::rayleigh_ritz() {
   const int n = nb_;
-  tn(n, n, Q_, P0_, Ap_, n);
-  tn(n, n, Q_, P1_, Am_, n);
-  tn(n, n, Q_, PS_, Sp_, n);
-  symmetrize_kernel<<<gridn((long)n * n), kB, 0, s_>>>(Ap_, n);
-  symmetrize_kernel<<<gridn((long)n * n), kB, 0, s_>>>(Am_, n);
-  symmetrize_kernel<<<gridn((long)n * n), kB, 0, s_>>>(Sp_, n);
+  const long nn = (long)n * n;
+  // Q P0^T, Q P1^T, Q PS^T in one batch (the three product sets lie one stride apart, as do the
+  // projected matrices), symmetrized
+  {
+    GemmDesc d = gd(n, n, (int)N_, 0, N_, 1, N_, n);
+    d.nb1 = 3;
+    d.sB1 = P1_ - P0_;
+    d.sC1 = Am_ - Ap_;
+    gemm(d, 1.0, Q_, P0_, 0.0, Ap_);
+  }
+  const bool metric = c_.order >= 2;
+  double* X = Spi_;  // [X; E] of the inverse metric's product form, each level in the other pair
+  double* E = U_;
+  projected_kernel<<<gridn(3 * nn), kB, 0, s_>>>(Ap_, Am_ - Ap_, n, metric ? E : nullptr, X);
   small_cholesky(n, Am_, L_, ival_, tmp_, s_);
-  // Sp^-1: the metric is the identity plus the (small) MP2 density correction, so
-  // Newton-Schulz X <- 2X - X Sp X from X = I converges quadratically; the Cholesky
-  // route is the fallback when |I - Sp X| does not reach rounding level.
-  identity_kernel<<<gridn((long)n * n), kB, 0, s_>>>(Spi_, n);
-  if (c_.order >= 2) {
-    for (int it = 0; it < 6; ++it) {
-      small_mm(n, n, n, Sp_, n, 0, Spi_, n, 0, tmp_, n);        // T = Sp X
-      small_mm(n, n, n, Spi_, n, 0, tmp_, n, 0, tmp2_, n);      // X T
-      axpby((long)n * n, 2.0, Spi_, 0.0, K_, s_);               // 2X
-      axpby((long)n * n, -1.0, tmp2_, 1.0, K_, s_);             // 2X - X T
-      PPW_HIP(hipMemcpyAsync(Spi_, K_, sizeof(double) * n * n, hipMemcpyDeviceToDevice, s_));
-    }
-    small_mm(n, n, n, Sp_, n, 0, Spi_, n, 0, tmp_, n);
-    ns_residual_kernel<<<1, 256, 0, s_>>>(n, tmp_, lam_);
+  // Sp^-1: the metric is the identity less the (small) MP2 density correction E, so
+  // Sp^-1 = (I + E)(I + E^2)(I + E^4)(I + E^8) to E^16, each level one GEMM of [X; E^j] by E^j.
+  // Where |I - Sp X| does not reach rounding level (|E| above 0.1), Newton-Schulz steps
+  // X <- 2X - X Sp X follow, and last the Cholesky route.
+  if (metric) {
+    small_mm(n, n, n, E, n, 0, E, n, 0, tmp2_ + nn, n);                      // E^2
+    PPW_HIP(hipMemcpyAsync(tmp2_, X, sizeof(double) * nn, hipMemcpyDeviceToDevice, s_));
+    small_mm(2 * n, n, n, tmp2_, n, 0, tmp2_ + nn, n, 0, tmp_, n);           // [X E^2; E^4]
+    add_kernel<<<gridn(nn), kB, 0, s_>>>(nn, tmp2_, tmp_);
+    small_mm(2 * n, n, n, tmp_, n, 0, tmp_ + nn, n, 0, tmp2_, n);            // [X E^4; E^8]
+    add_kernel<<<gridn(nn), kB, 0, s_>>>(nn, tmp_, tmp2_);
+    small_mm(n, n, n, tmp2_, n, 0, tmp2_ + nn, n, 0, X, n);                  // X E^8
+    add_kernel<<<gridn(nn), kB, 0, s_>>>(nn, tmp2_, X);
+    small_mm(n, n, n, Sp_, n, 0, X, n, 0, tmp_, n);
+    ns_residual_kernel<<<1, 1024, 0, s_>>>(n, tmp_, lam_);
+    PPW_LAUNCH_CHECK();
   }
   auto info = fetch(ival_, 1);
   if (info[0] != 0) throw Unstable("A - B is not positive definite in the subspace");
-  if (c_.order >= 2) {
-    auto res = fetch(lam_, 1);
-    if (!(res[0] < 1e-13)) {
+  if (metric) {
+    double res = fetch(lam_, 1)[0];
+    for (int it = 0; it < 2 && !(res < 1e-13) && res < 0.5; ++it) {
+      small_mm(n, n, n, X, n, 0, tmp_, n, 0, tmp2_, n);         // X T, T = Sp X
+      axpby(nn, -1.0, tmp2_, 2.0, X, s_);                       // 2X - X T
+      small_mm(n, n, n, Sp_, n, 0, X, n, 0, tmp_, n);
+      ns_residual_kernel<<<1, 1024, 0, s_>>>(n, tmp_, lam_);
+      PPW_LAUNCH_CHECK();
+      res = fetch(lam_, 1)[0];
+    }
+    if (!(res < 1e-13)) {
       small_cholesky(n, Sp_, Ls_, ival_ + 1, tmp_, s_);
       auto inf2 = fetch(ival_ + 1, 1);
       if (inf2[0] != 0) throw Unstable("S is not positive definite in the subspace");
@@ -964,34 +1022,36 @@ Solver::Ritz Solver::rayleigh_ritz() {
     }
   }
   // Mt = Sp^-1 L ; K = Mt^T Ap Mt
-  small_mm(n, n, n, Spi_, n, 0, L_, n, 0, tmp_, n);
-  small_mm(n, n, n, Ap_, n, 0, tmp_, n, 0, tmp2_, n);
-  small_mm(n, n, n, tmp_, n, 1, tmp2_, n, 0, K_, n);
-  symmetrize_kernel<<<gridn((long)n * n), kB, 0, s_>>>(K_, n);
+  const double* Mt = L_;
+  if (metric) {
+    small_mm(n, n, n, Spi_, n, 0, L_, n, 0, tmp_, n);
+    Mt = tmp_;
+  }
+  small_mm(n, n, n, Ap_, n, 0, Mt, n, 0, tmp2_, n);
+  small_mm(n, n, n, Mt, n, 1, tmp2_, n, 0, K_, n);
+  symmetrize_kernel<<<gridn(nn), kB, 0, s_>>>(K_, n);
   // eigenpairs of K nearest omega0^2 (candidate roots of the window)
   const int p = std::min(n, std::min(64, std::max(2 * m_ + 4, nr_ + 8)));
   const int q = partial_syev(n, K_, w0_ * w0_, p, th2_, Zk_, eigscr_, s_);
-  auto th2 = fetch(th2_, q);
-  for (int j = 0; j < q; ++j)
-    if (!(th2[j] > 0)) throw Unstable("A + B is not positive definite in the subspace");
-  std::vector<double> th(q);
-  for (int j = 0; j < q; ++j) th[j] = std::sqrt(th2[j]);
-  upload(th_, th);
-  rld_ = q;
-  // us = Mt Z / sqrt(theta),  ws = sqrt(theta) L^-T Z
-  small_mm(n, q, n, tmp_, n, 0, Zk_, p, 0, us_, q);
-  scale_cols_kernel<<<gridn((long)n * q), kB, 0, s_>>>(us_, n, q, q, th_, 3);
-  copy_cols_kernel<<<gridn((long)n * q), kB, 0, s_>>>(n, q, Zk_, p, ws_, q);
-  small_trsm_lt(n, L_, q, ws_, s_);
-  scale_cols_kernel<<<gridn((long)n * q), kB, 0, s_>>>(ws_, n, q, q, th_, 2);
-  // products of the Ritz halves: PU = P0 us, MW = P1 ws, SU = PS us, SW = PS ws  ([q][N])
-  expand(q, n, us_, q, P0_, RU_);
-  expand(q, n, ws_, q, P1_, RW_);
-  expand(q, n, us_, q, PS_, RSU_);
-  expand(q, n, ws_, q, PS_, RSW_);
-  residual_norms_kernel<<<q, kB, 0, s_>>>(N_, q, th_, w0_, RU_, RW_, RSU_, RSW_, stats_);
-  coeff_norms_kernel<<<(q + 63) / 64, 64, 0, s_>>>(n, q, us_, ws_, stats_ + 2 * q);
-  auto st = fetch(stats_, 3 * (size_t)q);
+  theta_kernel<<<1, 64, 0, s_>>>(q, th2_, th_);
+  rld_ = 2 * q;
+  us_ = uw_;
+  ws_ = uw_ + q;
+  // us = Mt Z / sqrt(theta),  ws = sqrt(theta) L^-T Z, side by side ([n][us | ws])
+  small_mm(n, q, n, Mt, n, 0, Zk_, p, 0, us_, rld_);
+  scale_cols_kernel<<<gridn((long)n * q), kB, 0, s_>>>(us_, n, q, rld_, th_, 3);
+  small_trsm_lt(n, L_, q, Zk_, p, th_, ws_, rld_, s_);
+  // products of the Ritz halves: PU = P0 us, MW = P1 ws ([q][N]); SU, SW = PS [us | ws] ([2q][N])
+  expand(q, n, us_, rld_, P0_, RU_);
+  expand(q, n, ws_, rld_, P1_, RW_);
+  expand(2 * q, n, us_, rld_, PS_, RS_);
+  residual_norms_kernel<<<q, kB, 0, s_>>>(N_, q, th_, w0_, RU_, RW_, RS_, RS_ + (size_t)q * N_, stats_);
+  coeff_norms_kernel<<<q, 64, 0, s_>>>(n, rld_, us_, ws_, stats_ + 2 * q);
+  PPW_HIP(hipMemcpyAsync(stats_ + 3 * q, th_, sizeof(double) * q, hipMemcpyDeviceToDevice, s_));
+  auto st = fetch(stats_, 4 * (size_t)q);
+  std::vector<double> th(st.begin() + 3 * q, st.end());
+  for (double t : th)
+    if (!(t > 0)) throw Unstable("A + B is not positive definite in the subspace");
   Ritz R;
   R.th = th;
   R.rn.resize(q);
@@ -1047,66 +1107,23 @@ void Solver::run(double* energies, double* vectors, double* osc, pp_solve_info* 
     // Riesz projector mode (subspace iteration): the filtered block replaces the subspace
     contour_step(knew);
     nb_ = 0;
-    extend(V_, 2 * knew);
+    extend(V_, 2 * knew, nullptr);
    } else if (knew > 0) {
     // X, Y halves are contiguous in V_: [X_0..X_k-1, Y_0..Y_k-1]
     const int kk = 2 * knew;
-    extend(V_, kk);
-    // coefficients of X_q (col q) and Y_q (col k+q) in Ctot_ (nb_ x kk, ld kk)
-    PPW_HIP(hipMemsetAsync(cx_, 0, sizeof(double) * nbmax_ * kmax_, s_));
-    PPW_HIP(hipMemsetAsync(cy_, 0, sizeof(double) * nbmax_ * kmax_, s_));
-    {
-      std::vector<int> a(knew), b(knew);
-      for (int q = 0; q < knew; ++q) {
-        a[q] = q;
-        b[q] = knew + q;
-      }
-      upload(sel_, a);
-      gather_cols_kernel<<<gridn((long)nb_ * knew), kB, 0, s_>>>(nb_, knew, sel_, Ctot_, kk, cx_, kmax_, 0);
-      upload(sel_, b);
-      gather_cols_kernel<<<gridn((long)nb_ * knew), kB, 0, s_>>>(nb_, knew, sel_, Ctot_, kk, cy_, kmax_, 0);
-    }
+    extend(V_, kk, cz_);
     for (int st = 1; st < opt_.krylov_steps; ++st) {
       if (nb_ + kk > nbmax_) break;
-      zprod(knew, cx_, cy_, T3_, T4_);
-      expand(knew, nb_, cx_, kmax_, Q_, T1_);
-      expand(knew, nb_, cy_, kmax_, Q_, T2_);
-      jacobi_dir_kernel<<<gridn(N_ * knew), kB, 0, s_>>>(N_, knew, w0_, clampv, c_.dA, c_.dS, T1_, T2_, T3_, T4_,
-                                                          V_, V_ + (size_t)knew * N_);
-      // keep Zt, Zb of the current z
-      PPW_HIP(hipMemcpyAsync(T5_, T3_, sizeof(double) * knew * N_, hipMemcpyDeviceToDevice, s_));
-      PPW_HIP(hipMemcpyAsync(T6_, T4_, sizeof(double) * knew * N_, hipMemcpyDeviceToDevice, s_));
-      extend(V_, kk);
-      PPW_HIP(hipMemsetAsync(cdx_, 0, sizeof(double) * nbmax_ * kmax_, s_));
-      PPW_HIP(hipMemsetAsync(cdy_, 0, sizeof(double) * nbmax_ * kmax_, s_));
-      {
-        std::vector<int> a(knew), b(knew);
-        for (int q = 0; q < knew; ++q) {
-          a[q] = q;
-          b[q] = knew + q;
-        }
-        upload(sel_, a);
-        gather_cols_kernel<<<gridn((long)nb_ * knew), kB, 0, s_>>>(nb_, knew, sel_, Ctot_, kk, cdx_, kmax_, 0);
-        upload(sel_, b);
-        gather_cols_kernel<<<gridn((long)nb_ * knew), kB, 0, s_>>>(nb_, knew, sel_, Ctot_, kk, cdy_, kmax_, 0);
-      }
-      // Zd in T3_, T4_ (Zt, Zb of z kept in T5_, T6_: unchanged by the basis extension)
-      PPW_HIP(hipMemcpyAsync(T1_, T5_, sizeof(double) * knew * N_, hipMemcpyDeviceToDevice, s_));
-      PPW_HIP(hipMemcpyAsync(T2_, T6_, sizeof(double) * knew * N_, hipMemcpyDeviceToDevice, s_));
-      // T1_/T2_ now hold Zt/Zb; zprod overwrites T1_, T2_, T5_, T6_ -> move Zt/Zb to AV_/BV_
-      PPW_HIP(hipMemcpyAsync(AV_, T1_, sizeof(double) * knew * N_, hipMemcpyDeviceToDevice, s_));
-      PPW_HIP(hipMemcpyAsync(BV_, T2_, sizeof(double) * knew * N_, hipMemcpyDeviceToDevice, s_));
-      zprod(knew, cdx_, cdy_, T3_, T4_);
-      // stats: [0] |Zz|^2, [1] Zz.Zd, [2] |Zd|^2, [3] c.cd, [4] |cd|^2, [5] |c|^2
-      two_dots(AV_, BV_, AV_, BV_, N_, knew, st_ + 0 * knew);
-      two_dots(AV_, BV_, T3_, T4_, N_, knew, st_ + 1 * knew);
-      two_dots(T3_, T4_, T3_, T4_, N_, knew, st_ + 2 * knew);
-      coeff_dots(knew, cx_, cy_, cdx_, cdy_, st_ + 3 * knew);
-      coeff_dots(knew, cdx_, cdy_, cdx_, cdy_, st_ + 4 * knew);
-      coeff_dots(knew, cx_, cy_, cx_, cy_, st_ + 5 * knew);
-      alpha_kernel<<<1, 64, 0, s_>>>(knew, st_, alpha_);
-      axpy_cols_kernel<<<gridn((long)nb_ * knew), kB, 0, s_>>>(nb_, knew, kmax_, alpha_, cdx_, kmax_, cx_);
-      axpy_cols_kernel<<<gridn((long)nb_ * knew), kB, 0, s_>>>(nb_, knew, kmax_, alpha_, cdy_, kmax_, cy_);
+      // Z z in T3_, z in T5_, the direction d in V_, Z d in T4_ (T3_ outlives the extension)
+      const size_t kN = (size_t)knew * N_;
+      zprod(knew, cz_, T3_);
+      expand(kk, nb_, cz_, kmax_, Q_, T5_);
+      jacobi_dir_kernel<<<gridn(N_ * knew), kB, 0, s_>>>(N_, knew, w0_, clampv, c_.dA, c_.dS, T5_, T5_ + kN, T3_,
+                                                          T3_ + kN, V_, V_ + kN);
+      extend(V_, kk, cd_);
+      zprod(knew, cd_, T4_);
+      jacobi_step_kernel<<<knew, kB, 0, s_>>>(N_, knew, nb_, kmax_, T3_, T4_, cz_, cd_);
+      PPW_LAUNCH_CHECK();
     }
    }
     R = rayleigh_ritz();
@@ -1382,19 +1399,18 @@ size_t window_solve_bytes(long N, int n_roots, const SolveOptions& opt) {
   const size_t D = sizeof(double);
   const size_t bN = (size_t)d.nbmax * N, kN = (size_t)d.kmax * N;
   const size_t bk = (size_t)d.nbmax * d.kmax, bb = (size_t)d.nbmax * d.nbmax, kk = (size_t)d.kmax * d.kmax;
-  size_t t = 12 * r(bN * D) + 10 * r(kN * D);
+  size_t t = 12 * r(bN * D) + 9 * r(kN * D);
   t += 2 * r(bk * D);                                   // c1, c2
   t += 2 * r(std::max(kk, bb) * D);                     // gram, eigvec
   t += r(d.nbmax * D);                                  // eigval
   t += r(std::max(kk, bk) * D) + r(kk * D);             // T, R
-  t += r(bk * D) + r(kk * D);                           // C, R tot
-  t += 2 * r(std::max(bk, bb) * D);                     // tmp, tmp2
+  t += r(kk * D);                                       // R tot
+  t += 2 * r(std::max(bk, 2 * bb) * D);                 // tmp, tmp2
   t += r(std::max(d.kmax, 8) * D);                      // norms
-  t += 6 * r(bk * D);                                   // cx, cy, cdx, cdy, cu, cw
-  t += r((size_t)8 * d.kmax * D) + r((size_t)d.kmax * D);  // stats, alpha
-  t += 9 * r(bb * D);                                   // Ap .. K
+  t += 3 * r(bk * D);                                   // cz, cd, uw2
+  t += 8 * r(bb * D);                                   // Ap .. K
   t += r(d.nbmax * D) + r(bb * D) + 2 * r(bb * D) + r(d.nbmax * D);  // theta2, Zk, us, ws, theta
-  t += r(std::max((size_t)2 * d.nbmax, (size_t)3 * 64) * D);
+  t += r(std::max((size_t)2 * d.nbmax, (size_t)4 * 64) * D);
   t += r(std::max((size_t)2 * std::max(bb, kk), partial_syev_scratch(d.nbmax, 64)) * D);
   t += 2 * r(std::max(d.kmax, d.nbmax) * sizeof(int)) + r(4 * sizeof(int));
   t += r((size_t)2 * d.m * N * D);                      // noise

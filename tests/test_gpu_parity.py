@@ -405,3 +405,17 @@ def test_response_from_windows_matches_resolvent(P, order):
     p0 = P.response(got_e, got_f, np.array([0.0]), 0.0)[0]
     ref0 = pencil.response_resolvent(A, B, S, sys_.dip, [0.0], 0.0)[0]
     assert abs(p0.real - ref0.real) < 1e-8 * abs(ref0.real) and p0.imag == 0.0
+
+
+@pytest.mark.parametrize("scale", [7.5, 9.0, 12.0])
+def test_window_strong_metric(P, scale):
+    """Windows of systems whose second-order metric departs from the identity by 0.13, 0.27 and
+    0.85: its projected inverse from the product form alone, after Newton-Schulz steps, and by
+    the Cholesky route."""
+    sys = gen(31, 6, 18, 50).scaled(scale)
+    A, B, S = dense.assemble(sys, 2)
+    om = pencil.solve_all(A, B, S)[0]
+    w0 = 1.2 * float(om.min())
+    with P.Handle.from_system(sys, order=2) as h:
+        e, vec, f, info = h.window_solve(w0, 4)
+    _check_window(sys, 2, w0, 4, e, vec, f, info)

@@ -1,11 +1,9 @@
-// One-workgroup FP64 dense kernels for the projected (subspace) problems.
+// FP64 dense kernels for the projected (subspace) problems of at most 512 vectors.  All of
+// them are chains of dependent steps: what counts is the latency of a step, so short vectors
+// and small matrices sit in registers or LDS and the work of a step is spread over just the
+// waves that shorten it.
 //
-// The subspace of the window solver never exceeds 512 vectors, so its symmetric
-// eigenproblems, Cholesky factors and triangular inverses fit one workgroup: the
-// matrices stay in global memory (L2-resident at these sizes), short vectors in
-// LDS, and every parallel step is a row/column sweep by 1024 threads.
-//
-// Symmetric eigensolver: Householder reduction to tridiagonal form with explicit
+// Symmetric eigensolver (syev_kernel): Householder reduction to tridiagonal form with explicit
 // accumulation of the orthogonal factor, then the implicit QL iteration with
 // Wilkinson-type shifts (the textbook tred2/tql2 pair), with the scalar
 // recurrence run by one thread and each rotation sequence applied to all rows of
@@ -361,143 +359,228 @@ __global__ __launch_bounds__(kT) void trinv_kernel(int n, const double* __restri
 // Spectrum slicing for the projected problem (only the eigenpairs near a target)
 // ---------------------------------------------------------------------------
 
-// Householder tridiagonalization (one workgroup).  d[n], e[n] (e[i] couples i, i+1);
-// Hh[k][n] holds the unit reflector u_k of step k (zero in entries <= k).
-//
-// Step k reflects column k of the trailing block B (rows and columns k+1..n-1):
-// u from that column, q = B u - (u.B u) u, then B -= 2 (u q^T + q u^T).  The kernel is
-// bound by the bandwidth between the L2 and its one CU, so the rank-2 update of step k
-// and the product B' u' of step k+1 share one sweep over the block: column k+1 of the
-// updated block (which defines u') is formed first from the update formula, then every
-// updated element of rows and columns k+2.. is written back and multiplied into B' u'
-// in the same pass (one read and one write per element per step instead of two reads
-// and one write).
-__device__ __forceinline__ void reflector(int m, const double* __restrict__ col, double* __restrict__ u,
-                                          double* red, double& alpha, bool& nonzero) {
-  // u = (col - alpha e_0) / |col - alpha e_0| with alpha = -sign(col_0) |col|
-  double part = 0.0;
-  for (int r = threadIdx.x; r < m; r += blockDim.x) part += col[r] * col[r];
-  const double xx = block_reduce_sum(part, red);
-  const double x0 = col[0];
-  const double xnorm = sqrt(xx);
-  nonzero = xnorm != 0.0;
-  alpha = x0 > 0 ? -xnorm : xnorm;
-  if (!nonzero) return;
-  const double vnorm = sqrt(2.0 * xx - 2.0 * x0 * alpha);
-  for (int r = threadIdx.x; r < m; r += blockDim.x) u[r] = (r == 0 ? col[r] - alpha : col[r]) / vnorm;
-  __syncthreads();
+// Sum over the wave, in every lane: row shifts and row broadcasts (about 150 cycles, a quarter
+// of the time of lane permutes through LDS).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_get(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+  v += dpp_get<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds its sum
+  v += dpp_get<0x112, 0xf>(v);
+  v += dpp_get<0x114, 0xf>(v);
+  v += dpp_get<0x118, 0xf>(v);
+  v += dpp_get<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  v += dpp_get<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+  return __hiloint2double(hi, lo);
 }
 
-__global__ __launch_bounds__(kT) void tridiag_kernel(int n, const double* __restrict__ A, double* __restrict__ W,
-                                                     double* __restrict__ dout, double* __restrict__ eout,
-                                                     double* __restrict__ Hh) {
-  __shared__ double u[kMaxN], q[kMaxN], un[kMaxN], qn[kMaxN], col[kMaxN];
-  __shared__ double red[40];
-  const int tid = threadIdx.x;
-  const long nn = (long)n * n;
-  for (long i = tid; i < nn; i += kT) {
-    W[i] = A[i];
-    Hh[i] = 0.0;
-  }
-  __syncthreads();
-  // q = B u for the block of step k (rows/columns k+1..k+m), u in LDS
-  auto symv = [&](int k, int m) {
-    for (int r = tid; r < m; r += kT) {
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Householder tridiagonalization: d[n], e[n] (e[i] couples i, i+1); Hh[k][n] holds the unit
+// reflector u_k of step k (zero in entries <= k).
+//
+// Step k reflects column k of the trailing block B (rows and columns k+1..n-1): u from that
+// column, q = B u - (u.B u) u, then B -= 2 (u q^T + q u^T).  The n - 2 steps depend on each
+// other, and one CU cannot hold the matrix (1.8 MB at n = 480), so one workgroup spends 7 us
+// (n = 100) to 12 us (n = 400) a step in sweeps through the L2 and block-wide reductions.
+// Here the matrix stays in registers: 64 waves (16 workgroups of 4, one SIMD each), wave w
+// holding the columns 64 t + w, lane l the rows 64 s + l.  Every wave keeps u, q and the next
+// column whole (row r in lane r % 64) and computes all scalars itself, from the same values in
+// the same order, so a step needs one exchange and no barrier: each wave publishes q_c of its
+// columns, the owner of column k+1 that column as it was before the update, and each wave
+// reads both back.  A value is its own flag: the exchange (2 n doubles per step, a fresh row
+// for every step) starts filled with kUnset, a NaN that no published value equals, and is
+// written and read with relaxed device-scope atomics, so it holds whichever XCDs the
+// workgroups run on.  Which lanes and register slots a step touches depends on k / 64 alone:
+// phase P handles the steps with k + 1 in slot P.  Measured in window solves: 0.27 ms at
+// n = 128, 0.58 ms at n = 240 and 1.13 ms at n = 400 (2.4-2.8 us a step, mostly the exchange),
+// against 0.78 ms at n = 100 and 3.0 ms on average over n = 40..430 in one workgroup.
+//
+// Every wait ends: the waves take 16 slots of one workgroup each, all waves that a wait depends
+// on are in the same grid, other kernels' workgroups end by themselves, and a wave that has
+// polled kPolls times (seconds) reports in *err and leaves.
+constexpr unsigned long long kUnset = ~0ull;
+constexpr int kPolls = 1 << 22;
+constexpr int kTriWaves = 64;
+
+__global__ void exchange_fill_kernel(long n, unsigned long long* __restrict__ x, int* __restrict__ err) {
+  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) x[i] = kUnset;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *err = 0;
+}
+
+__device__ __forceinline__ void publish(unsigned long long* p, double v) {
+  unsigned long long b = v == v ? (unsigned long long)__double_as_longlong(v) : 0x7ff8000000000000ull;
+  __hip_atomic_store(p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int S>
+struct TriState {
+  double a[S][S];  // [t][s]: rows 64 s + lane of column 64 t + w
+  double col[S];   // column k of the updated matrix
+};
+
+// Steps k with k + 1 in [64 P, 64 P + 63]; false when a wait gave up.
+template <int P, int S>
+__device__ __forceinline__ bool tri_phase(TriState<S>& st, int n, int w, int lane, unsigned long long* ex,
+                                          double* __restrict__ dout, double* __restrict__ eout,
+                                          double* __restrict__ Hh, int* err) {
+  const int k1 = min(64 * P + 62, n - 3);
+  for (int k = P ? 64 * P - 1 : 0; k <= k1; ++k) {
+    const int nl = (k + 1) & 63;
+    // reflector of column k
+    double u[S], q[S], cn[S], qc[S];
+    double part = 0.0;
+#pragma unroll
+    for (int t = P; t < S; ++t) {
+      u[t] = 64 * t + lane > k ? st.col[t] : 0.0;
+      part = fma(u[t], u[t], part);
+    }
+    const double xx = wave_total(part);
+    const double x0 = lane_value(u[P], nl);
+    double alpha = 0.0, rv = 0.0;
+    if (xx != 0.0) {
+      alpha = x0 > 0.0 ? -sqrt(xx) : sqrt(xx);
+      rv = 1.0 / sqrt(2.0 * xx - 2.0 * x0 * alpha);
+    }
+    if (lane == nl) u[P] -= alpha;
+#pragma unroll
+    for (int t = P; t < S; ++t) u[t] *= rv;
+    // q of the own columns, published as they come
+    unsigned long long* eq = ex + (long)k * 2 * n;
+    unsigned long long* ec = eq + n;
+    if (w == nl) {
+#pragma unroll
+      for (int s = P; s < S; ++s) {
+        const int r = 64 * s + lane;
+        if (r > k && r < n) publish(ec + r, st.a[P][s]);
+      }
+    }
+#pragma unroll
+    for (int t = P; t < S; ++t) {
       double acc = 0.0;
-      for (int cc = 0; cc < m; ++cc) acc += W[(long)(k + 1 + cc) * n + (k + 1 + r)] * u[cc];
-      q[r] = acc;
-    }
-    __syncthreads();
-  };
-  // reflector and product of step k from the stored column k (no pending update)
-  bool refl = false;
-  double alpha = 0.0;
-  auto start_step = [&](int k) {
-    const int m = n - k - 1;
-    for (int r = tid; r < m; r += kT) col[r] = W[(long)(k + 1 + r) * n + k];
-    __syncthreads();
-    reflector(m, col, u, red, alpha, refl);
-    if (refl) symv(k, m);
-  };
-  if (n >= 3) start_step(0);
-  for (int k = 0; k + 2 < n; ++k) {
-    const int m = n - k - 1;
-    if (tid == 0) dout[k] = W[(long)k * n + k];
-    if (!refl) {
-      // column k is already reduced: nothing to apply
-      if (tid == 0) eout[k] = 0.0;
-      __syncthreads();
-      if (k + 3 < n) start_step(k + 1);
-      continue;
-    }
-    double kp = 0.0;
-    for (int r = tid; r < m; r += kT) kp += u[r] * q[r];
-    const double K = block_reduce_sum(kp, red);
-    for (int r = tid; r < m; r += kT) {
-      q[r] = q[r] - K * u[r];
-      Hh[(long)k * n + k + 1 + r] = u[r];
-    }
-    if (tid == 0) eout[k] = alpha;
-    __syncthreads();
-    if (k + 3 < n) {
-      // column k+1 of the updated block (rows k+2..) and its diagonal element
-      for (int r = tid + 1; r < m; r += kT)
-        col[r - 1] = W[(long)(k + 1 + r) * n + (k + 1)] - 2.0 * (u[r] * q[0] + q[r] * u[0]);
-      if (tid == 0) W[(long)(k + 1) * n + (k + 1)] -= 2.0 * (u[0] * q[0] + q[0] * u[0]);
-      __syncthreads();
-      bool nref = false;
-      double nalpha = 0.0;
-      reflector(m - 1, col, un, red, nalpha, nref);
-      // fused sweep over rows/columns k+2..n-1: update, and accumulate B' u'
-      for (int c = tid + 1; c < m; c += kT) {
-        const double qc = q[c], uc = u[c];
-        double* Wc = W + (long)(k + 1) * n + (k + 1 + c);  // element (row r, this column) at Wc[r * n]
-        double acc = 0.0;
-        int r = 1;
-        // twelve rows per batch: the loads are issued before any store of the batch, so
-        // they are in flight together (a store to W could otherwise alias a later load)
-        for (; r + 12 <= m; r += 12) {
-          double w[12];
 #pragma unroll
-          for (int t = 0; t < 12; ++t) w[t] = Wc[(long)(r + t) * n];
+      for (int s = P; s < S; ++s) acc = fma(st.a[t][s], u[s], acc);
+      qc[t] = wave_total(acc);
+      const int c = 64 * t + w;
+      if (lane == 0 && c > k && c < n) publish(eq + c, qc[t]);
+    }
+    if (w == (k & (kTriWaves - 1))) {
 #pragma unroll
-          for (int t = 0; t < 12; ++t) {
-            w[t] = w[t] - 2.0 * (u[r + t] * qc + q[r + t] * uc);
-            Wc[(long)(r + t) * n] = w[t];
-            if (nref) acc += w[t] * un[r + t - 1];
-          }
-        }
-        for (; r < m; ++r) {
-          const double w = Wc[(long)r * n] - 2.0 * (u[r] * qc + q[r] * uc);
-          Wc[(long)r * n] = w;
-          if (nref) acc += w * un[r - 1];
-        }
-        qn[c - 1] = acc;
+      for (int t = 0; t < S; ++t) {
+        const int r = 64 * t + lane;
+        if (r < n) Hh[(long)k * n + r] = t >= P ? u[t] : 0.0;
       }
-      __syncthreads();
-      for (int r = tid; r < m - 1; r += kT) {
-        u[r] = un[r];
-        q[r] = qn[r];
+      if (lane == 0) eout[k] = alpha;
+    }
+    // all of q and the next column
+    for (int it = 0;; ++it) {
+      bool ok = true;
+      unsigned long long bq[S], bc[S];
+#pragma unroll
+      for (int t = P; t < S; ++t) {
+        const int r = 64 * t + lane;
+        const bool act = r > k && r < n;
+        bq[t] = act ? __hip_atomic_load(eq + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+        bc[t] = act ? __hip_atomic_load(ec + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
       }
-      refl = nref;
-      alpha = nalpha;
-      __syncthreads();
-    } else {
-      const long mm = (long)m * m;
-      for (long idx = tid; idx < mm; idx += kT) {
-        const int r = (int)(idx / m), cc = (int)(idx % m);
-        W[(long)(k + 1 + r) * n + (k + 1 + cc)] -= 2.0 * (u[r] * q[cc] + q[r] * u[cc]);
+#pragma unroll
+      for (int t = P; t < S; ++t) {
+        ok = ok && bq[t] != kUnset && bc[t] != kUnset;
+        q[t] = __longlong_as_double((long long)bq[t]);
+        cn[t] = __longlong_as_double((long long)bc[t]);
       }
-      __syncthreads();
+      if (__all(ok)) break;
+      if (it >= kPolls) {
+        if (lane == 0) *err = 1;
+        return false;
+      }
+    }
+    part = 0.0;
+#pragma unroll
+    for (int t = P; t < S; ++t) part = fma(u[t], q[t], part);
+    const double K = wave_total(part);
+#pragma unroll
+    for (int t = P; t < S; ++t) q[t] = fma(-K, u[t], q[t]);
+    const double u2 = -2.0 * lane_value(u[P], nl), q2 = -2.0 * lane_value(q[P], nl);
+#pragma unroll
+    for (int t = P; t < S; ++t) st.col[t] = fma(u[t], q2, fma(q[t], u2, cn[t]));
+    if (w == nl && lane == nl) dout[k + 1] = st.col[P];
+#pragma unroll
+    for (int t = P; t < S; ++t) {
+      const double uc = lane_value(u[t], w);
+      const double uc2 = -2.0 * uc, qc2 = -2.0 * fma(-K, uc, qc[t]);
+#pragma unroll
+      for (int s = P; s < S; ++s) st.a[t][s] = fma(u[s], qc2, fma(q[s], uc2, st.a[t][s]));
     }
   }
-  if (tid == 0) {
-    if (n >= 2) {
-      dout[n - 2] = W[(long)(n - 2) * n + (n - 2)];
-      eout[n - 2] = W[(long)(n - 1) * n + (n - 2)];
+  if constexpr (P + 1 < S)
+    return tri_phase<P + 1, S>(st, n, w, lane, ex, dout, eout, Hh, err);
+  else
+    return true;
+}
+
+template <int S>
+__global__ __launch_bounds__(256, 2) void tridiag_kernel(int n, const double* __restrict__ A,
+                                                         unsigned long long* ex, double* __restrict__ dout,
+                                                         double* __restrict__ eout, double* __restrict__ Hh,
+                                                         int* err) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (w >= n) return;
+  TriState<S> st;
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int c = 64 * t + w;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int r = 64 * s + lane;
+      st.a[t][s] = r < n && c < n ? A[(long)c * n + r] : 0.0;  // A is symmetric
     }
-    dout[n - 1] = W[(long)(n - 1) * n + (n - 1)];
-    eout[n - 1] = 0.0;
+    st.col[t] = 64 * t + lane < n ? A[64 * t + lane] : 0.0;
+  }
+  if (w == 0 && lane == 0) dout[0] = st.col[0];
+  if (!tri_phase<0, S>(st, n, w, lane, ex, dout, eout, Hh, err)) return;
+  // the last 2 x 2 block: column n-2 is in col, d[n-1] in the owner of column n-1
+#pragma unroll
+  for (int t = 0; t < S; ++t) {
+    const int r = 64 * t + lane;
+    if (r == n - 1 && w == 0) {
+      if (n >= 2) eout[n - 2] = st.col[t];
+      eout[n - 1] = 0.0;
+    }
+    if (r == n - 1 && 64 * t + w == n - 1) dout[n - 1] = st.a[t][t];
+  }
+}
+
+template <int S>
+void launch_tridiag(int n, const double* A, double* ex, double* d, double* e, double* Hh, int* err, hipStream_t s) {
+  unsigned long long* x = reinterpret_cast<unsigned long long*>(ex);
+  const long cells = 2L * n * std::max(0, n - 2);
+  exchange_fill_kernel<<<(int)std::max(1L, std::min(256L, (cells + 255) / 256)), 256, 0, s>>>(cells, x, err);
+  PPW_LAUNCH_CHECK();
+  const int waves = std::min(n, kTriWaves);
+  tridiag_kernel<S><<<(waves + 3) / 4, 256, 0, s>>>(n, A, x, d, e, Hh, err);
+  PPW_LAUNCH_CHECK();
+}
+
+void tridiagonalize(int n, const double* A, double* ex, double* d, double* e, double* Hh, int* err, hipStream_t s) {
+  switch ((n + 63) / 64) {
+    case 1: return launch_tridiag<1>(n, A, ex, d, e, Hh, err, s);
+    case 2: return launch_tridiag<2>(n, A, ex, d, e, Hh, err, s);
+    case 3: return launch_tridiag<3>(n, A, ex, d, e, Hh, err, s);
+    case 4: return launch_tridiag<4>(n, A, ex, d, e, Hh, err, s);
+    case 5: return launch_tridiag<5>(n, A, ex, d, e, Hh, err, s);
+    case 6: return launch_tridiag<6>(n, A, ex, d, e, Hh, err, s);
+    case 7: return launch_tridiag<7>(n, A, ex, d, e, Hh, err, s);
+    default: return launch_tridiag<8>(n, A, ex, d, e, Hh, err, s);
   }
 }
 
@@ -856,26 +939,6 @@ __global__ void tridiag_apply_kernel(int n, int p, const double* __restrict__ d,
   }
 }
 
-// Sum over the wave, in every lane: row shifts and row broadcasts (about 150 cycles, a quarter
-// of the time of lane permutes through LDS).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_get(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_total(double v) {
-  v += dpp_get<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds its sum
-  v += dpp_get<0x112, 0xf>(v);
-  v += dpp_get<0x114, 0xf>(v);
-  v += dpp_get<0x118, 0xf>(v);
-  v += dpp_get<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
-  v += dpp_get<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-  return __hiloint2double(hi, lo);
-}
-
 // Z[r][j] = (H_0 ... H_{n-3} v_j)[r], one wave per vector with the vector in registers (8 per
 // lane up to n = 512): a reflector costs one wave sum and no barrier, and the next one's
 // elements are loaded meanwhile.  At n = 480: 60 us against 150 us with a workgroup per vector.
@@ -985,14 +1048,14 @@ void small_syev(int n, const double* A, double* w, double* Z, hipStream_t s, dou
 }
 
 size_t partial_syev_scratch(int n, int p) {
-  return (size_t)2 * n * n + 2 * (size_t)n + 4 * (size_t)p * n + 5 * (size_t)p * p + 2 * (size_t)p + 64;
+  return (size_t)3 * n * n + 2 * (size_t)n + 4 * (size_t)p * n + 5 * (size_t)p * p + 2 * (size_t)p + 64;
 }
 
 int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch,
                  hipStream_t s) {
   if (n < 1 || n > kMaxN || p < 1 || p > 64 || p > n) throw InvalidArg("partial_syev: size out of range");
-  double* W = scratch;
-  double* Hh = W + (size_t)n * n;
+  double* ex = scratch;  // the tridiagonalization's exchange
+  double* Hh = ex + (size_t)2 * n * n;
   double* d = Hh + (size_t)n * n;
   double* e = d + n;
   double* V = e + n;
@@ -1005,10 +1068,9 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   double* T1 = UG + (size_t)p * p;
   double* H = T1 + (size_t)p * p;
   double* UH = H + (size_t)p * p;
-  tridiag_kernel<<<1, kT, 0, s>>>(n, A, W, d, e, Hh);
-  PPW_LAUNCH_CHECK();
   double* cand = work;
-  int* nc = reinterpret_cast<int*>(work + 2 * p);
+  int* nc = reinterpret_cast<int*>(work + 2 * p);  // a count, and whether the tridiagonalization gave up
+  tridiagonalize(n, A, ex, d, e, Hh, nc + 1, s);
   multisect_kernel<<<2 * p, 64, 0, s>>>(n, d, e, target, p, cand, nc);
   PPW_LAUNCH_CHECK();
   inverse_iteration_kernel<<<p, 64, 0, s>>>(n, d, e, target, p, cand, nc, lam, V);
@@ -1018,7 +1080,13 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   g.M = p; g.N = p; g.K = n; g.transA = 0; g.lda = n; g.transB = 1; g.ldb = n; g.ldc = p;
   gemm_f64(g, 1.0, V, V, 0.0, G, s);
   // (T1 is p x q, ld q; R goes to UG)
-  const int q = orth_factors(p, G, 1e-12, T1, UG, nc, s);
+  orth_factors_kernel<<<1, 64, 0, s>>>(p, G, 1e-12, T1, UG, nc);
+  PPW_LAUNCH_CHECK();
+  int got[2] = {0, 0};
+  PPW_HIP(hipMemcpyAsync(got, nc, sizeof(got), hipMemcpyDeviceToHost, s));
+  PPW_HIP(hipStreamSynchronize(s));
+  if (got[1]) throw DeviceError("tridiagonalization: a workgroup waited in vain for the others");
+  const int q = got[0];
   if (q == 0) throw Unstable("partial_syev: inverse iteration produced no independent vectors");
   // V1[j][r] = sum_t T1[t][j] V[t][r]
   GemmDesc a;

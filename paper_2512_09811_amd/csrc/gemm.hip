@@ -878,7 +878,7 @@ int gemm_group_impl(const std::vector<GemmCall<T>>& calls, hipStream_t s) {
 // keep their FP32 strides (a multiple of 8 values) and an FP32 array is split in place.
 //
 // Kernel: WM x WN wave64s on BM x BN tiles (4 x 2 on 256 x 256 at one workgroup per CU,
-// 2 x 2 on 128 x 128 or 64 x 64 at two), ST LDS stages; a k tile is 32 values = 4 chunks
+// 2 x 2 on 128 x 128 or 64 x 64 at two), two LDS buffers; a k tile is 32 values = 4 chunks
 // = 128 B per row, loaded straight into LDS (global_load_lds_dwordx4) in the swizzled
 // slot layout of the FP64 kernel (16-byte slot s of row r at 8r + (s ^ ((r >> 1) & 7)),
 // logical slot 2c holding chunk c's hi parts and 2c + 1 its lo parts), so a fragment
@@ -898,10 +898,9 @@ constexpr int kSbBK = 32;
 __device__ __forceinline__ int row32(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
 // WM x WN waves (64 WM WN threads), each owning a (BM / WM) x (BN / WN) block of the tile;
-// ST LDS buffers, the loads of tile kt + ST - 1 issued while tile kt is multiplied; OCC
-// workgroups per CU (register budget).  TAG only distinguishes kernel symbols (1: the
+// two LDS buffers; OCC workgroups per CU (register budget).  TAG only distinguishes kernel symbols (1: the
 // amplitude contraction, so that profiles can attribute its time); the code is identical.
-template <int BM, int BN, int WM, int WN, int ST, int OCC, int TAG = 0>
+template <int BM, int BN, int WM, int WN, int OCC, int TAG = 0>
 __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
     GemmDesc d, float alpha, const float* __restrict__ A, const float* __restrict__ B, float beta,
     float* __restrict__ C) {
@@ -910,9 +909,13 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
   constexpr int SA = BM * BK, SB = BN * BK;       // storage floats per buffer
   constexpr int CA = BM / (8 * NW), CB = BN / (8 * NW);  // 1 KB wave loads (8 rows each) per operand tile
   static_assert(CA * 8 * NW == BM && CB * 8 * NW == BN && TM * 32 == WTM && TN * 32 == WTN, "tile shape");
-  static_assert(ST >= 2 && ST <= 4 && (ST - 2) * (CA + CB) <= 63, "stages");
-  __shared__ __attribute__((aligned(16))) float As[ST][SA];
-  __shared__ __attribute__((aligned(16))) float Bs[ST][SB];
+  // separate arrays, and a loop unrolled by two: a buffer being filled and the buffer being
+  // read are distinct objects to the compiler, which otherwise waits for the loads in flight
+  // before every fragment read
+  __shared__ __attribute__((aligned(16))) float As0[SA];
+  __shared__ __attribute__((aligned(16))) float As1[SA];
+  __shared__ __attribute__((aligned(16))) float Bs0[SB];
+  __shared__ __attribute__((aligned(16))) float Bs1[SB];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave / WN, wn = wave % WN;
   const int tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
   int tm, tn;
@@ -938,13 +941,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
   // a ragged last k tile
   const int nkt = (d.K + BK - 1) / BK;
   const int ndma = rows_ok ? d.K / BK : 0;
-  auto fill = [&](int buf, int kt) {
+  auto fill = [&](float* Ab, float* Bb, int kt, auto whole) {
     const int k0 = kt * BK;
     const float* Ak = At + k0;
     const float* Bk = Bt + k0;
-    float* Ab = As[buf];
-    float* Bb = Bs[buf];
-    if (kt < ndma) {
+    if (decltype(whole)::value || kt < ndma) {
 #pragma unroll
       for (int c = 0; c < CA; ++c)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Ak + offA[c]),
@@ -980,50 +981,45 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
   const int rl = lane & 31, hl = lane >> 5;
-  // one k tile = two 16-value steps: the fragment reads of both steps are issued first
-  // (B, then A in MFMA order), so the second step's reads land during the first step's
-  // MFMAs
-  auto tile = [&](int buf) {
-    const float* Ab = As[buf];
-    const float* Bb = Bs[buf];
-    bf16x8_t ah[2][TM], al[2][TM], bh[2][TN], bl[2][TN];
+  // fragments of 16-value step st of the k tile in buffer (Ab, Bb)
+  struct Frags {
+    bf16x8_t ah[TM], al[TM], bh[TN], bl[TN];
+  };
+  auto frags = [&](const float* Ab, const float* Bb, int st, Frags& f) {
+    const int ch = 2 * st + hl;
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
-      const int ch = 2 * st + hl;
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int r = wm * WTM + i * 32 + rl;
-        ah[st][i] = *reinterpret_cast<const bf16x8_t*>(Ab + 4 * swz16(r, 2 * ch));
-        al[st][i] = *reinterpret_cast<const bf16x8_t*>(Ab + 4 * swz16(r, 2 * ch + 1));
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int r = wn * WTN + j * 32 + rl;
-        bh[st][j] = *reinterpret_cast<const bf16x8_t*>(Bb + 4 * swz16(r, 2 * ch));
-        bl[st][j] = *reinterpret_cast<const bf16x8_t*>(Bb + 4 * swz16(r, 2 * ch + 1));
-      }
+    for (int i = 0; i < TM; ++i) {
+      const int r = wm * WTM + i * 32 + rl;
+      f.ah[i] = *reinterpret_cast<const bf16x8_t*>(Ab + 4 * swz16(r, 2 * ch));
+      f.al[i] = *reinterpret_cast<const bf16x8_t*>(Ab + 4 * swz16(r, 2 * ch + 1));
     }
-    // per step and column block: the hi-lo products of its row blocks, then lo-hi, then
-    // hi-hi (consecutive MFMAs accumulate into different blocks, each element still sums
-    // hl, lh, hh in that order, and a column block's B fragments die once it is done)
 #pragma unroll
-    for (int st = 0; st < 2; ++st)
+    for (int j = 0; j < TN; ++j) {
+      const int r = wn * WTN + j * 32 + rl;
+      f.bh[j] = *reinterpret_cast<const bf16x8_t*>(Bb + 4 * swz16(r, 2 * ch));
+      f.bl[j] = *reinterpret_cast<const bf16x8_t*>(Bb + 4 * swz16(r, 2 * ch + 1));
+    }
+  };
+  // per column block: the hi-lo products of its row blocks, then lo-hi, then hi-hi
+  // (consecutive MFMAs accumulate into different blocks, each element still sums hl, lh, hh
+  // in that order, and a column block's B fragments die once it is done)
+  auto mma = [&](const Frags& f) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
+    for (int j = 0; j < TN; ++j) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[st][i], bl[st][j], acc[i][j], 0, 0, 0);
+      for (int i = 0; i < TM; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.ah[i], f.bl[j], acc[i][j], 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[st][i], bh[st][j], acc[i][j], 0, 0, 0);
+      for (int i = 0; i < TM; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.al[i], f.bh[j], acc[i][j], 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[st][i], bh[st][j], acc[i][j], 0, 0, 0);
-      }
-    // issue order pinned: the first step's fragment reads, then its MFMAs with the second
-    // step's reads interleaved one by one, then the second step's MFMAs
+      for (int i = 0; i < TM; ++i)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.ah[i], f.bh[j], acc[i][j], 0, 0, 0);
+    }
+  };
+  // issue order pinned: one step's MFMAs with the next step's fragment reads between them
+  auto interleave = [&]() {
     constexpr int R = 2 * (TM + TN), Mf = 3 * TM * TN, P = R < Mf ? R : Mf;
-    __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
 #pragma unroll
     for (int n = 0; n < P; ++n) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -1031,34 +1027,51 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
     }
     if constexpr (Mf > P) __builtin_amdgcn_sched_group_barrier(0x008, Mf - P, 0);
     if constexpr (R > P) __builtin_amdgcn_sched_group_barrier(0x100, R - P, 0);
-    __builtin_amdgcn_sched_group_barrier(0x008, Mf, 0);
   };
-  // vmcnt(n), other counters left alone (gfx9 s_waitcnt encoding)
-  constexpr int kWaitKeep = 0x0F70 | (((ST - 2) * (CA + CB)) & 15) | (((((ST - 2) * (CA + CB)) >> 4) & 3) << 14);
-#pragma unroll
-  for (int s0 = 0; s0 + 1 < ST; ++s0)
-    if (s0 < nkt) fill(s0, s0);
-  if (ST > 2 && ST - 1 <= ndma)  // tile 0 has landed
-    __builtin_amdgcn_s_waitcnt(kWaitKeep);
-  else
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-  __syncthreads();
-  int buf = 0;
-  for (int kt = 0; kt < nkt; ++kt) {
-    const int kn = kt + ST - 1;
-    if (kn < nkt) fill(buf == 0 ? ST - 1 : buf - 1, kn);
-    tile(buf);
-    // tile kt + 1 must have landed for every wave: the loads of the tiles after it may stay
-    // in flight when they all went straight into LDS
-    if (kt + 1 < nkt) {
-      if (ST > 2 && kt + ST - 1 < ndma)
-        __builtin_amdgcn_s_waitcnt(kWaitKeep);
-      else
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-    }
+  // A k tile is two 16-value steps, and its one barrier stands between them: the fragments of a
+  // tile's second step are read during the MFMAs of its first, those of the next tile's first
+  // step during the MFMAs of its second (its loads into LDS, issued a whole tile earlier, are
+  // waited for at the barrier), and the buffer that the barrier frees is refilled at once.  So
+  // no MFMA waits for a read that was not issued a step earlier: with the barrier at the end of
+  // the tile, both waves of a SIMD read 12 fragments each with the matrix cores idle (768 cycles
+  // of LDS time in every 3100 of MFMA time).  Measured on the amplitude contraction at
+  // 128/512/1536 (33792 x 24576 x 65536): matrix units busy 60 -> 80 % of the active cycles and
+  // 259 -> 242 ms a launch (420 -> 450 TF/s).  The clock falls from 1.97 to 1.65 GHz as they fill
+  // (2.4 nominal): the launch is bound by power, as the library's bf16 product is (1323 TF/s at
+  // 16384^3, 441 per three products).
+  constexpr int kWaitAll = 0x0F70;  // vmcnt(0), other counters left alone (gfx9 s_waitcnt encoding)
+  auto reduce = [&](auto whole) {
+    Frags f0, f1;
+    fill(As0, Bs0, 0, whole);
+    __builtin_amdgcn_s_waitcnt(kWaitAll);
     __syncthreads();
-    buf = buf + 1 == ST ? 0 : buf + 1;
-  }
+    if (nkt > 1) fill(As1, Bs1, 1, whole);
+    frags(As0, Bs0, 0, f0);
+    auto step = [&](float* Ac, float* Bc, const float* An, const float* Bn, int kt) {
+      frags(Ac, Bc, 1, f1);
+      mma(f0);
+      interleave();
+      __builtin_amdgcn_s_waitcnt(kWaitAll);
+      __syncthreads();
+      if (kt + 2 < nkt) fill(Ac, Bc, kt + 2, whole);
+      frags(An, Bn, 0, f0);
+      mma(f1);
+      interleave();
+    };
+    for (int kt = 0; kt + 1 < nkt; kt += 2) {
+      step(As0, Bs0, As1, Bs1, kt);
+      if (kt + 2 < nkt) step(As1, Bs1, As0, Bs0, kt + 1);
+    }
+    frags((nkt & 1) ? As0 : As1, (nkt & 1) ? Bs0 : Bs1, 1, f1);
+    mma(f0);
+    interleave();
+    mma(f1);
+  };
+  // whole tiles get a loop without the ragged path, whose addresses would not fit the registers
+  if (ndma == nkt)
+    reduce(std::true_type{});
+  else
+    reduce(std::false_type{});
   // epilogue: column offsets once per thread, row offsets once per accumulator row
   const bool mapped = (d.cRm | d.cRn) != 0;
   long coff[TN];
@@ -1137,19 +1150,19 @@ void gemm_sbf16(const GemmDesc& d, float alpha, const float* A, const float* B, 
     if (d.tile == 256 || (d.tile != 128 && r256 * 2.0 / 1.05 < r128)) {
       const long wgs = checked_workgroups<256, 256, kSbBK>(d);
       if (amplitude)
-        gemm_sbf16_kernel<256, 256, 4, 2, 2, 1, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(d, alpha, A, B, beta, C);
+        gemm_sbf16_kernel<256, 256, 4, 2, 1, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(d, alpha, A, B, beta, C);
       else
-        gemm_sbf16_kernel<256, 256, 4, 2, 2, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(d, alpha, A, B, beta, C);
+        gemm_sbf16_kernel<256, 256, 4, 2, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(d, alpha, A, B, beta, C);
     } else {
       const long wgs = checked_workgroups<128, 128, kSbBK>(d);
       if (amplitude)
-        gemm_sbf16_kernel<128, 128, 2, 2, 2, 2, 1><<<dim3((unsigned)wgs), kThreads, 0, s>>>(d, alpha, A, B, beta, C);
+        gemm_sbf16_kernel<128, 128, 2, 2, 2, 1><<<dim3((unsigned)wgs), kThreads, 0, s>>>(d, alpha, A, B, beta, C);
       else
-        gemm_sbf16_kernel<128, 128, 2, 2, 2, 2><<<dim3((unsigned)wgs), kThreads, 0, s>>>(d, alpha, A, B, beta, C);
+        gemm_sbf16_kernel<128, 128, 2, 2, 2><<<dim3((unsigned)wgs), kThreads, 0, s>>>(d, alpha, A, B, beta, C);
     }
   } else {
     const long wgs = checked_workgroups<64, 64, kSbBK>(d);
-    gemm_sbf16_kernel<64, 64, 2, 2, 2, 2><<<dim3((unsigned)wgs), kThreads, 0, s>>>(d, alpha, A, B, beta, C);
+    gemm_sbf16_kernel<64, 64, 2, 2, 2><<<dim3((unsigned)wgs), kThreads, 0, s>>>(d, alpha, A, B, beta, C);
   }
   PPW_LAUNCH_CHECK();
 }

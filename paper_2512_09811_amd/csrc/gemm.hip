@@ -73,6 +73,44 @@ __device__ __forceinline__ void tile_coords(int id, int tiles_m, int tiles_n, in
   tn = r / gsize;
 }
 
+// Tiles of a product whose columns d.sym .. d.sym + M - 1 form a symmetric block with its rows
+// (GemmDesc): in the grouped order, without the columns of a band of 8 tile rows that lie below
+// the block's diagonal for all of them.  Works for host and device.
+constexpr int kBand = 8;
+__host__ __device__ inline int sym_excluded(const GemmDesc& d, int m0, int BN, int& lo) {
+  lo = (int)((d.sym + BN - 1) / BN);
+  const int hi = (int)((d.sym + m0) / BN);
+  return hi > lo ? hi - lo : 0;
+}
+__device__ __forceinline__ bool sym_tile_coords(const GemmDesc& d, long id, int BM, int BN, int tiles_m, int tiles_n,
+                                                int& tm, int& tn) {
+  for (int first = 0; first < tiles_m; first += kBand) {
+    const int gsize = min(tiles_m - first, kBand);
+    int lo;
+    const int ex = sym_excluded(d, first * BM, BN, lo);
+    const long cnt = (long)gsize * (tiles_n - ex);
+    if (id < cnt) {
+      tm = first + (int)(id % gsize);
+      tn = (int)(id / gsize);
+      if (tn >= lo) tn += ex;
+      // a tile of the band that is below the diagonal for its own rows
+      return !((long)tn * BN >= d.sym && (long)tn * BN + BN <= d.sym + (long)tm * BM);
+    }
+    id -= cnt;
+  }
+  return false;
+}
+template <int BM, int BN>
+long sym_tiles(const GemmDesc& d) {
+  const int tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
+  long n = 0;
+  for (int first = 0; first < tiles_m; first += kBand) {
+    int lo;
+    n += (long)std::min(tiles_m - first, kBand) * (tiles_n - sym_excluded(d, first * BM, BN, lo));
+  }
+  return n;
+}
+
 // ---------------------------------------------------------------------------
 // FP64 tiles with both operands contiguous along k (the amplitude contraction and its
 // grouped launches): operand tiles go from global memory straight into LDS
@@ -343,6 +381,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
     return;
   }
   using acc_t = typename Mfma<T>::acc_t;
+  constexpr bool SYM = !AK && !BKC && BM == 128;  // the strips' integrals (B^ov)^T B^ov
   constexpr int PK = 2;   // pad of k-contiguous tiles
   constexpr int PM = 16;  // pad of m/n-contiguous tiles
   constexpr int WTM = BM / 2, WTN = BN / 2;
@@ -366,9 +405,14 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
   const int tiles_m = (d.M + BM - 1) / BM;
   const int tiles_n = (d.N + BN - 1) / BN;
   const long ntiles = (long)tiles_m * tiles_n;
-  const int batch = (int)(flat / ntiles);
+  int batch = (int)(flat / ntiles);
   int tm, tn;
-  tile_coords((int)(flat % ntiles), tiles_m, tiles_n, tm, tn);
+  if (SYM && d.sym >= 0) {
+    batch = 0;
+    if (!sym_tile_coords(d, flat, BM, BN, tiles_m, tiles_n, tm, tn)) return;
+  } else {
+    tile_coords((int)(flat % ntiles), tiles_m, tiles_n, tm, tn);
+  }
   const int m0 = tm * BM, n0 = tn * BN;
   const int b1 = batch / d.nb2, b2 = batch % d.nb2;
 
@@ -684,7 +728,7 @@ void launch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T* C, hi
   // is bit-identical to the unpeeled GEMM.  The peeled part has its own kernel symbol
   // (TAG + 2) so that traces tell the two apart.
   if constexpr (TAG < 2 && BM == 128 && BN == 128) {
-   if (nbatch == 1 && ntiles >= 2 * kResident && d.splitk <= 1) {
+   if (nbatch == 1 && ntiles >= 2 * kResident && d.splitk <= 1 && d.sym < 0) {
     const long rem = ntiles % kResident;
     const int cols = (int)((rem + tiles_m - 1) / tiles_m);
     if (rem > 0 && rem <= kResident / 2 && cols < tiles_n) {
@@ -714,6 +758,19 @@ void launch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T* C, hi
       throw InvalidArg("gemm: workspace too small for the requested reduction splits");
   }
   dim3 grid((unsigned)(ntiles * nbatch), (unsigned)splitk, 1);
+  if (d.sym >= 0) {
+    // tiles left out only in the plain launch of the strips' integrals; elsewhere (64 x 64
+    // tiles, reduction splits) the whole product
+    constexpr bool SYM = !AK && !BKC && BM == 128 && TAG == 0;
+    GemmDesc f = d;
+    if (!SYM || splitk != 1 || nbatch != 1) {
+      f.sym = -1;
+      f.splitk = splitk;
+      launch<T, BM, BN, BK, AK, BKC, TAG>(f, alpha, A, B, beta, C, s, ws);
+      return;
+    }
+    grid.x = (unsigned)sym_tiles<BM, BN>(d);
+  }
   if constexpr (TAG == 0 && BM == 64 && !(std::is_same<T, double>::value && AK && BKC)) {
     // short accumulating reductions: load C before the reduction (same arithmetic)
     if (splitk == 1 && beta != T(0) && total <= 4 && !(d.cRm | d.cRn)) {
@@ -770,6 +827,7 @@ void launch_group(const GemmCall<T>* const* calls, int n, hipStream_t s) {
   for (int i = 0; i < n; ++i) {
     const GemmCall<T>& c = *calls[i];
     g.m[i] = GroupMember<T>{c.d, c.A, c.B, c.C, c.alpha, c.beta, total};
+    g.m[i].d.sym = -1;
     total += checked_workgroups<BM, BN, BK>(c.d);
   }
   g.n = n;
@@ -890,7 +948,6 @@ int gemm_group_impl(const std::vector<GemmCall<T>>& calls, hipStream_t s) {
 // 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.  Ragged tiles (an edge in m, n or k) are
 // copied chunk by chunk through registers into the same layout; values past K inside the
 // last chunk of a row must be zero (split_sbf16 of a zero-padded row leaves them so).
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kSbBK = 32;
@@ -919,7 +976,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave / WN, wn = wave % WN;
   const int tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
   int tm, tn;
-  tile_coords((int)xcd_remap(blockIdx.x, (long)gridDim.x), tiles_m, tiles_n, tm, tn);
+  if (d.sym >= 0) {
+    if (!sym_tile_coords(d, xcd_remap(blockIdx.x, (long)gridDim.x), BM, BN, tiles_m, tiles_n, tm, tn)) return;
+  } else {
+    tile_coords((int)xcd_remap(blockIdx.x, (long)gridDim.x), tiles_m, tiles_n, tm, tn);
+  }
   const int m0 = tm * BM, n0 = tn * BN;
   const float* At = A + (long)m0 * d.lda;
   const float* Bt = B + (long)n0 * d.ldb;
@@ -1101,18 +1162,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
 // In-place split of n / 8 chunks of 8 FP32 values into the chunk layout above.
 __global__ void split_sbf16_kernel(long nchunks, float* __restrict__ x) {
   for (long c = blockIdx.x * (long)blockDim.x + threadIdx.x; c < nchunks; c += (long)gridDim.x * blockDim.x) {
-    f32x4_t* p = reinterpret_cast<f32x4_t*>(x + 8 * c);
+    const f32x4_t* p = reinterpret_cast<const f32x4_t*>(x + 8 * c);
     const f32x4_t a = p[0], b = p[1];
-    bf16x8_t hi, lo;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      hi[t] = (__bf16)a[t];
-      hi[t + 4] = (__bf16)b[t];
-      lo[t] = (__bf16)(a[t] - (float)hi[t]);
-      lo[t + 4] = (__bf16)(b[t] - (float)hi[t + 4]);
-    }
-    *reinterpret_cast<bf16x8_t*>(x + 8 * c) = hi;
-    *reinterpret_cast<bf16x8_t*>(x + 8 * c + 4) = lo;
+    const float w[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+    store_sbf16_chunk(w, x + 8 * c);
   }
 }
 
@@ -1144,17 +1197,19 @@ void gemm_sbf16(const GemmDesc& d, float alpha, const float* A, const float* B, 
     // 386 TF/s): each round of resident 256-tiles holds twice the work of a round of
     // 128-tiles and runs about 1.05 times faster per flop, so the larger tile is taken
     // when its whole rounds finish first
-    const long t256 = (long)((d.M + 255) / 256) * ((d.N + 255) / 256);
-    const long t128 = (long)((d.M + 127) / 128) * ((d.N + 127) / 128);
+    const long t256 = d.sym >= 0 ? sym_tiles<256, 256>(d) : (long)((d.M + 255) / 256) * ((d.N + 255) / 256);
+    const long t128 = d.sym >= 0 ? sym_tiles<128, 128>(d) : (long)((d.M + 127) / 128) * ((d.N + 127) / 128);
     const double r256 = (double)((t256 + kCUs - 1) / kCUs), r128 = (double)((t128 + 2 * kCUs - 1) / (2 * kCUs));
     if (d.tile == 256 || (d.tile != 128 && r256 * 2.0 / 1.05 < r128)) {
-      const long wgs = checked_workgroups<256, 256, kSbBK>(d);
+      checked_workgroups<256, 256, kSbBK>(d);
+      const long wgs = t256;
       if (amplitude)
         gemm_sbf16_kernel<256, 256, 4, 2, 1, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(d, alpha, A, B, beta, C);
       else
         gemm_sbf16_kernel<256, 256, 4, 2, 1><<<dim3((unsigned)wgs), 512, 0, s>>>(d, alpha, A, B, beta, C);
     } else {
-      const long wgs = checked_workgroups<128, 128, kSbBK>(d);
+      checked_workgroups<128, 128, kSbBK>(d);
+      const long wgs = t128;
       if (amplitude)
         gemm_sbf16_kernel<128, 128, 2, 2, 2, 1><<<dim3((unsigned)wgs), kThreads, 0, s>>>(d, alpha, A, B, beta, C);
       else
@@ -1162,7 +1217,9 @@ void gemm_sbf16(const GemmDesc& d, float alpha, const float* A, const float* B, 
     }
   } else {
     const long wgs = checked_workgroups<64, 64, kSbBK>(d);
-    gemm_sbf16_kernel<64, 64, 2, 2, 2><<<dim3((unsigned)wgs), kThreads, 0, s>>>(d, alpha, A, B, beta, C);
+    GemmDesc f = d;
+    f.sym = -1;  // too small to be worth leaving tiles out
+    gemm_sbf16_kernel<64, 64, 2, 2, 2><<<dim3((unsigned)wgs), kThreads, 0, s>>>(f, alpha, A, B, beta, C);
   }
   PPW_LAUNCH_CHECK();
 }

@@ -10,7 +10,8 @@ namespace ppw {
 void permute3(const double* in, double* out, int d0, int d1, int d2, const int perm[3], hipStream_t s);
 
 // Amplitude strip for occupied rows k0 .. k0+ib-1.  S[(k,x)][(l,y)] = (kx|ly) (rows
-// k-local).  Writes (each output optional):
+// k-local; where l lies in the strip too, read only for (l,y) not before (k,x): S is
+// symmetric there).  Writes (t, tEv, tEo together or none; partial optional):
 //   tau[(k,x)][(l,y)] = (2 S[(k,x)][(l,y)] - S[(k,y)][(l,x)]) / D,  D = e_k + e_l - e_x - e_y
 //   t   = S / D
 //   tEv = t * (e_k + e_l - e_y)
@@ -20,11 +21,13 @@ void tau_strip(const double* S, int o, int v, int k0, int ib, const double* eps_
                double* tau, double* t, double* tEv, double* tEo, double* partial, hipStream_t s);
 long tau_blocks(int o, int v, int ib);
 // Same strip built in FP32 (for the reduced-precision product path): tau only, rows of
-// ld >= o v values (columns o v .. ld - 1 are not written).
+// ld >= o v values (columns o v .. ld - 1 are not written, or with split left as they are:
+// zeros); split: in the chunk layout of split_sbf16.
 void tau_strip_f32(const float* S, int o, int v, int k0, int ib, const double* eps_o, const double* eps_v,
-                   float* tau, long ld, hipStream_t s);
+                   float* tau, long ld, bool split, hipStream_t s);
 
-// Deterministic sum of n doubles (single block).
+// Deterministic sum of n doubles into out[0]; out has room for 1 + kSumBlocks doubles.
+constexpr int kSumBlocks = 1024;
 void sum_reduce(const double* x, long n, double* out, hipStream_t s);
 
 // Jacobi/preconditioner diagonals.

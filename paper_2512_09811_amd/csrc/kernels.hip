@@ -54,64 +54,125 @@ __global__ void permute3_kernel(const double* __restrict__ in, double* __restric
   }
 }
 
-template <typename T>
-__global__ void tau_strip_kernel(const T* __restrict__ S, int o, int v, int k0, int ib, const double* __restrict__ eo,
-                                 const double* __restrict__ ev, T* __restrict__ tau, long ldt, double* __restrict__ t,
-                                 double* __restrict__ tEv, double* __restrict__ tEo, double* __restrict__ partial) {
-  // block: one (k_local, l) pair and a 32x32 (x, y) tile; 256 threads, 4 elements each
-  __shared__ T T1[32][33];
-  __shared__ T T2[32][33];
-  const int nt = (v + 31) / 32;
-  const int tile = blockIdx.x;
-  const int tx = tile % nt, ty = tile / nt;   // x tile, y tile
-  const int kl = blockIdx.y;                  // (k_local, l) pair
-  const int kloc = kl / o, l = kl % o;
-  const int k = k0 + kloc;
-  const long N = (long)o * v;
-  const int x0 = tx * 32, y0 = ty * 32;
+// Amplitudes of a strip from its integrals S[(k, x)][(l, y)] (k in the strip, any l).  Bound by
+// the bytes of S and tau.  The element (x, y) also needs S at (y, x), so a workgroup takes the
+// 32 x 32 tiles (X, Y) and (Y, X) of a pair k, l together and S is read once; and where l lies in
+// the strip too, S is read above its diagonal only (row (k, x), column (l, y) with (l, y) not
+// before (k, x): the part the integral GEMM computes) and the pair l, k comes from the tiles of
+// k, l.  SPLIT: tau goes out in the chunk layout of split_sbf16 (v a multiple of 8, so that no
+// chunk crosses a pair).  Measured at 96/384/1152 in FP64, one strip: see tau_strip.
+template <typename T, bool SPLIT>
+__global__ __launch_bounds__(kBlock) void tau_strip_kernel(const T* __restrict__ S, int o, int v, int k0, int ib,
+                                                           const double* __restrict__ eo,
+                                                           const double* __restrict__ ev, T* __restrict__ tau, long ldt,
+                                                           double* __restrict__ t, double* __restrict__ tEv,
+                                                           double* __restrict__ tEo, double* __restrict__ partial) {
+  __shared__ T Ta[32][33];  // S[(k, X)][(l, Y)]
+  __shared__ T Tb[32][33];  // S[(k, Y)][(l, X)]
+  __shared__ T Out[SPLIT ? 32 : 1][33];
+  const int nt = (v + 31) / 32, pairs = nt * (nt + 1) / 2;
+  const int kl = (int)(blockIdx.x / (unsigned)pairs), pr = (int)(blockIdx.x % (unsigned)pairs);
+  const int kloc = kl / o, l = kl % o, k = k0 + kloc, lloc = l - k0;
   const int tid = threadIdx.x;
-  // T1[x][y] = S[(k, x0+x)][(l, y0+y)],  T2[y][x] = S[(k, y0+y)][(l, x0+x)]
-  for (int e = tid; e < 1024; e += 256) {
+  const bool inside = lloc >= 0 && lloc < ib;
+  if (inside && lloc < kloc) {
+    if (partial && tid == 0) partial[blockIdx.x] = 0.0;
+    return;
+  }
+  // tile pair (tx <= ty)
+  int ty = (int)((sqrtf(8.0f * (float)pr + 1.0f) - 1.0f) * 0.5f);
+  while ((ty + 1) * (ty + 2) / 2 <= pr) ++ty;
+  while (ty * (ty + 1) / 2 > pr) --ty;
+  const int tx = pr - ty * (ty + 1) / 2;
+  const int x0 = tx * 32, y0 = ty * 32;
+  const long N = (long)o * v;
+  const bool diag = inside && lloc == kloc;
+  for (int e = tid; e < 1024; e += kBlock) {
     const int r = e / 32, c = e % 32;
-    const int x = x0 + r, y = y0 + c;
-    T a = T(0), b = T(0);
-    if (x < v && y < v) a = S[((long)kloc * v + x) * N + (long)l * v + y];
-    const int yy = y0 + r, xx = x0 + c;
-    if (yy < v && xx < v) b = S[((long)kloc * v + yy) * N + (long)l * v + xx];
-    T1[r][c] = a;
-    T2[r][c] = b;
+    const T a = x0 + r < v && y0 + c < v ? S[((long)kloc * v + x0 + r) * N + (long)l * v + y0 + c] : T(0);
+    Ta[r][c] = a;
+    if (diag) {
+      if (tx != ty || c >= r) Tb[c][r] = a;  // S is symmetric
+    } else if (tx != ty) {
+      Tb[r][c] = y0 + r < v && x0 + c < v ? S[((long)kloc * v + y0 + r) * N + (long)l * v + x0 + c] : T(0);
+    } else {
+      Tb[r][c] = a;
+    }
   }
   __syncthreads();
-  double acc = 0.0;
-  const double ekl = eo[k] + eo[l];
-  for (int e = tid; e < 1024; e += 256) {
-    const int r = e / 32, c = e % 32;
-    const int x = x0 + r, y = y0 + c;
-    if (x < v && y < v) {
-      const double sxy = (double)T1[r][c];
-      const double syx = (double)T2[c][r];
-      const double D = ekl - ev[x] - ev[y];
-      const double tt = sxy / D;
-      const double tu = (2.0 * sxy - syx) / D;
-      const long idx = ((long)kloc * v + x) * N + (long)l * v + y;
-      if (tau) tau[((long)kloc * v + x) * ldt + (long)l * v + y] = (T)tu;
-      if (t) t[idx] = tt;
-      if (tEv) tEv[idx] = tt * (ekl - ev[y]);
-      if (tEo) tEo[idx] = tt * (eo[k] - ev[x] - ev[y]);
-      acc += tu * sxy;
+  if (diag && tx == ty) {  // above its diagonal only: Tb holds the lower half
+    for (int e = tid; e < 1024; e += kBlock) {
+      const int r = e / 32, c = e % 32;
+      if (c < r)
+        Ta[r][c] = Tb[r][c];
+      else
+        Tb[r][c] = Ta[r][c];
     }
+    __syncthreads();
+  }
+  double acc = 0.0;
+  // elements (xb + r, yb + c) of the pair p, q (p local row block ploc): s1 = S there, s2 = S at
+  // the exchanged virtuals
+  auto emit = [&](int p, int ploc, int q, int xb, int yb, auto s1f, auto s2f) {
+    const double epq = eo[p] + eo[q];
+    for (int e = tid; e < 1024; e += kBlock) {
+      const int r = e / 32, c = e % 32;
+      const int x = xb + r, y = yb + c;
+      double tu = 0.0;
+      if (x < v && y < v) {
+        const double sxy = (double)s1f(r, c), syx = (double)s2f(r, c);
+        const double D = epq - ev[x] - ev[y];
+        tu = (2.0 * sxy - syx) / D;
+        const long row = (long)ploc * v + x, col = (long)q * v + y;
+        if (!SPLIT) tau[row * ldt + col] = (T)tu;
+        if (t) {
+          const double tt = sxy / D;
+          const long idx = row * N + col;
+          t[idx] = tt;
+          tEv[idx] = tt * (epq - ev[y]);
+          tEo[idx] = tt * (eo[p] - ev[x] - ev[y]);
+        }
+        acc += tu * sxy;
+      }
+      if (SPLIT) Out[r][c] = (T)tu;
+    }
+    if constexpr (SPLIT) {
+      __syncthreads();
+      if (tid < 128) {
+        const int r = tid / 4, c = (tid % 4) * 8;
+        if (xb + r < v && yb + c < v) {
+          float w[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) w[i] = (float)Out[r][c + i];
+          store_sbf16_chunk(w, (float*)tau + ((long)ploc * v + xb + r) * ldt + (long)q * v + yb + c);
+        }
+      }
+      __syncthreads();
+    }
+  };
+  auto a = [&](int r, int c) { return Ta[r][c]; };
+  auto at = [&](int r, int c) { return Ta[c][r]; };
+  auto b = [&](int r, int c) { return Tb[r][c]; };
+  auto bt = [&](int r, int c) { return Tb[c][r]; };
+  emit(k, kloc, l, x0, y0, a, bt);
+  if (tx != ty) emit(k, kloc, l, y0, x0, b, at);
+  if (inside && lloc > kloc) {  // S of the pair l, k is that of k, l transposed
+    emit(l, lloc, k, x0, y0, bt, a);
+    if (tx != ty) emit(l, lloc, k, y0, x0, at, b);
   }
   if (partial) {
     const double s = block_sum(acc);
-    if (tid == 0) partial[(long)blockIdx.y * gridDim.x + blockIdx.x] = s;
+    if (tid == 0) partial[blockIdx.x] = s;
   }
 }
 
-__global__ void sum_reduce_kernel(const double* __restrict__ x, long n, double* __restrict__ out) {
+// one block per chunk of x; fixed order
+__global__ void sum_reduce_kernel(const double* __restrict__ x, long n, long chunk, double* __restrict__ out) {
+  const long i1 = min(n, (blockIdx.x + 1) * chunk);
   double acc = 0.0;
-  for (long i = threadIdx.x; i < n; i += blockDim.x) acc += x[i];
+  for (long i = blockIdx.x * chunk + threadIdx.x; i < i1; i += blockDim.x) acc += x[i];
   const double s = block_sum(acc);
-  if (threadIdx.x == 0) *out = s;
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 __global__ void diag_integrals_kernel(const double* __restrict__ Bov, const double* __restrict__ Boo,
@@ -343,29 +404,54 @@ void permute3(const double* in, double* out, int d0, int d1, int d2, const int p
 
 long tau_blocks(int o, int v, int ib) {
   const long nt = (v + 31) / 32;
-  return nt * nt * (long)ib * o;
+  return nt * (nt + 1) / 2 * (long)ib * o;
 }
 
+namespace {
+dim3 tau_grid(int o, int v, int ib) {
+  const long n = tau_blocks(o, v, ib);
+  if (n > 2147483647L) throw InvalidArg("amplitude strip: too many workgroups");
+  return dim3((unsigned)n);
+}
+}  // namespace
+
+// One FP64 strip at 96/384/1152 (the whole 36864^2 matrix): 3.6 ms against 6.05 ms when every
+// tile read its transpose as well and S was complete.
 void tau_strip(const double* S, int o, int v, int k0, int ib, const double* eps_o, const double* eps_v, double* tau,
                double* t, double* tEv, double* tEo, double* partial, hipStream_t s) {
-  const int nt = (v + 31) / 32;
-  dim3 grid(nt * nt, ib * o);
-  tau_strip_kernel<double><<<grid, 256, 0, s>>>(S, o, v, k0, ib, eps_o, eps_v, tau, (long)o * v, t, tEv, tEo,
-                                                 partial);
+  tau_strip_kernel<double, false><<<tau_grid(o, v, ib), kBlock, 0, s>>>(S, o, v, k0, ib, eps_o, eps_v, tau, (long)o * v,
+                                                                        t, tEv, tEo, partial);
   PPW_LAUNCH_CHECK();
 }
 
+// split: tau in the chunk layout of split_sbf16, written by this kernel where v is a multiple of
+// 8 (the strip is then not read and written once more: 12.2 -> 4 ms a strip at 128/512/1536),
+// else by a pass over the finished rows.
 void tau_strip_f32(const float* S, int o, int v, int k0, int ib, const double* eps_o, const double* eps_v, float* tau,
-                   long ld, hipStream_t s) {
-  const int nt = (v + 31) / 32;
-  dim3 grid(nt * nt, ib * o);
-  tau_strip_kernel<float><<<grid, 256, 0, s>>>(S, o, v, k0, ib, eps_o, eps_v, tau, ld, nullptr, nullptr, nullptr,
-                                                nullptr);
+                   long ld, bool split, hipStream_t s) {
+  const dim3 g = tau_grid(o, v, ib);
+  if (split && v % 8 == 0) {
+    tau_strip_kernel<float, true><<<g, kBlock, 0, s>>>(S, o, v, k0, ib, eps_o, eps_v, tau, ld, nullptr, nullptr,
+                                                       nullptr, nullptr);
+    PPW_LAUNCH_CHECK();
+    return;
+  }
+  tau_strip_kernel<float, false><<<g, kBlock, 0, s>>>(S, o, v, k0, ib, eps_o, eps_v, tau, ld, nullptr, nullptr, nullptr,
+                                                      nullptr);
   PPW_LAUNCH_CHECK();
+  if (split) split_sbf16((long)ib * v * ld, tau, s);
 }
 
 void sum_reduce(const double* x, long n, double* out, hipStream_t s) {
-  sum_reduce_kernel<<<1, kBlock, 0, s>>>(x, n, out);
+  const long blocks = std::max(1L, std::min<long>(kSumBlocks, n / 1024));
+  if (blocks > 1) {
+    const long chunk = (n + blocks - 1) / blocks;
+    sum_reduce_kernel<<<(unsigned)blocks, kBlock, 0, s>>>(x, n, chunk, out + 1);
+    PPW_LAUNCH_CHECK();
+    x = out + 1;
+    n = blocks;
+  }
+  sum_reduce_kernel<<<1, kBlock, 0, s>>>(x, n, n, out);
   PPW_LAUNCH_CHECK();
 }
 

@@ -210,6 +210,7 @@ Context* setup_context(const SetupParams& p) {
         double* tau_b = store ? c->tau + (size_t)k0 * v * N : tauS;
         // S[(k,x)][(l,y)] = sum_P B_P,kx B_P,ly
         GemmDesc d = gd(nb * v, (int)N, X, 1, N, 0, N, N);
+        d.sym = (long)k0 * v;
         gemm_f64(d, 1.0, c->Bov + (size_t)k0 * v, c->Bov, 0.0, S, s, c->ws);
         tau_strip(S, o, v, k0, nb, c->eps_o, c->eps_v, tau_b, t, tEv, tEo, partial + pofs, s);
         pofs += tau_blocks(o, v, nb);
@@ -231,7 +232,7 @@ Context* setup_context(const SetupParams& p) {
         GemmDesc l = gd(X, nb * v, (int)N, 0, N, 1, N, N);
         gemm_f64(l, 1.0, c->Bov, tau_b, 0.0, c->Lam + (size_t)k0 * v, s, c->ws);
       }
-      double* e2 = c->arena.alloc<double>(1, "emp2");
+      double* e2 = c->arena.alloc<double>(1 + kSumBlocks, "emp2");
       sum_reduce(partial, pofs, e2, s);
       PPW_HIP(hipMemcpyAsync(&c->emp2, e2, sizeof(double), hipMemcpyDeviceToHost, s));
       PPW_HIP(hipStreamSynchronize(s));
@@ -411,12 +412,12 @@ void gemm_hhat_t<float>(const GemmDesc& d, float a, const float* A, const float*
   gemm_f32_hhat(d, a, A, B, b, C, s, ws);
 }
 inline void tau_strip_t(const double* S, int o, int v, int k0, int ib, const double* eo, const double* ev, double* tau,
-                        long, hipStream_t s) {
+                        long, bool, hipStream_t s) {
   tau_strip(S, o, v, k0, ib, eo, ev, tau, nullptr, nullptr, nullptr, nullptr, s);
 }
 inline void tau_strip_t(const float* S, int o, int v, int k0, int ib, const double* eo, const double* ev, float* tau,
-                        long ld, hipStream_t s) {
-  tau_strip_f32(S, o, v, k0, ib, eo, ev, tau, ld, s);
+                        long ld, bool split, hipStream_t s) {
+  tau_strip_f32(S, o, v, k0, ib, eo, ev, tau, ld, split, s);
 }
 
 // Operands and workspace of one precision.
@@ -669,24 +670,21 @@ void contract(Context& c, const Ops<T>& t, Emit<T>& e, int order, int k, const T
     const int r1 = std::min(rg.i1 < 0 ? o : rg.i1, o);
     for (int i0 = std::max(rg.i0, 0); i0 < r1; i0 += ib) {
       const int nb = std::min(ib, r1 - i0);
-      if (t.sbf) {
-        // (kx|ly) of the strip rows from the split transposed B^ov (rows of X8 values)
-        const long lx = c.X8;
-        e.gemm(gd(nb * v, (int)N, X, 0, lx, 1, lx, N), one, t.BovT + (size_t)i0 * v * lx, t.BovT, zero, t.S, c.ws,
-               2);
-      } else {
-        e.gemm(gd(nb * v, (int)N, X, 1, N, 0, N, N), one, t.Bov + (size_t)i0 * v, t.Bov, zero, t.S, c.ws);
-      }
+      // (kx|ly) of the strip rows; in split BF16 from the split transposed B^ov (rows of X8 values)
+      const long lx = c.X8;
+      GemmDesc di = t.sbf ? gd(nb * v, (int)N, X, 0, lx, 1, lx, N) : gd(nb * v, (int)N, X, 1, N, 0, N, N);
+      di.sym = (long)i0 * v;
+      if (t.sbf)
+        e.gemm(di, one, t.BovT + (size_t)i0 * v * lx, t.BovT, zero, t.S, c.ws, 2);
+      else
+        e.gemm(di, one, t.Bov + (size_t)i0 * v, t.Bov, zero, t.S, c.ws);
       {
         const T* Sst = t.S;
         T* tw = t.tau_w;
         const double *eo = c.eps_o, *evv = c.eps_v;
         const long ldst = t.ldst;
         const bool sbf = t.sbf;
-        e.call([=](hipStream_t st) {
-          tau_strip_t(Sst, o, v, i0, nb, eo, evv, tw, ldst, st);
-          if (sbf) split_sbf16((long)nb * v * ldst, reinterpret_cast<float*>(tw), st);
-        });
+        e.call([=](hipStream_t st) { tau_strip_t(Sst, o, v, i0, nb, eo, evv, tw, ldst, sbf, st); });
       }
       GemmDesc d = gd(nb * v, (int)kX, (int)N, 0, t.ldst, 1, t.ldG, X);
       d.cRn = X;
@@ -725,7 +723,7 @@ Footprint context_footprint(int o, int v, int X, int order, bool dip, bool store
     if (store) keep += r(N * N * D);
     const size_t strip = (size_t)ib * v * N * D;
     temp += (store ? 4 : 5) * r(strip);
-    temp += r((size_t)tau_blocks(o, v, ib) * ((o + ib - 1) / ib) * D) + r(D);
+    temp += r((size_t)tau_blocks(o, v, ib) * ((o + ib - 1) / ib) * D) + r((1 + kSumBlocks) * D);
   }
   keep += r((size_t)o * ns * X * v * D);
   if (want_f32 && order >= 1) {

@@ -195,14 +195,18 @@ pp_status pp_sigma(pp_handle* h, int32_t order, int32_t m, const double* X, doub
     (void)product_precision(h, flags);
     const int k = 2 * m;
     const size_t per = (size_t)k * N;
-    struct Free {
+    struct Staging {
       ppw::Context& c;
-      std::vector<void*> p;
-      ~Free() {
-        for (void* q : p) c.arena.free(q);
+      void* p = nullptr;
+      bool done = false;
+      ~Staging() {
+        if (!p) return;
+        if (!done) (void)hipStreamSynchronize(c.stream);  // after an error work may still run
+        c.arena.return_staging(p);
       }
-    } fr{c, {}};
-    double *V, *AV, *BV, *SV;
+    } fr{c};
+    double *V, *out = outp;
+    size_t each = per;
     if (async) {
       // handle-owned staging, grown only after earlier asynchronous work is done
       if (per > h->acap) {
@@ -214,25 +218,16 @@ pp_status pp_sigma(pp_handle* h, int32_t order, int32_t m, const double* X, doub
         h->acap = per;
       }
       V = h->abuf;
-      AV = V + h->acap;
-      BV = AV + h->acap;
-      SV = BV + h->acap;
+      each = h->acap;
     } else {
       settle(h);
-      V = c.arena.alloc<double>(per, "sigma V");
-      fr.p.push_back(V);
-      AV = c.arena.alloc<double>(per, "sigma AV");
-      fr.p.push_back(AV);
-      BV = c.arena.alloc<double>(per, "sigma BV");
-      fr.p.push_back(BV);
-      SV = c.arena.alloc<double>(per, "sigma SV");
-      fr.p.push_back(SV);
+      fr.p = c.arena.take_staging((4 * per + (dev ? 0 : (size_t)2 * m * N)) * sizeof(double), "sigma staging");
+      V = static_cast<double*>(fr.p);
+      if (!dev) out = V + 4 * per;
     }
-    double* out = outp;
-    if (!dev) {
-      out = c.arena.alloc<double>((size_t)2 * m * N, "sigma out");
-      fr.p.push_back(out);
-    }
+    double* AV = V + each;
+    double* BV = AV + each;
+    double* SV = BV + each;
     const hipMemcpyKind kin = dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     PPW_HIP(hipMemcpy2DAsync(V, N * sizeof(double), X, 2 * N * sizeof(double), N * sizeof(double), m, kin,
                              c.stream));
@@ -248,6 +243,7 @@ pp_status pp_sigma(pp_handle* h, int32_t order, int32_t m, const double* X, doub
       return;
     }
     PPW_HIP(hipStreamSynchronize(c.stream));
+    fr.done = true;
   });
 }
 

@@ -19,6 +19,11 @@ inline long padded_stride(long n) {
 
 // Device allocations with a byte budget.  Every allocation of a handle goes
 // through its arena, so the footprint is known and bounded.
+//
+// hipMalloc costs 20-170 us and hipFree, which waits for all work on the device, 20-600 us, so
+// arrays that live and die together are cut from one segment: between open(bytes) and close()
+// allocations come from one hipMalloc of that size while they fit, and the segment goes back
+// when the last of its arrays has been freed.  The accounting is per array either way.
 class Arena {
  public:
   explicit Arena(size_t budget = 0) : budget_(budget) {}
@@ -30,47 +35,157 @@ class Arena {
   size_t used() const { return used_; }
   size_t budget() const { return budget_; }
 
+  // bytes an array of n elements of size e takes
+  static size_t rounded(size_t n, size_t e) { return (n * e + 255) / 256 * 256; }
+
+  // Segment for the allocations up to close(): 'bytes' is the sum of their rounded sizes.  Without
+  // effect where the budget or the device has no room for it (they then come one by one).
+  void open(size_t bytes) {
+    close();
+    if (bytes == 0 || (budget_ && used_ + bytes + (spare_busy_ ? 0 : spare_bytes_) > budget_)) return;
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    segs_.push_back({static_cast<char*>(p), bytes, 0, 0});
+    open_ = (int)segs_.size() - 1;
+  }
+  void close() {
+    const int s = open_;
+    open_ = -1;
+    if (s >= 0 && segs_[s].live == 0) drop(s);
+  }
+
   template <typename T>
   T* alloc(size_t n, const char* what) {
-    const size_t bytes = ((n * sizeof(T) + 255) / 256) * 256;
-    if (budget_ && used_ + bytes > budget_)
-      throw OutOfBudget(std::string("device budget exceeded allocating ") + what + " (" +
-                        std::to_string(bytes) + " B, " + std::to_string(used_) + " of " +
-                        std::to_string(budget_) + " B in use)");
+    const size_t bytes = rounded(n, sizeof(T));
+    if (budget_ && !spare_busy_ && used_ + bytes + spare_bytes_ > budget_) drop_spare();
+    check(bytes, what);
     void* p = nullptr;
+    int seg = -1;
     if (bytes) {
-      hipError_t e = hipMalloc(&p, bytes);
-      if (e != hipSuccess) {
-        (void)hipGetLastError();
-        throw OutOfBudget(std::string("hipMalloc failed for ") + what + ": " + hipGetErrorString(e));
+      if (open_ >= 0 && segs_[open_].off + bytes <= segs_[open_].size) {
+        seg = open_;
+        p = segs_[seg].base + segs_[seg].off;
+        segs_[seg].off += bytes;
+        ++segs_[seg].live;
+      } else {
+        p = device_alloc(bytes, what);
       }
     }
-    blocks_.push_back({p, bytes});
+    blocks_.push_back({p, bytes, seg});
     used_ += bytes;
     return static_cast<T*>(p);
   }
   void free(void* p) {
     for (size_t i = 0; i < blocks_.size(); ++i)
       if (blocks_[i].p == p) {
-        if (p) (void)hipFree(p);
+        const int seg = blocks_[i].seg;
         used_ -= blocks_[i].bytes;
         blocks_.erase(blocks_.begin() + i);
+        if (seg >= 0) {
+          if (--segs_[seg].live == 0 && seg != open_) drop(seg);
+        } else if (p) {
+          (void)hipFree(p);
+        }
         return;
       }
   }
+
+  // Staging of one synchronous call (a single one at a time): an array of at most kSpare bytes
+  // stays with the arena for the next call, until anything else needs the room.  The work that
+  // used it must be done when it is returned.
+  void* take_staging(size_t bytes, const char* what) {
+    bytes = rounded(bytes, 1);
+    if (bytes > kSpare || spare_busy_) return alloc<char>(bytes, what);
+    if (spare_bytes_ < bytes) {
+      drop_spare();
+      check(bytes, what);
+      spare_ = device_alloc(bytes, what);
+      spare_bytes_ = bytes;
+    } else {
+      check(bytes, what);
+    }
+    spare_busy_ = true;
+    spare_used_ = bytes;
+    used_ += bytes;
+    return spare_;
+  }
+  void return_staging(void* p) {
+    if (spare_busy_ && p == spare_) {
+      spare_busy_ = false;
+      used_ -= spare_used_;
+    } else {
+      free(p);
+    }
+  }
+
   void release() {
     for (auto& b : blocks_)
-      if (b.p) (void)hipFree(b.p);
+      if (b.p && b.seg < 0) (void)hipFree(b.p);
     blocks_.clear();
+    for (auto& s : segs_)
+      if (s.base) (void)hipFree(s.base);
+    segs_.clear();
+    open_ = -1;
+    if (spare_) (void)hipFree(spare_);
+    spare_ = nullptr;
+    spare_bytes_ = 0;
+    spare_busy_ = false;
     used_ = 0;
   }
 
  private:
+  static constexpr size_t kSpare = (size_t)64 << 20;
   struct Block {
     void* p;
     size_t bytes;
+    int seg;  // -1: a hipMalloc of its own
   };
+  struct Segment {
+    char* base;
+    size_t size, off;
+    int live;
+  };
+  void check(size_t bytes, const char* what) {
+    if (budget_ && used_ + bytes > budget_)
+      throw OutOfBudget(std::string("device budget exceeded allocating ") + what + " (" +
+                        std::to_string(bytes) + " B, " + std::to_string(used_) + " of " +
+                        std::to_string(budget_) + " B in use)");
+  }
+  void* device_alloc(size_t bytes, const char* what) {
+    void* p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e != hipSuccess && spare_ && !spare_busy_) {
+      (void)hipGetLastError();
+      drop_spare();
+      e = hipMalloc(&p, bytes);
+    }
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      throw OutOfBudget(std::string("hipMalloc failed for ") + what + ": " + hipGetErrorString(e));
+    }
+    return p;
+  }
+  void drop(int s) {
+    if (segs_[s].base) (void)hipFree(segs_[s].base);
+    segs_[s].base = nullptr;
+    while (!segs_.empty() && !segs_.back().base) segs_.pop_back();
+  }
+  void drop_spare() {
+    if (spare_ && !spare_busy_) {
+      (void)hipFree(spare_);
+      spare_ = nullptr;
+      spare_bytes_ = 0;
+    }
+  }
   std::vector<Block> blocks_;
+  std::vector<Segment> segs_;
+  int open_ = -1;
+  void* spare_ = nullptr;
+  size_t spare_bytes_ = 0, spare_used_ = 0;
+  bool spare_busy_ = false;
   size_t used_ = 0;
   size_t budget_ = 0;
 };
@@ -207,6 +322,7 @@ struct Context {
   float *w32_V = nullptr, *w32_c = nullptr, *w32_J = nullptr, *w32_G = nullptr, *w32_U = nullptr,
         *w32_H = nullptr, *w32_S = nullptr, *w32_tau = nullptr, *w32_P = nullptr, *w32_AV = nullptr,
         *w32_BV = nullptr;
+  std::vector<hipStream_t> solver_streams;  // one per concurrent window, kept between solves
   Workspace ws;      // split-K workspace
   size_t ws_bytes = 0;
 
@@ -265,9 +381,9 @@ struct PassJob {
 
 // Products of several systems (distinct contexts) in one pass on stream s: every
 // contraction step is issued for all systems together, its GEMMs merged into grouped
-// launches.  No GEMM takes split-K unless its split was fixed when it was recorded, so a
-// system's products are bitwise the same whichever systems share the pass.  Each context's workspace must already hold its k vectors
-// (sigma_reserve); inputs must be ready on s.  Returns the number of grouped GEMM
+// launches.  Each GEMM's reduction splits follow from its own shape, so a system's products
+// are bitwise the same whichever systems share the pass.  Each context's workspace must already
+// hold its k vectors (sigma_reserve); inputs must be ready on s.  Returns the number of grouped GEMM
 // launches issued (steps whose GEMMs were too small to fill the chip together are
 // launched one by one).
 int sigma_group(const std::vector<PassJob>& jobs, hipStream_t s);

@@ -237,6 +237,7 @@ ContourFilter::ContourFilter(Context& c, int kblock, int nodes_max, int chunk, h
   if (kblock < 1 || nodes_max < 1 || chunk < 2 * kblock) throw InvalidArg("contour filter: bad dimensions");
   const size_t rows = (size_t)4 * nodes_max * kblock;
   const size_t n = rows * N_;
+  c_.arena.open(bytes(N_, kblock, nodes_max));
   X_ = get<double>(n, "contour x");
   R_ = get<double>(n, "contour r");
   Z_ = get<double>(n, "contour u");
@@ -255,6 +256,7 @@ ContourFilter::ContourFilter(Context& c, int kblock, int nodes_max, int chunk, h
   bn2_ = get<double>(ns, "contour |b|^2");
   zw_ = get<double>((size_t)4 * nodes_max, "contour nodes");
   done_ = get<int>(ns, "contour done");
+  c_.arena.close();
 }
 
 ContourFilter::~ContourFilter() {

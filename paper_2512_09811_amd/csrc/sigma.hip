@@ -34,6 +34,7 @@ namespace ppw {
 
 Context::~Context() {
   arena.release();
+  for (hipStream_t q : solver_streams) (void)hipStreamDestroy(q);
   if (own_stream && stream) (void)hipStreamDestroy(stream);
 }
 
@@ -147,11 +148,16 @@ Context* setup_context(const SetupParams& p) {
     const int o = p.o, v = p.v, X = p.naux;
     const long N = c->N;
 
+    auto r = [](size_t n, size_t e = sizeof(double)) { return Arena::rounded(n, e); };
+    c->ns = p.order >= 2 ? 2 : 1;
+    const size_t ws0 = std::max<size_t>((size_t)64 << 20, (size_t)X * 1024 * sizeof(double));
+    c->arena.open(r(o) + r(v) + 2 * r((size_t)X * o * o) + r((size_t)X * v * v) + r((size_t)c->ns * X * N) +
+                  (p.dip ? r((size_t)3 * N) : 0) + r(ws0, 1) + 3 * r(N) +
+                  (p.order >= 2 ? 2 * r((size_t)v * v) + 2 * r((size_t)o * o) : 0));
     c->eps_o = c->arena.alloc<double>(o, "eps_o");
     c->eps_v = c->arena.alloc<double>(v, "eps_v");
     c->Boo = c->arena.alloc<double>((size_t)X * o * o, "B_oo");
     c->Bvv = c->arena.alloc<double>((size_t)X * v * v, "B_vv");
-    c->ns = p.order >= 2 ? 2 : 1;
     c->BovLam = c->arena.alloc<double>((size_t)c->ns * X * N, "B_ov");
     c->Bov = c->BovLam;
     if (p.order >= 2) c->Lam = c->BovLam + (size_t)X * N;
@@ -168,20 +174,23 @@ Context* setup_context(const SetupParams& p) {
     c->Boo_t = c->arena.alloc<double>((size_t)o * o * X, "B_oo [i][j][P]");
     const int perm[3] = {1, 2, 0};
     permute3(c->Boo, c->Boo_t, X, o, o, perm, s);
-    ensure_ws(*c, std::max<size_t>((size_t)64 << 20, (size_t)X * 1024 * sizeof(double)));
-
-    double* coul = c->arena.alloc<double>(N, "diag tmp");
-    double* exch = c->arena.alloc<double>(N, "diag tmp");
-    diag_integrals(c->Bov, c->Boo, c->Bvv, o, v, X, coul, exch, s);
+    ensure_ws(*c, ws0);
     c->dA = c->arena.alloc<double>(N, "diag A");
     c->dB = c->arena.alloc<double>(N, "diag B");
     c->dS = c->arena.alloc<double>(N, "diag S");
-
     if (p.order >= 2) {
       c->Gv = c->arena.alloc<double>((size_t)v * v, "Gv");
       c->Ev = c->arena.alloc<double>((size_t)v * v, "Ev");
       c->Go = c->arena.alloc<double>((size_t)o * o, "Go");
       c->Eo = c->arena.alloc<double>((size_t)o * o, "Eo");
+    }
+    c->arena.open(2 * r(N));
+    double* coul = c->arena.alloc<double>(N, "diag tmp");
+    double* exch = c->arena.alloc<double>(N, "diag tmp");
+    c->arena.close();
+    diag_integrals(c->Bov, c->Boo, c->Bvv, o, v, X, coul, exch, s);
+
+    if (p.order >= 2) {
       PPW_HIP(hipMemsetAsync(c->Gv, 0, sizeof(double) * v * v, s));
       PPW_HIP(hipMemsetAsync(c->Ev, 0, sizeof(double) * v * v, s));
       PPW_HIP(hipMemsetAsync(c->Go, 0, sizeof(double) * o * o, s));
@@ -197,13 +206,16 @@ Context* setup_context(const SetupParams& p) {
       int ib = p.strip_rows > 0 ? std::min(p.strip_rows, o) : strip_rows_for(*c, room / 3, store ? 4 : 5);
       c->strip_rows = ib;
       const size_t strip = (size_t)ib * v * N;
+      const size_t parts = (size_t)tau_blocks(o, v, ib) * ((o + ib - 1) / ib);
+      c->arena.open((store ? 4 : 5) * r(strip) + r(parts) + r(1 + kSumBlocks));
       double* S = c->arena.alloc<double>(strip, "strip S");
       double* tauS = store ? nullptr : c->arena.alloc<double>(strip, "strip tau");
       double* t = c->arena.alloc<double>(strip, "strip t");
       double* tEv = c->arena.alloc<double>(strip, "strip tEv");
       double* tEo = c->arena.alloc<double>(strip, "strip tEo");
-      const long nblk = tau_blocks(o, v, ib);
-      double* partial = c->arena.alloc<double>((size_t)nblk * ((o + ib - 1) / ib), "energy partials");
+      double* partial = c->arena.alloc<double>(parts, "energy partials");
+      double* e2 = c->arena.alloc<double>(1 + kSumBlocks, "emp2");
+      c->arena.close();
       long pofs = 0;
       for (int k0 = 0; k0 < o; k0 += ib) {
         const int nb = std::min(ib, o - k0);
@@ -232,7 +244,6 @@ Context* setup_context(const SetupParams& p) {
         GemmDesc l = gd(X, nb * v, (int)N, 0, N, 1, N, N);
         gemm_f64(l, 1.0, c->Bov, tau_b, 0.0, c->Lam + (size_t)k0 * v, s, c->ws);
       }
-      double* e2 = c->arena.alloc<double>(1 + kSumBlocks, "emp2");
       sum_reduce(partial, pofs, e2, s);
       PPW_HIP(hipMemcpyAsync(&c->emp2, e2, sizeof(double), hipMemcpyDeviceToHost, s));
       PPW_HIP(hipStreamSynchronize(s));
@@ -248,7 +259,9 @@ Context* setup_context(const SetupParams& p) {
                   s);
     c->tda = p.tda;
     if (c->tda) PPW_HIP(hipMemsetAsync(c->dB, 0, sizeof(double) * N, s));
-    if (c->dip && p.order >= 2) {
+    const bool own_dipS = c->dip && p.order >= 2;
+    c->arena.open((own_dipS ? r((size_t)3 * N) : 0) + r((size_t)o * c->ns * X * v));
+    if (own_dipS) {
       // property vector over the MP2 ground state through second order: S mu, with
       // S V = V - Go V - V Gv (the metric), for the three dipole components
       c->dipS = c->arena.alloc<double>((size_t)3 * N, "dip S mu");
@@ -267,9 +280,17 @@ Context* setup_context(const SetupParams& p) {
       c->dipS = c->dip;
     }
     c->R = c->arena.alloc<double>((size_t)o * c->ns * X * v, "ring operand");
+    c->arena.close();
     build_ring_operand(c->Bov, c->Lam, o, v, X, c->R, s);
     if (p.want_f32 && p.order >= 1) {
       // FP32 copies of every operand of the reduced-precision product path
+      const size_t F = sizeof(float);
+      c->arena.open(r((size_t)c->ns * X * N, F) + 2 * r((size_t)X * o * o, F) + r((size_t)X * v * v, F) +
+                    r((size_t)o * c->ns * X * v, F) +
+                    (p.order < 2 ? 0
+                                 : 2 * r((size_t)v * v, F) + 2 * r((size_t)o * o, F) +
+                                       (c->tau ? r((size_t)N * (c->split_bf16 ? c->N8 : N), F)
+                                               : (c->split_bf16 ? r((size_t)N * c->X8, F) : 0))));
       auto cp32 = [&](const double* src, size_t n, const char* w) {
         float* d = c->arena.alloc<float>(n, w);
         to_f32((long)n, src, d, s);
@@ -300,6 +321,7 @@ Context* setup_context(const SetupParams& p) {
         c->Go32 = cp32(c->Go, (size_t)o * o, "Go fp32");
         c->Eo32 = cp32(c->Eo, (size_t)o * o, "Eo fp32");
       }
+      c->arena.close();
     }
     PPW_HIP(hipStreamSynchronize(s));
     c->arena.free(exch);
@@ -314,19 +336,43 @@ Context* setup_context(const SetupParams& p) {
 
 namespace {
 
-template <typename T>
-T* regrow(Context& c, T*& p, size_t n, const char* w) {
-  if (p) c.arena.free(p);
-  p = c.arena.alloc<T>(n, w);
-  return p;
-}
+// Workspace arrays of one capacity: the old ones are freed, then the new ones come from one
+// segment.  A failure leaves the capacity at 0 (nothing usable), never a freed pointer in use.
+class Grow {
+ public:
+  explicit Grow(Context& c) : c_(c) {}
+  template <typename T>
+  void add(T*& p, size_t n, const char* w) {
+    if (p) c_.arena.free(p);
+    p = nullptr;
+    bytes_ += Arena::rounded(n, sizeof(T));
+    make_.push_back([this, &p, n, w] { p = c_.arena.alloc<T>(n, w); });
+  }
+  void done(int& cap, int k) {
+    cap = 0;
+    c_.arena.open(bytes_);
+    struct Close {
+      Arena& a;
+      ~Close() { a.close(); }
+    } close{c_.arena};
+    for (auto& f : make_) f();
+    cap = k;
+  }
+
+ private:
+  Context& c_;
+  size_t bytes_ = 0;
+  std::vector<std::function<void()>> make_;
+};
 
 // FP64 buffers every product pass needs for the final (FP64) assembly
 void grow_assembly(Context& c, int k) {
   if (k <= c.kcap_asm) return;
-  regrow(c, c.w_J, (size_t)k * c.N, "ws J");
-  regrow(c, c.w_P, (size_t)4 * k * c.N, "ws P");
-  c.kcap_asm = k;
+  Grow g(c);
+  c.kcap_asm = 0;
+  g.add(c.w_J, (size_t)k * c.N, "ws J");
+  g.add(c.w_P, (size_t)4 * k * c.N, "ws P");
+  g.done(c.kcap_asm, k);
 }
 
 void grow_workspace(Context& c, int k) {
@@ -334,18 +380,20 @@ void grow_workspace(Context& c, int k) {
   if (k <= c.kcap) return;
   const int o = c.o, v = c.v, X = c.naux;
   const long N = c.N;
-  regrow(c, c.w_c, (size_t)X * k, "ws c");
-  regrow(c, c.w_G, (size_t)k * X * N, "ws G");
-  regrow(c, c.w_U, (size_t)k * o * c.ns * X * o, "ws U");
+  Grow g(c);
+  c.kcap = 0;
+  g.add(c.w_c, (size_t)X * k, "ws c");
+  g.add(c.w_G, (size_t)k * X * N, "ws G");
+  g.add(c.w_U, (size_t)k * o * c.ns * X * o, "ws U");
   if (c.order >= 2) {
     const int ib = c.tau ? o : c.strip_rows;
-    regrow(c, c.w_H, (size_t)ib * v * k * X, "ws H");
+    g.add(c.w_H, (size_t)ib * v * k * X, "ws H");
     if (!c.tau) {
-      regrow(c, c.w_S, (size_t)c.strip_rows * v * N, "ws strip S");
-      regrow(c, c.w_tau, (size_t)c.strip_rows * v * N, "ws strip tau");
+      g.add(c.w_S, (size_t)c.strip_rows * v * N, "ws strip S");
+      g.add(c.w_tau, (size_t)c.strip_rows * v * N, "ws strip tau");
     }
   }
-  c.kcap = k;
+  g.done(c.kcap, k);
 }
 
 void grow_workspace32(Context& c, int k) {
@@ -353,29 +401,31 @@ void grow_workspace32(Context& c, int k) {
   if (k <= c.kcap32) return;
   const int o = c.o, v = c.v, X = c.naux;
   const long N = c.N;
-  regrow(c, c.w32_V, (size_t)k * N, "ws32 V");
-  regrow(c, c.w32_AV, (size_t)k * N, "ws32 AV");
-  regrow(c, c.w32_BV, (size_t)k * N, "ws32 BV");
-  regrow(c, c.w32_J, (size_t)k * N, "ws32 J");
-  regrow(c, c.w32_P, (size_t)4 * k * N, "ws32 P");
-  regrow(c, c.w32_c, (size_t)X * k, "ws32 c");
-  // G rows (q,P) of N8 values; the padding past N stays zero (split-BF16 chunks)
-  regrow(c, c.w32_G, (size_t)k * X * c.N8, "ws32 G");
-  PPW_HIP(hipMemsetAsync(c.w32_G, 0, sizeof(float) * k * X * c.N8, c.stream));
-  PPW_HIP(hipStreamSynchronize(c.stream));  // products may run on another stream
-  regrow(c, c.w32_U, (size_t)k * o * c.ns * X * o, "ws32 U");
+  Grow g(c);
+  c.kcap32 = 0;
+  g.add(c.w32_V, (size_t)k * N, "ws32 V");
+  g.add(c.w32_AV, (size_t)k * N, "ws32 AV");
+  g.add(c.w32_BV, (size_t)k * N, "ws32 BV");
+  g.add(c.w32_J, (size_t)k * N, "ws32 J");
+  g.add(c.w32_P, (size_t)4 * k * N, "ws32 P");
+  g.add(c.w32_c, (size_t)X * k, "ws32 c");
+  g.add(c.w32_G, (size_t)k * X * c.N8, "ws32 G");
+  g.add(c.w32_U, (size_t)k * o * c.ns * X * o, "ws32 U");
+  const bool stored = amplitudes_stored(c, 1);
   if (c.order >= 2) {
-    const bool stored = amplitudes_stored(c, 1);
     const int ib = stored ? o : c.strip_rows;
-    regrow(c, c.w32_H, (size_t)ib * v * k * X, "ws32 H");
+    g.add(c.w32_H, (size_t)ib * v * k * X, "ws32 H");
     if (!stored) {
-      regrow(c, c.w32_S, (size_t)c.strip_rows * v * N, "ws32 strip S");
-      regrow(c, c.w32_tau, (size_t)c.strip_rows * v * c.N8, "ws32 strip tau");
-      PPW_HIP(hipMemsetAsync(c.w32_tau, 0, sizeof(float) * c.strip_rows * v * c.N8, c.stream));
-      PPW_HIP(hipStreamSynchronize(c.stream));
+      g.add(c.w32_S, (size_t)c.strip_rows * v * N, "ws32 strip S");
+      g.add(c.w32_tau, (size_t)c.strip_rows * v * c.N8, "ws32 strip tau");
     }
   }
-  c.kcap32 = k;
+  g.done(c.kcap32, k);
+  // G rows (q,P) and strip rows of N8 values; the padding past N stays zero (split-BF16 chunks)
+  PPW_HIP(hipMemsetAsync(c.w32_G, 0, sizeof(float) * k * X * c.N8, c.stream));
+  if (c.order >= 2 && !stored)
+    PPW_HIP(hipMemsetAsync(c.w32_tau, 0, sizeof(float) * c.strip_rows * v * c.N8, c.stream));
+  PPW_HIP(hipStreamSynchronize(c.stream));  // products may run on another stream
 }
 
 template <typename T>
@@ -950,15 +1000,19 @@ int sigma_group(const std::vector<PassJob>& jobs, hipStream_t s) {
     for (auto& t : tapes) {
       if (p >= t.size()) continue;
       Step& st = t[p];
-      // a GEMM whose reduction splits the launch would choose by itself is issued without
-      // split-K, grouped or not, so that each system's products round the same way
-      // whichever systems share the pass (fixed splits are kept)
+      // A GEMM's reduction splits are fixed here from its own shape and workspace, as its launch
+      // alone would choose them, so each system's products round the same way whichever systems
+      // share the pass; GEMMs without splits can share grouped launches.  (Without any split the
+      // skinny products, few output tiles over a reduction of N, ran on a few workgroups: at six
+      // requests of n_occ 11..16 they took half of the pass, 45 of 84 ms a run.)
       if (st.kind == 0) {
         g64.push_back(st.g64);
-        if (g64.back().d.splitk == 0) g64.back().d.splitk = 1;
+        GemmCall<double>& g = g64.back();
+        if (g.tag < 2) g.d.splitk = gemm_auto_splitk(g.d, g.ws.bytes, false);
       } else if (st.kind == 1) {
         g32.push_back(st.g32);
-        if (g32.back().d.splitk == 0) g32.back().d.splitk = 1;
+        GemmCall<float>& g = g32.back();
+        if (g.tag < 2) g.d.splitk = gemm_auto_splitk(g.d, g.ws.bytes, true);
       } else {
         st.fn(s);
       }

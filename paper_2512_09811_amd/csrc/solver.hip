@@ -468,10 +468,12 @@ class ProductBatcher : public ProductSink {
   }
   void reserve(int ktot) {
     const size_t n = (size_t)ktot * c_.N;
+    c_.arena.open(4 * Arena::rounded(n, sizeof(double)));
     V_ = c_.arena.alloc<double>(n, "batch V");
     AV_ = c_.arena.alloc<double>(n, "batch AV");
     BV_ = c_.arena.alloc<double>(n, "batch BV");
     SV_ = c_.arena.alloc<double>(n, "batch SV");
+    c_.arena.close();
     bufs_ = {V_, AV_, BV_, SV_};
     cap_ = ktot;
     // vectors per product pass: all of them when their product workspaces fit the
@@ -601,26 +603,25 @@ SolverDims solver_dims(long N, int nroots, const SolveOptions& o) {
 
 class Solver {
  public:
-  Solver(Context& c, const SolveOptions& o, double w0, int nroots, ProductSink* pb, int id)
-      : c_(c), opt_(o), w0_(w0), nr_(nroots), N_(c.N), pb_(pb), id_(id) {
+  // s: the stream of the subspace work (the context's own where nothing else runs on it meanwhile)
+  Solver(Context& c, const SolveOptions& o, double w0, int nroots, ProductSink* pb, int id, hipStream_t s)
+      : c_(c), opt_(o), w0_(w0), nr_(nroots), s_(s), N_(c.N), pb_(pb), id_(id) {
     const SolverDims dm = solver_dims(N_, nroots, o);
     m_ = dm.m;
     nbmax_ = dm.nbmax;
     kmax_ = dm.kmax;  // new vectors per extension (X and Y halves of a block)
     trace_ = std::getenv("PPWIN_TRACE") != nullptr;
-    PPW_HIP(hipStreamCreateWithFlags(&s_, hipStreamNonBlocking));
     PPW_HIP(hipEventCreateWithFlags(&ev_ready_, hipEventDisableTiming));
     PPW_HIP(hipEventCreateWithFlags(&ev_done_, hipEventDisableTiming));
     alloc();
     if (opt_.method == 1) cf_.reset(new ContourFilter(c_, m_, opt_.contour_nodes, kmax_, s_));
   }
   ~Solver() {
-    if (s_) (void)hipStreamSynchronize(s_);
+    (void)hipStreamSynchronize(s_);
     cf_.reset();
     for (void* p : owned_) c_.arena.free(p);
     if (ev_ready_) (void)hipEventDestroy(ev_ready_);
     if (ev_done_) (void)hipEventDestroy(ev_done_);
-    if (s_) (void)hipStreamDestroy(s_);
   }
   int kmax() const { return kmax_; }
 
@@ -631,7 +632,7 @@ class Solver {
   SolveOptions opt_;
   double w0_;
   int nr_, m_, nbmax_, kmax_;
-  hipStream_t s_ = nullptr;
+  hipStream_t s_;
   long N_;
   ProductSink* pb_;
   int id_;
@@ -1339,8 +1340,15 @@ void window_solve_many(Context& c, const SolveOptions& opt, int nw, const double
   }
   std::vector<std::unique_ptr<Solver>> sv;
   std::vector<int> ktot(ngroups, 0);
+  // one window takes turns with its products, so it shares their stream; several have one each
+  while (nw > 1 && (int)c.solver_streams.size() < nw) {
+    hipStream_t q = nullptr;
+    PPW_HIP(hipStreamCreateWithFlags(&q, hipStreamNonBlocking));
+    c.solver_streams.push_back(q);
+  }
   for (int w = 0; w < nw; ++w) {
-    sv.emplace_back(new Solver(c, opt, omega0[w], n_roots, pbs[w % ngroups].get(), w));
+    sv.emplace_back(new Solver(c, opt, omega0[w], n_roots, pbs[w % ngroups].get(), w,
+                               nw > 1 ? c.solver_streams[w] : c.stream));
     ktot[w % ngroups] += sv.back()->kmax();
   }
   for (int g = 0; g < ngroups; ++g) pbs[g]->reserve(ktot[g]);
@@ -1422,7 +1430,7 @@ size_t window_solve_bytes(long N, int n_roots, const SolveOptions& opt) {
 void window_solve_shared(Context& c, const SolveOptions& opt, double omega0, int n_roots, ProductSink& sink, int id,
                          double* energies, double* vectors, double* osc, pp_solve_info* info) {
   PPW_HIP(hipSetDevice(c.device));
-  Solver sv(c, opt, omega0, n_roots, &sink, id);
+  Solver sv(c, opt, omega0, n_roots, &sink, id, c.stream);
   PPW_HIP(hipStreamSynchronize(c.stream));
   sv.run(energies, vectors, osc, info);
 }

@@ -630,6 +630,126 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmDesc d, T alpha, 
                                               xcd_remap(blockIdx.x, (long)gridDim.x), blockIdx.y);
 }
 
+// ---------------------------------------------------------------------------
+// Small FP64 products: the projected matrices and coefficient products of the window solver
+// (M, N <= 512, reductions of 40 .. N) and the contractions of small systems.  They are bound by
+// latency: a tiled launch of a few workgroups takes 7-20 us (its pipeline fill, one k tile in
+// flight, 20-40 KB of unrolled code through a cold instruction cache), and a reduction split
+// over workgroups adds a second launch of 3-8 us.  Here a wave computes one 16 x 16 tile with
+// operands loaded from the caches straight into the MFMA layout, 4 steps of 8 in flight while
+// the last 4 are multiplied, and where the output has few tiles the reduction is shared by WK
+// waves of one workgroup (16 at most) and summed through LDS in wave order: one launch, a
+// compact loop.  Neither edges nor short reductions are padded beyond 16 rows and 8 values.
+// Measured in window solves: n = 240 square 27 -> 7 us, 128 x 24 over 1024 14 -> 6 us.
+template <int WK>
+__device__ __forceinline__ void gemm_small_tile(const GemmDesc& d, double alpha, const double* __restrict__ A,
+                                                const double* __restrict__ B, double beta, double* __restrict__ C,
+                                                int id) {
+  using acc_t = Mfma<double>::acc_t;
+  constexpr int U = 4;
+  __shared__ acc_t part[WK > 1 ? WK : 1][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int tiles_m = (d.M + 15) / 16, tiles_n = (d.N + 15) / 16;
+  int tm, tn, batch;
+  if constexpr (WK == 1) {  // 2 x 2 tiles, one per wave
+    const int gm = (tiles_m + 1) / 2, gn = (tiles_n + 1) / 2;
+    batch = id / (gm * gn);
+    tm = 2 * (id % (gm * gn) / gn) + (wave >> 1);
+    tn = 2 * (id % gn) + (wave & 1);
+  } else {
+    batch = id / (tiles_m * tiles_n);
+    tm = id % (tiles_m * tiles_n) / tiles_n;
+    tn = id % tiles_n;
+  }
+  const int m0 = tm * 16, n0 = tn * 16, kq = lane >> 4;
+  const int b1 = batch / d.nb2, b2 = batch % d.nb2;
+  const long am = d.transA ? 1 : d.lda, ak = d.transA ? d.lda : 1;
+  const long bn = d.transB ? d.ldb : 1, bk = d.transB ? 1 : d.ldb;
+  // rows and columns past the edge repeat the last one (their results are not stored)
+  const double* a = A + b1 * d.sA1 + b2 * d.sA2 + min(m0 + (lane & 15), d.M - 1) * am + 2 * kq * ak;
+  const double* b = B + b1 * d.sB1 + b2 * d.sB2 + min(n0 + (lane & 15), d.N - 1) * bn + 2 * kq * bk;
+  // steps of 8 values, the K values of each outer block padded to whole steps; lane group kq takes
+  // values 2 kq and 2 kq + 1 of a step (any order of the reduction will do, as long as A and B
+  // share it), so that an operand contiguous along k comes in 16-byte loads: of the 16 rows of a
+  // load each gives a whole 64-byte line, and the loads per MFMA, which bound this kernel, halve
+  const int S = (d.K + 7) / 8, total = d.KB * S;
+  const int kw = WK == 1 ? 0 : wave;
+  const int s0 = (int)((long)total * kw / WK), s1 = (int)((long)total * (kw + 1) / WK);
+  const bool pa = ak == 1 && (d.lda % 2) == 0 && (d.sAk % 2) == 0 && (d.sA1 % 2) == 0 && (d.sA2 % 2) == 0 &&
+                  (d.K % 2) == 0 && ((uintptr_t)A % 16) == 0;
+  const bool pb = bk == 1 && (d.ldb % 2) == 0 && (d.sBk % 2) == 0 && (d.sB1 % 2) == 0 && (d.sB2 % 2) == 0 &&
+                  (d.K % 2) == 0 && ((uintptr_t)B % 16) == 0;
+  typedef double pair_t __attribute__((ext_vector_type(2)));
+  auto one = [&](const double* p, long k1, bool pairs, int k, bool in) {
+    pair_t v = pair_t{0.0, 0.0};
+    if (pairs) {
+      if (in && k < d.K) v = *reinterpret_cast<const pair_t*>(p);
+    } else {
+      if (in && k < d.K) v[0] = p[0];
+      if (in && k + 1 < d.K) v[1] = p[k1];
+    }
+    return v;
+  };
+  int kb = s0 / S, ks = s0 % S;
+  auto load = [&](int first, pair_t (&x)[U], pair_t (&y)[U]) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const bool in = first + i < s1;
+      const int k = 8 * ks + 2 * kq;
+      x[i] = one(a + (kb * d.sAk + 8 * ks * ak), ak, pa, k, in);
+      y[i] = one(b + (kb * d.sBk + 8 * ks * bk), bk, pb, k, in);
+      if (++ks == S) {
+        ks = 0;
+        ++kb;
+      }
+    }
+  };
+  acc_t acc = acc_t{0, 0, 0, 0};
+  auto mul = [&](const pair_t (&x)[U], const pair_t (&y)[U]) {
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      acc = Mfma<double>::mma(x[i][0], y[i][0], acc);
+      acc = Mfma<double>::mma(x[i][1], y[i][1], acc);
+    }
+  };
+  pair_t x0[U], y0[U], x1[U], y1[U];
+  load(s0, x0, y0);
+  for (int st = s0; st < s1; st += 2 * U) {
+    load(st + U, x1, y1);
+    mul(x0, y0);
+    load(st + 2 * U, x0, y0);
+    mul(x1, y1);
+  }
+  if constexpr (WK > 1) {
+    part[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll 3
+    for (int q = 1; q < WK; ++q) acc += part[q][lane];
+  }
+  const int col = n0 + (lane & 15);
+  if (col >= d.N) return;
+  const bool mapped = (d.cRm | d.cRn) != 0;
+  const long co = b1 * d.sC1 + b2 * d.sC2 + (mapped ? c_index(d.cRn ? col + d.cBn : col, d.cRn, d.cSn, 1) : (long)col);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = m0 + Mfma<double>::row(lane, r);
+    if (row >= d.M) continue;
+    double* cp = C + co + (mapped ? c_index(row, d.cRm, d.cSm, d.ldc) : (long)row * d.ldc);
+    double out = alpha * acc[r];
+    if (beta != 0.0) out += beta * (*cp);
+    *cp = out;
+  }
+}
+
+template <int WK>
+__global__ __launch_bounds__(WK == 16 ? 1024 : 256) void gemm_small_kernel(GemmDesc d, double alpha,
+                                                                          const double* __restrict__ A,
+                                                                          const double* __restrict__ B, double beta,
+                                                                          double* __restrict__ C) {
+  gemm_small_tile<WK>(d, alpha, A, B, beta, C, (int)xcd_remap(blockIdx.x, gridDim.x));
+}
+
 // Up to kGroupMax independent GEMMs of one tile shape in one grid: member g owns the
 // flattened workgroup ids [start_g, start_{g+1}).  The member is found by a
 // wave-uniform scan of the start table, so every member keeps the single-GEMM tile
@@ -658,6 +778,75 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_group_kernel(GroupArgs<T> g)
     if (flat >= g.m[q].start) j = q;
   const GroupMember<T>& mb = g.m[__builtin_amdgcn_readfirstlane(j)];
   gemm_tile<T, BM, BN, BK, AK, BKC>(mb.d, mb.alpha, mb.A, mb.B, mb.beta, mb.C, nullptr, 1, flat - mb.start, 0);
+}
+
+template <int WK>
+__global__ __launch_bounds__(WK == 16 ? 1024 : 256) void gemm_small_group_kernel(GroupArgs<double> g) {
+  const long flat = xcd_remap(blockIdx.x, (long)gridDim.x);
+  int j = 0;
+  for (int q = 1; q < g.n; ++q)
+    if (flat >= g.m[q].start) j = q;
+  const GroupMember<double>& mb = g.m[__builtin_amdgcn_readfirstlane(j)];
+  gemm_small_tile<WK>(mb.d, mb.alpha, mb.A, mb.B, mb.beta, mb.C, (int)(flat - mb.start));
+}
+
+// The line between the small products and the tiled ones, from both measured (us, tiled with its
+// reduction launch | small): at most 2048 tiles (two waves per SIMD of the chip; a larger output
+// fills it with 64 x 64 tiles, which read each operand element once per 64 outputs and can share
+// grouped launches) and 6e4 steps of 8 values in all: 480 x 480 x 480 26.9 | 18.0,
+// 481 x 660 x 481 38.1 | 42.8; and 512 steps in a reduction, as the 16 waves of a tile share one
+// CU's loads: 240 x 40 over 1024 15.7 | 12.4, 78 x 37 over 4070 26.6 | 26.4, 24 x 24 over 6400
+// 33 | 50.  Depends on the shape alone, so a product rounds the same way in every launch that it
+// is part of.
+inline long small_tiles(const GemmDesc& d) {
+  return (long)((d.M + 15) / 16) * ((d.N + 15) / 16) * d.nb1 * d.nb2;
+}
+inline long small_steps(const GemmDesc& d) { return (long)d.KB * ((d.K + 7) / 8); }
+inline int small_waves(const GemmDesc& d) {
+  const long tiles = small_tiles(d), steps = small_steps(d);
+  if (tiles >= 1024 || steps <= 8) return 1;
+  return tiles >= 256 || steps <= 64 ? 4 : 16;
+}
+inline bool small_gemm(const GemmDesc& d) {
+  const long tiles = small_tiles(d), steps = small_steps(d);
+  return tiles <= 2048 && steps <= 512 && tiles * steps <= 60000;
+}
+inline long small_workgroups(const GemmDesc& d) {
+  return small_waves(d) == 1 ? (long)((d.M + 31) / 32) * ((d.N + 31) / 32) * d.nb1 * d.nb2 : small_tiles(d);
+}
+void launch_small(const GemmDesc& d, double alpha, const double* A, const double* B, double beta, double* C,
+                  hipStream_t s) {
+  if (d.cRm < 0 || d.cRn < 0) throw InvalidArg("gemm: negative C index split");
+  const int wk = small_waves(d);
+  const long t = small_workgroups(d);
+  if (wk == 1)
+    gemm_small_kernel<1><<<(unsigned)t, 256, 0, s>>>(d, alpha, A, B, beta, C);
+  else if (wk == 4)
+    gemm_small_kernel<4><<<(unsigned)t, 256, 0, s>>>(d, alpha, A, B, beta, C);
+  else
+    gemm_small_kernel<16><<<(unsigned)t, 1024, 0, s>>>(d, alpha, A, B, beta, C);
+  PPW_LAUNCH_CHECK();
+}
+
+// n <= kGroupMax small products of the same waves per tile in one launch.
+void launch_small_group(const GemmCall<double>* const* calls, int n, hipStream_t s) {
+  GroupArgs<double> g{};
+  long total = 0;
+  for (int i = 0; i < n; ++i) {
+    const GemmCall<double>& c = *calls[i];
+    if (c.d.cRm < 0 || c.d.cRn < 0) throw InvalidArg("gemm: negative C index split");
+    g.m[i] = GroupMember<double>{c.d, c.A, c.B, c.C, c.alpha, c.beta, total};
+    total += small_workgroups(c.d);
+  }
+  g.n = n;
+  const int wk = small_waves(calls[0]->d);
+  if (wk == 1)
+    gemm_small_group_kernel<1><<<(unsigned)total, 256, 0, s>>>(g);
+  else if (wk == 4)
+    gemm_small_group_kernel<4><<<(unsigned)total, 256, 0, s>>>(g);
+  else
+    gemm_small_group_kernel<16><<<(unsigned)total, 1024, 0, s>>>(g);
+  PPW_LAUNCH_CHECK();
 }
 
 template <typename T>
@@ -793,11 +982,26 @@ void launch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T* C, hi
   }
 }
 
+// The tiled kernels' limits hold for small products too.
+inline void check_small(const GemmDesc& d) {
+  if (d.M >= 96 && d.N >= 96 && d.tile != 64)
+    checked_workgroups<128, 128, 16>(d);
+  else
+    checked_workgroups<64, 64, 16>(d);
+}
+
 template <typename T, int TAG = 0>
 void gemm_dispatch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T* C, hipStream_t s,
                    Workspace ws) {
   if (d.M <= 0 || d.N <= 0 || d.nb1 <= 0 || d.nb2 <= 0) return;
   if (d.K <= 0 || d.KB <= 0) throw InvalidArg("gemm: empty reduction");
+  if constexpr (std::is_same<T, double>::value) {
+    if (small_gemm(d)) {
+      check_small(d);
+      launch_small(d, alpha, A, B, beta, C, s);
+      return;
+    }
+  }
   const bool big = d.M >= 96 && d.N >= 96 && d.tile != 64;
   const bool ak = d.transA == 0, bk = d.transB != 0;
 #define PPW_GEMM_CASE(BMv, BNv, AKv, BKv)                                           \
@@ -886,10 +1090,19 @@ int gemm_group_impl(const std::vector<GemmCall<T>>& calls, hipStream_t s) {
   };
   std::vector<Key> keys;
   std::vector<std::vector<const GemmCall<T>*>> sets;
+  std::vector<const GemmCall<T>*> small[3];  // small products by waves per tile
   for (const auto& c : calls) {
     const GemmDesc& d = c.d;
     if (d.M <= 0 || d.N <= 0 || d.nb1 <= 0 || d.nb2 <= 0) continue;
     if (d.K <= 0 || d.KB <= 0) throw InvalidArg("gemm: empty reduction");
+    if constexpr (std::is_same<T, double>::value) {
+      if (small_gemm(d)) {
+        check_small(d);
+        const int wk = small_waves(d);
+        small[wk == 1 ? 0 : (wk == 4 ? 1 : 2)].push_back(&c);
+        continue;
+      }
+    }
     if (d.splitk > 1 || c.tag >= 2) {
       // fixed reduction splits need the split-K launch; split-BF16 has its own kernel
       single_dispatch(c, s);
@@ -903,6 +1116,18 @@ int gemm_group_impl(const std::vector<GemmCall<T>>& calls, hipStream_t s) {
       sets.emplace_back();
     }
     sets[i].push_back(&c);
+  }
+  if constexpr (std::is_same<T, double>::value) {
+    for (auto& set : small)
+      for (size_t j = 0; j < set.size(); j += kGroupMax) {
+        const int n = (int)std::min<size_t>(kGroupMax, set.size() - j);
+        if (n == 1) {
+          single_dispatch(*set[j], s);
+        } else {
+          launch_small_group(set.data() + j, n, s);
+          ++grouped;
+        }
+      }
   }
   for (size_t i = 0; i < keys.size(); ++i) {
     const Key& k = keys[i];

@@ -518,3 +518,29 @@ def test_partial_syev_ranges(B, n, p, scale, target):
     np.testing.assert_allclose(np.sort(wh), nearest, rtol=0, atol=1e-12 * np.abs(lam).max())
     assert np.linalg.norm(A @ Zh - Zh * wh, axis=0).max() < 1e-11 * np.abs(lam).max()
     np.testing.assert_allclose(Zh.T @ Zh, np.eye(p), atol=1e-11)
+
+
+@pytest.mark.parametrize("M,N,K,KB,nb", [(16, 16, 4, 1, 1), (17, 15, 64, 1, 3), (33, 31, 65, 1, 1), (100, 200, 61, 1, 2),
+                                         (480, 28, 480, 1, 1), (30, 500, 1021, 1, 1), (5, 9, 13, 150, 2),
+                                         (24, 24, 4096, 1, 1), (24, 24, 4100, 1, 1), (500, 1024, 40, 1, 1),
+                                         (500, 1040, 40, 1, 1)])
+def test_gemm_small(B, M, N, K, KB, nb):
+    """Small FP64 products on the wave-per-tile kernel, on both sides of its lines: reductions of
+    1, 8, 9 and up to 512 steps of 8 values (one, 4 and 16 waves per tile), ragged edges in m, n and
+    k, an outer reduction, batches; the last four lie at its limits and just past them.  Rounding error
+    of a dot product of K KB terms of size one: eps sqrt(K KB) with a margin of 8."""
+    rng = np.random.default_rng(M + N + K)
+    A = rng.uniform(-1, 1, (nb, KB, M, K))
+    Bt = rng.uniform(-1, 1, (nb, KB, N, K))
+    C0 = rng.uniform(-1, 1, (nb, M, N))
+    ref = 0.5 * np.matmul(A, Bt.transpose(0, 1, 3, 2)).sum(1) - C0
+    tol = 8 * 2.3e-16 * np.sqrt(K * KB)
+    for tA in (0, 1):
+        for tB in (0, 1):
+            a = torch.tensor(A.transpose(0, 1, 3, 2) if tA else A, device="cuda").contiguous()
+            b = torch.tensor(Bt if tB else Bt.transpose(0, 1, 3, 2), device="cuda").contiguous()
+            c = torch.tensor(C0, device="cuda")
+            B.gemm(a, b, c, M=M, N=N, K=K, KB=KB, nbatch=nb, transA=tA, lda=M if tA else K, sA=KB * M * K, sAk=M * K,
+                   transB=tB, ldb=K if tB else N, sB=KB * N * K, sBk=N * K, ldc=N, sC=M * N, alpha=0.5, beta=-1.0,
+                   ws_bytes=1 << 24)
+            assert np.abs(c.cpu().numpy() - ref).max() <= tol, (tA, tB)

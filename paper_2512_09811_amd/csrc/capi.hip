@@ -767,8 +767,10 @@ pp_status ppint_partial_syev(int32_t n, const double* A, double target, int32_t 
   g_setup_error.clear();
   double* scr = nullptr;
   pp_status st = guarded(&g_setup_error, [&] {
-    PPW_HIP(hipMalloc(&scr, sizeof(double) * ppw::partial_syev_scratch(n, p)));
-    const int got = ppw::partial_syev(n, A, target, p, lam, Z, scr, nullptr);
+    const size_t words = ppw::partial_syev_scratch(n, p);
+    PPW_HIP(hipMalloc(&scr, sizeof(double) * (words + 2)));
+    PPW_HIP(hipMemset(scr + words, 0, 2 * sizeof(double)));
+    const int got = ppw::partial_syev(n, A, target, p, lam, Z, scr, reinterpret_cast<int*>(scr + words), nullptr);
     PPW_HIP(hipDeviceSynchronize());
     if (q) *q = got;
   });

@@ -36,6 +36,42 @@ __device__ double block_reduce_sum(double v, double* red) {
   return s;
 }
 
+// Sum over the wave, in every lane: row shifts and row broadcasts (about 150 cycles, a quarter
+// of the time of lane permutes through LDS).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_get(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+  v += dpp_get<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds its sum
+  v += dpp_get<0x112, 0xf>(v);
+  v += dpp_get<0x114, 0xf>(v);
+  v += dpp_get<0x118, 0xf>(v);
+  v += dpp_get<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  v += dpp_get<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+  return __hiloint2double(hi, lo);
+}
+
+// Largest of non-negative values over the wave, in every lane.
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, dpp_get<0x111, 0xf>(v));
+  v = fmax(v, dpp_get<0x112, 0xf>(v));
+  v = fmax(v, dpp_get<0x114, 0xf>(v));
+  v = fmax(v, dpp_get<0x118, 0xf>(v));
+  v = fmax(v, dpp_get<0x142, 0xa>(v));
+  v = fmax(v, dpp_get<0x143, 0xc>(v));
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                          __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
 // W: n x n working copy (row-major, symmetric), Zc: n x n, column-major eigenvectors.
 // NT threads (1024 for the large projected problems; one wave for n <= 64, where the
 // block-wide barriers of the rotation sweeps cost more than the arithmetic).  INLDS
@@ -260,20 +296,22 @@ __global__ __launch_bounds__(NT) void syev_kernel(int n, const double* __restric
 // non-positive pivot j (later panels then stop).
 //
 // The panel is a chain of jb columns, so its time is the latency of one column.  Every
-// workgroup factors the 64-row diagonal block itself and then owns 128 of the rows below it,
-// which removes all exchange between workgroups; a thread keeps one row, its part of the panel
-// in LDS (column-major: the lanes of a wave read consecutive words, and the pivot row's entry is
-// one broadcast), subtracts the earlier columns in order and finds the pivot by itself, so a
-// column costs one barrier of three waves.  Measured at n = 480: 8 panels of 0.30 ms in one
-// workgroup that updated the whole panel in global memory per column; now 0.03 ms each.
-constexpr int kCholNB = 64, kCholRows = 128;
+// workgroup factors the 64-row diagonal block itself (wave 0, a row per lane) and then owns 128
+// of the rows below it (waves 1 and 2), which removes all exchange between workgroups.  Columns
+// go in blocks of 16 held in registers: the earlier columns' part is subtracted first, from LDS
+// (column-major: lanes read consecutive words, the pivot rows' entries are broadcasts), then wave
+// 0 factors the block with lane reads alone and the other waves follow behind the one barrier
+// per block, so that they solve a block while wave 0 is at the next.  Measured at n = 480: 8
+// panels of 0.30 ms in one workgroup that updated the panel in global memory, 0.08 ms with a
+// barrier per column, now 0.04 ms (0.055 beside three other windows).
+constexpr int kCholNB = 64, kCholRows = 128, kCholC = 16;
 __global__ __launch_bounds__(kCholNB + kCholRows) void chol_panel_kernel(int n, int j0, int jb,
                                                                          const double* __restrict__ W,
                                                                          double* __restrict__ L,
                                                                          int* __restrict__ info) {
   __shared__ double Ds[kCholNB][kCholNB];    // [column][row] of the diagonal block
   __shared__ double Os[kCholNB][kCholRows];  // [column][row] of this workgroup's rows below it
-  __shared__ double dg[kCholNB];
+  __shared__ int bad;
   const int tid = threadIdx.x, nt = kCholNB + kCholRows;
   if (info && j0 > 0 && *info != 0) return;
   const int j1 = j0 + jb, r0 = j1 + (int)blockIdx.x * kCholRows;
@@ -286,44 +324,60 @@ __global__ __launch_bounds__(kCholNB + kCholRows) void chol_panel_kernel(int n, 
     const int r = i / jb, k = i % jb;
     Os[k][r] = W[(long)(r0 + r) * n + j0 + k];
   }
+  if (tid == 0) bad = 0;
   __syncthreads();
   const bool diag = tid < kCholNB;
   const int row = diag ? tid : tid - kCholNB;
   const bool live = diag ? row < jb : row < nown;
   double* mine = diag ? &Ds[0][row] : &Os[0][row];
   const int ld = diag ? kCholNB : kCholRows;
-  int bad = 0;
-  for (int j = 0; j < jb; ++j) {
-    double acc = live ? mine[j * ld] : 0.0, piv = Ds[j][j];
-    int k = 0;
-    for (; k + 4 <= j; k += 4) {
-      double m[4], l[4];
+  for (int c0 = 0; c0 < jb; c0 += kCholC) {
+    const int cn = min(kCholC, jb - c0);
+    double a[kCholC];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        m[t] = mine[(k + t) * ld];
-        l[t] = Ds[k + t][j];
-      }
+    for (int c = 0; c < kCholC; ++c) a[c] = live && c < cn ? mine[(c0 + c) * ld] : 0.0;
+#pragma unroll 2
+    for (int k = 0; k < c0; ++k) {
+      const double m = live ? mine[k * ld] : 0.0;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        acc = fma(-m[t], l[t], acc);
-        piv = fma(-l[t], l[t], piv);
+      for (int c = 0; c < kCholC; ++c) a[c] = fma(-m, Ds[k][c0 + c], a[c]);
+    }
+    if (diag) {
+      // (rows above the diagonal of the block hold what is never read)
+      bool ok = true;
+#pragma unroll
+      for (int c = 0; c < kCholC; ++c) {
+        if (c < cn && ok) {
+          const double piv = lane_value(a[c], c0 + c);
+          if (!(piv > 0.0)) {
+            ok = false;
+            if (tid == 0) bad = j0 + c0 + c + 1;
+          } else {
+            const double ljj = sqrt(piv);
+            a[c] = row == c0 + c ? ljj : a[c] / ljj;
+#pragma unroll
+            for (int d = c + 1; d < kCholC; ++d) a[d] = fma(-a[c], lane_value(a[c], (c0 + d) & 63), a[d]);
+            Ds[c0 + c][row] = a[c];
+          }
+        }
       }
     }
-    for (; k < j; ++k) {
-      const double l = Ds[k][j];
-      acc = fma(-mine[k * ld], l, acc);
-      piv = fma(-l, l, piv);
-    }
-    if (!(piv > 0.0)) {  // the same value in every thread
-      bad = j0 + j + 1;
-      break;
-    }
-    const double ljj = sqrt(piv);
-    // the pivot goes to its own array: the column's diagonal entry is still being read
-    if (diag && row == j) dg[j] = ljj;
-    if (live && (!diag || row > j)) mine[j * ld] = acc / ljj;
     __syncthreads();
+    // (wave 0 may be a block ahead by now: a failure there is this loop's next turn)
+    if (bad && bad <= j0 + c0 + cn) break;
+    if (!diag) {
+#pragma unroll
+      for (int c = 0; c < kCholC; ++c) {
+        if (c < cn) {
+          a[c] = a[c] / Ds[c0 + c][c0 + c];
+#pragma unroll
+          for (int d = c + 1; d < kCholC; ++d) a[d] = fma(-a[c], Ds[c0 + c][(c0 + d) & 63], a[d]);
+          Os[c0 + c][row] = a[c];
+        }
+      }
+    }
   }
+  __syncthreads();
   if (bad) {
     if (info && blockIdx.x == 0 && tid == 0) *info = bad;
     return;
@@ -332,7 +386,7 @@ __global__ __launch_bounds__(kCholNB + kCholRows) void chol_panel_kernel(int n, 
   if (blockIdx.x == 0)
     for (int i = tid; i < jb * jb; i += nt) {
       const int r = i / jb, k = i % jb;
-      L[(long)(j0 + r) * n + j0 + k] = k < r ? Ds[k][r] : (k == r ? dg[k] : 0.0);
+      L[(long)(j0 + r) * n + j0 + k] = k <= r ? Ds[k][r] : 0.0;
     }
   for (int i = tid; i < nown * jb; i += nt) {
     const int r = i / jb, k = i % jb;
@@ -358,31 +412,6 @@ __global__ __launch_bounds__(kT) void trinv_kernel(int n, const double* __restri
 // ---------------------------------------------------------------------------
 // Spectrum slicing for the projected problem (only the eigenpairs near a target)
 // ---------------------------------------------------------------------------
-
-// Sum over the wave, in every lane: row shifts and row broadcasts (about 150 cycles, a quarter
-// of the time of lane permutes through LDS).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_get(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_total(double v) {
-  v += dpp_get<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds its sum
-  v += dpp_get<0x112, 0xf>(v);
-  v += dpp_get<0x114, 0xf>(v);
-  v += dpp_get<0x118, 0xf>(v);
-  v += dpp_get<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
-  v += dpp_get<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-  return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                          __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
 
 // Householder tridiagonalization: d[n], e[n] (e[i] couples i, i+1); Hh[k][n] holds the unit
 // reflector u_k of step k (zero in entries <= k).
@@ -775,7 +804,7 @@ __global__ __launch_bounds__(64) void inverse_iteration_kernel(int n, const doub
 // (both in the original order of the columns); *q_out = q.
 //
 // The vectors only have to be orthonormal and to span the same space, so a triangular factor
-// does for the symmetric one (eigenvectors of G): k dependent steps of one wave in LDS, 20 us at
+// does for the symmetric one (eigenvectors of G): k dependent steps of one wave in LDS, 18 us at
 // k = 40, where the eigensolver below took 260 us (its rotations are a scalar recurrence of
 // about k^2 steps).
 __global__ __launch_bounds__(64) void orth_factors_kernel(int k, const double* __restrict__ G, double thresh,
@@ -791,20 +820,12 @@ __global__ __launch_bounds__(64) void orth_factors_kernel(int k, const double* _
   bool done = lane >= k;
   int q = 0;
   for (; q < k; ++q) {
-    double best = done ? -1.0 : dj;
-    int at = lane;
-    for (int off = 32; off > 0; off >>= 1) {
-      const double ob = __shfl_xor(best, off, 64);
-      const int oa = __shfl_xor(at, off, 64);
-      if (ob > best || (ob == best && oa < at)) {
-        best = ob;
-        at = oa;
-      }
-    }
+    const double best = wave_max(done ? 0.0 : fmax(dj, 0.0));  // (a NaN counts as 0)
+    const int at = __ffsll((long long)__ballot(!done && dj == best)) - 1;
     if (!(best > thresh)) break;
     const double piv = sqrt(best);
     double acc = Gs[at][lane];
-#pragma unroll 4
+#pragma unroll 8
     for (int t = 0; t < q; ++t) acc = fma(-Rs[t][at], Rs[t][lane], acc);
     const double r = done ? 0.0 : (lane == at ? piv : acc / piv);
     Rs[q][lane] = r;
@@ -1051,7 +1072,7 @@ size_t partial_syev_scratch(int n, int p) {
   return (size_t)3 * n * n + 2 * (size_t)n + 4 * (size_t)p * n + 5 * (size_t)p * p + 2 * (size_t)p + 64;
 }
 
-int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch,
+int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch, int* flags,
                  hipStream_t s) {
   if (n < 1 || n > kMaxN || p < 1 || p > 64 || p > n) throw InvalidArg("partial_syev: size out of range");
   double* ex = scratch;  // the tridiagonalization's exchange
@@ -1063,14 +1084,14 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   double* Y = V1 + (size_t)p * n;
   double* V2 = Y + (size_t)p * n;
   double* work = V2 + (size_t)p * n;
-  double* G = work + (size_t)2 * p + 2;
+  double* G = work + (size_t)2 * p;
   double* UG = G + (size_t)p * p;
   double* T1 = UG + (size_t)p * p;
   double* H = T1 + (size_t)p * p;
   double* UH = H + (size_t)p * p;
   double* cand = work;
-  int* nc = reinterpret_cast<int*>(work + 2 * p);  // a count, and whether the tridiagonalization gave up
-  tridiagonalize(n, A, ex, d, e, Hh, nc + 1, s);
+  int* nc = flags + 2;  // a count, and whether the tridiagonalization gave up
+  tridiagonalize(n, A, ex, d, e, Hh, flags + 3, s);
   multisect_kernel<<<2 * p, 64, 0, s>>>(n, d, e, target, p, cand, nc);
   PPW_LAUNCH_CHECK();
   inverse_iteration_kernel<<<p, 64, 0, s>>>(n, d, e, target, p, cand, nc, lam, V);
@@ -1082,11 +1103,12 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   // (T1 is p x q, ld q; R goes to UG)
   orth_factors_kernel<<<1, 64, 0, s>>>(p, G, 1e-12, T1, UG, nc);
   PPW_LAUNCH_CHECK();
-  int got[2] = {0, 0};
-  PPW_HIP(hipMemcpyAsync(got, nc, sizeof(got), hipMemcpyDeviceToHost, s));
+  int got[4] = {0, 0, 0, 0};
+  PPW_HIP(hipMemcpyAsync(got, flags, sizeof(got), hipMemcpyDeviceToHost, s));
   PPW_HIP(hipStreamSynchronize(s));
-  if (got[1]) throw DeviceError("tridiagonalization: a workgroup waited in vain for the others");
-  const int q = got[0];
+  if (got[0]) return 0;
+  if (got[3]) throw DeviceError("tridiagonalization: a workgroup waited in vain for the others");
+  const int q = got[2];
   if (q == 0) throw Unstable("partial_syev: inverse iteration produced no independent vectors");
   // V1[j][r] = sum_t T1[t][j] V[t][r]
   GemmDesc a;

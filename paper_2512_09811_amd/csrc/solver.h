@@ -88,8 +88,12 @@ namespace ppw {
 // n x n symmetric A (row-major, device) whose eigenvalues are nearest 'target'
 // (p <= n, p <= 64).  lam[p] ascending; Z[n][p] row-major (column j = vector j).
 // scratch: partial_syev_scratch(n, p) doubles (device).
-// Returns q <= p, the number of independent pairs found (columns 0..q-1 valid).
-int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch,
+// flags: 4 device ints; [2] and [3] are used here, and all four are read back at the one wait
+// for the stream, so that the caller's own ([0]: nonzero if A is not to be used, such as a failed
+// factorisation it was formed from) needs no wait of its own.
+// Returns q <= p, the number of independent pairs found (columns 0..q-1 valid; at least 1), or 0
+// when flags[0] is set.
+int partial_syev(int n, const double* A, double target, int p, double* lam, double* Z, double* scratch, int* flags,
                  hipStream_t s);
 size_t partial_syev_scratch(int n, int p);
 // X[:, j] = sqrt(th[j]) L^-T B[:, j] for lower-triangular L (n x n) and p columns (row-major,

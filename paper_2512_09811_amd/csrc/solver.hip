@@ -1002,8 +1002,7 @@ Solver::Ritz Solver::rayleigh_ritz() {
     ns_residual_kernel<<<1, 1024, 0, s_>>>(n, tmp_, lam_);
     PPW_LAUNCH_CHECK();
   }
-  auto info = fetch(ival_, 1);
-  if (info[0] != 0) throw Unstable("A - B is not positive definite in the subspace");
+  // (a failed factorisation is seen at the eigensolver's wait)
   if (metric) {
     double res = fetch(lam_, 1)[0];
     for (int it = 0; it < 2 && !(res < 1e-13) && res < 0.5; ++it) {
@@ -1015,6 +1014,7 @@ Solver::Ritz Solver::rayleigh_ritz() {
       res = fetch(lam_, 1)[0];
     }
     if (!(res < 1e-13)) {
+      if (fetch(ival_, 1)[0] != 0) throw Unstable("A - B is not positive definite in the subspace");
       small_cholesky(n, Sp_, Ls_, ival_ + 1, tmp_, s_);
       auto inf2 = fetch(ival_ + 1, 1);
       if (inf2[0] != 0) throw Unstable("S is not positive definite in the subspace");
@@ -1033,7 +1033,8 @@ Solver::Ritz Solver::rayleigh_ritz() {
   symmetrize_kernel<<<gridn(nn), kB, 0, s_>>>(K_, n);
   // eigenpairs of K nearest omega0^2 (candidate roots of the window)
   const int p = std::min(n, std::min(64, std::max(2 * m_ + 4, nr_ + 8)));
-  const int q = partial_syev(n, K_, w0_ * w0_, p, th2_, Zk_, eigscr_, s_);
+  const int q = partial_syev(n, K_, w0_ * w0_, p, th2_, Zk_, eigscr_, ival_, s_);
+  if (q == 0) throw Unstable("A - B is not positive definite in the subspace");
   theta_kernel<<<1, 64, 0, s_>>>(q, th2_, th_);
   rld_ = 2 * q;
   us_ = uw_;

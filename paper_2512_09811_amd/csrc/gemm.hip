@@ -208,19 +208,20 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   const long it1 = min(total, it0 + chunk);
   const int lda32 = (int)d.lda, ldb32 = (int)d.ldb;
   const int mrem = d.M - m0, nrem = d.N - n0;
-  const bool rows_ok = mrem >= BM && nrem >= BN && (d.lda % 2) == 0 && (d.ldb % 2) == 0 && (d.sAk % 2) == 0 &&
+  // (rows past the edge repeat the last one: their results are not stored)
+  const bool rows_ok = (d.lda % 2) == 0 && (d.ldb % 2) == 0 && (d.sAk % 2) == 0 &&
                        (d.sBk % 2) == 0 && ((uintptr_t)Atile % 16) == 0 && ((uintptr_t)Btile % 16) == 0;
   // source element (within a tile, k0 = 0) of this lane's slot in each of its chunks
   int offA[CA], offB[CB];
 #pragma unroll
   for (int c = 0; c < CA; ++c) {
     const int sl = (wave + 4 * c) * 64 + lane, r = sl >> 3, kp = (sl & 7) ^ ((r >> 1) & 7);
-    offA[c] = r * lda32 + 2 * kp;
+    offA[c] = min(r, mrem - 1) * lda32 + 2 * kp;
   }
 #pragma unroll
   for (int c = 0; c < CB; ++c) {
     const int sl = (wave + 4 * c) * 64 + lane, r = sl >> 3, kp = (sl & 7) ^ ((r >> 1) & 7);
-    offB[c] = r * ldb32 + 2 * kp;
+    offB[c] = min(r, nrem - 1) * ldb32 + 2 * kp;
   }
   typedef double pair_t __attribute__((ext_vector_type(2)));
   // fill buffer (Ab, Bb) with the k tile (kb, kt)
@@ -463,12 +464,14 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
   const T* Atile = Ab + (AK ? (long)m0 * d.lda : (long)m0);
   const T* Btile = Bb + (BKC ? (long)n0 * d.ldb : (long)n0);
   const int lda32 = (int)d.lda, ldb32 = (int)d.ldb;
-  // Pair loads are whole-vector loads when every pair of this tile is in range and
-  // 2-element aligned (decided once per tile; wave-uniform).
+  // Pair loads are whole-vector loads when no pair of this tile crosses the edge of its operand
+  // and all are 2-element aligned (decided once per tile; wave-uniform).  Pairs past the edge in
+  // m or n repeat the last one (their results are not stored), pairs past the end of K are zero.
   const int mrem = d.M - m0, nrem = d.N - n0;
-  const bool vec_ok = mrem >= BM && nrem >= BN && (d.lda % 2) == 0 && (d.ldb % 2) == 0 && (d.sAk % 2) == 0 &&
-                      (d.sBk % 2) == 0 && ((uintptr_t)Atile % (2 * sizeof(T))) == 0 &&
+  const bool vec_ok = (AK || mrem % 2 == 0) && (BKC || nrem % 2 == 0) && (d.lda % 2) == 0 && (d.ldb % 2) == 0 &&
+                      (d.sAk % 2) == 0 && (d.sBk % 2) == 0 && ((uintptr_t)Atile % (2 * sizeof(T))) == 0 &&
                       ((uintptr_t)Btile % (2 * sizeof(T))) == 0;
+  const int mlast = AK ? mrem - 1 : mrem - 2, nlast = BKC ? nrem - 1 : nrem - 2;
   auto load = [&](int kb, int kt) {
     const int k0 = kt * BK;
     const T* Ak = Atile + kb * d.sAk + (AK ? (long)k0 : (long)k0 * d.lda);
@@ -479,13 +482,36 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
       for (int i = 0; i < PA; ++i) {
         int m, k;
         a_pair(i * kThreads + tid, m, k);
+        m = min(m, mlast);
         ra[i] = *reinterpret_cast<const pair_t*>(Ak + (AK ? (m * lda32 + k) : (k * lda32 + m)));
       }
 #pragma unroll
       for (int i = 0; i < PB; ++i) {
         int n, k;
         b_pair(i * kThreads + tid, n, k);
+        n = min(n, nlast);
         rb[i] = *reinterpret_cast<const pair_t*>(Bk + (BKC ? (n * ldb32 + k) : (k * ldb32 + n)));
+      }
+    } else if (vec_ok && (!(AK || BKC) || krem % 2 == 0)) {
+#pragma unroll
+      for (int i = 0; i < PA; ++i) {
+        int m, k;
+        a_pair(i * kThreads + tid, m, k);
+        m = min(m, mlast);
+        const bool in = k < krem;
+        const int kc = in ? k : 0;
+        const pair_t v = *reinterpret_cast<const pair_t*>(Ak + (AK ? (m * lda32 + kc) : (kc * lda32 + m)));
+        ra[i] = in ? v : pair_t{T(0), T(0)};
+      }
+#pragma unroll
+      for (int i = 0; i < PB; ++i) {
+        int n, k;
+        b_pair(i * kThreads + tid, n, k);
+        n = min(n, nlast);
+        const bool in = k < krem;
+        const int kc = in ? k : 0;
+        const pair_t v = *reinterpret_cast<const pair_t*>(Bk + (BKC ? (n * ldb32 + kc) : (kc * ldb32 + n)));
+        rb[i] = in ? v : pair_t{T(0), T(0)};
       }
     } else {
 #pragma unroll
@@ -626,8 +652,13 @@ template <typename T, int BM, int BN, int BK, bool AK, bool BKC, int TAG>
 __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmDesc d, T alpha, const T* __restrict__ A,
                                                         const T* __restrict__ B, T beta, T* __restrict__ C,
                                                         T* __restrict__ W, int splitk) {
-  gemm_tile<T, BM, BN, BK, AK, BKC, TAG == 4>(d, alpha, A, B, beta, C, W, splitk,
-                                              xcd_remap(blockIdx.x, (long)gridDim.x), blockIdx.y);
+  // workgroups of all splits in one flat order, so that the tiles of a split, which read the same
+  // part of both operands, meet in one XCD's L2.  Measured with the vector loads of edge tiles, at
+  // 40/160/600 in FP64: ladder term 823 -> 723 us, ring exchange 519 -> 305, U R 428 -> 370.
+  const int per = (int)gridDim.x;
+  const int flat = (int)xcd_remap((long)blockIdx.y * per + blockIdx.x, (long)per * gridDim.y);
+  const int split = __builtin_amdgcn_readfirstlane(flat / per);
+  gemm_tile<T, BM, BN, BK, AK, BKC, TAG == 4>(d, alpha, A, B, beta, C, W, splitk, flat - split * per, split);
 }
 
 // ---------------------------------------------------------------------------
@@ -640,7 +671,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmDesc d, T alpha, 
 // the last 4 are multiplied, and where the output has few tiles the reduction is shared by WK
 // waves of one workgroup (16 at most) and summed through LDS in wave order: one launch, a
 // compact loop.  Neither edges nor short reductions are padded beyond 16 rows and 8 values.
-// Measured in window solves: n = 240 square 27 -> 7 us, 128 x 24 over 1024 14 -> 6 us.
+// Measured, tiled with its reduction launch | here: 240 square 23.5 | 6.4 us, 40 x 1024 over 240
+// 13.4 | 6.2, 960 x 160 over 160 23.6 | 9.6.
 template <int WK>
 __device__ __forceinline__ void gemm_small_tile(const GemmDesc& d, double alpha, const double* __restrict__ A,
                                                 const double* __restrict__ B, double beta, double* __restrict__ C,

@@ -544,3 +544,37 @@ def test_gemm_small(B, M, N, K, KB, nb):
                    transB=tB, ldb=K if tB else N, sB=KB * N * K, sBk=N * K, ldc=N, sC=M * N, alpha=0.5, beta=-1.0,
                    ws_bytes=1 << 24)
             assert np.abs(c.cpu().numpy() - ref).max() <= tol, (tA, tB)
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("M,N,K,KB", [(40, 90, 40, 520), (33, 97, 42, 520), (130, 160, 45, 300), (200, 130, 600, 30),
+                                      (128, 128, 16, 700), (128, 128, 32, 513), (64, 2, 1040, 17)])
+def test_gemm_tiled_edges(B, fp32, M, N, K, KB):
+    """Tiles that end past the operands' edges, with rows padded by NaN: nothing past an edge may
+    enter a result, for whole and ragged k tiles, an even and an odd number of them, with and
+    without reduction splits.  Rows of an even stride take the vector loads, rows of an odd one
+    the guarded loads; the order of the sums is the same, so the results are equal bit for bit."""
+    rng = np.random.default_rng(M + N + K)
+    A = rng.uniform(-1, 1, (KB, M, K))
+    Bt = rng.uniform(-1, 1, (KB, N, K))
+    dt = torch.float32 if fp32 else torch.float64
+
+    def padded(x, odd):  # NaN after each row, to a stride of the given parity
+        n = x.shape[-1]
+        p = np.full(x.shape[:-1] + (n + 2 + ((n + odd) & 1),), np.nan)
+        p[..., :n] = x
+        return torch.tensor(p, device="cuda", dtype=dt)
+
+    for tA in (0, 1):
+        for tB in (0, 1):
+            for ws in (0, 1 << 26):
+                got = []
+                for odd in (0, 1):
+                    a = padded(A.transpose(0, 2, 1) if tA else A, odd)
+                    b = padded(Bt if tB else Bt.transpose(0, 2, 1), odd)
+                    c = torch.full((M, N + 1), -7.0, device="cuda", dtype=dt)
+                    B.gemm(a, b, c, M=M, N=N, K=K, KB=KB, transA=tA, lda=a.shape[2], sAk=a.shape[1] * a.shape[2],
+                           transB=tB, ldb=b.shape[2], sBk=b.shape[1] * b.shape[2], ldc=N + 1, ws_bytes=ws, fp32=fp32)
+                    got.append(c.cpu())
+                assert torch.isfinite(got[0]).all() and (got[0][:, N] == -7.0).all()
+                assert torch.equal(got[0], got[1]), (tA, tB, ws)

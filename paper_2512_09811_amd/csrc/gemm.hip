@@ -502,12 +502,14 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
                       (d.sAk % 2) == 0 && (d.sBk % 2) == 0 && ((uintptr_t)Atile % (2 * sizeof(T))) == 0 &&
                       ((uintptr_t)Btile % (2 * sizeof(T))) == 0;
   const int mlast = AK ? mrem - 1 : mrem - 2, nlast = BKC ? nrem - 1 : nrem - 2;
-  auto load = [&](int kb, int kt) {
+  // MODE 0: whole k tiles on the vector path, 1: the vector path with a ragged last one, 2: guarded
+  auto load = [&](int kb, int kt, auto mode) {
+    constexpr int MODE = decltype(mode)::value;
     const int k0 = kt * BK;
     const T* Ak = Atile + kb * d.sAk + (AK ? (long)k0 : (long)k0 * d.lda);
     const T* Bk = Btile + kb * d.sBk + (BKC ? (long)k0 : (long)k0 * d.ldb);
     const int krem = d.K - k0;
-    if (vec_ok && krem >= BK) {
+    if constexpr (MODE == 0) {
 #pragma unroll
       for (int i = 0; i < PA; ++i) {
         int m, k;
@@ -522,7 +524,7 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
         n = min(n, nlast);
         rb[i] = *reinterpret_cast<const pair_t*>(Bk + (BKC ? (n * ldb32 + k) : (k * ldb32 + n)));
       }
-    } else if (vec_ok && (!(AK || BKC) || krem % 2 == 0)) {
+    } else if constexpr (MODE == 1) {
 #pragma unroll
       for (int i = 0; i < PA; ++i) {
         int m, k;
@@ -599,51 +601,78 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
       for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::mma(a[i], b[j], acc[i][j]);
   };
 
-  if (it0 < it1) {
-    // (outer block, k tile) of the current iteration, stepped without division
-    int kb = (int)(it0 / nkt), kt = (int)(it0 % nkt);
-    load(kb, kt);
-    store(0);
-    __syncthreads();
-    int buf = 0;
-    for (long it = it0; it < it1; ++it) {
-      const bool more = it + 1 < it1;
-      int nkb = kb, nkt2 = kt + 1;
-      if (nkt2 == nkt) {
-        nkt2 = 0;
-        ++nkb;
-      }
-      // fragments alternate between two register sets: the reads of k group g + 1
-      // are in flight while the MFMAs of group g run
-      T a0[TM], b0[TN], a1[TM], b1v[TN];
-      frag(buf, 0, a0, b0);
-      if (more) load(nkb, nkt2);
+  // issue order pinned: one k group's MFMAs with the next group's fragment reads, and the stores or
+  // the loads of a tile where there are any, between them
+  auto interleave = [&](auto stores, auto loads) {
+    constexpr int R = TM + TN, S = decltype(stores)::value ? PA + PB : 0, L = decltype(loads)::value ? PA + PB : 0;
+    static_assert(TM * TN >= R && TM * TN >= PA + PB, "one read, store or load per MFMA");
 #pragma unroll
-      for (int kk = 0; kk < BK; kk += 8) {
-        frag(buf, kk + 4, a1, b1v);
-        mma(a0, b0);
-        if (kk + 8 < BK) frag(buf, kk + 8, a0, b0);
-        mma(a1, b1v);
-      }
-      // Issue order for the scheduler: the fragment reads of each following k group
-      // are spread one per MFMA over the first MFMAs of the current group, leaving
-      // the rest of the group to cover their LDS latency.
-#pragma unroll
-      for (int g = 0; g + 1 < BK / 4; ++g) {
-#pragma unroll
-        for (int r = 0; r < TM + TN; ++r) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        if constexpr (TM * TN > TM + TN) __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - (TM + TN), 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
-      if (more) store(buf ^ 1);
-      __syncthreads();
-      buf ^= 1;
-      kb = nkb;
-      kt = nkt2;
+    for (int r = 0; r < TM * TN; ++r) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (r < R) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (r < S) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+      if (r < L) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
     }
+  };
+  // As in the kernel above, the one barrier of a k tile stands before its last k group, whose
+  // fragments are in registers by then.  The registers that hold the next tile go to the other
+  // buffer during the first k group (the previous tile's barrier has freed it) and take the tile
+  // after it during the second, so that a load has a whole tile's time to arrive.  Measured against
+  // loads, reads and stores in a row and a barrier at the end of the tile: integrals of the strips
+  // at 96/384/1152 25.1 -> 23.4 ms (59 -> 67 TF/s), K_A and U R of the RPA product there 3.08 ->
+  // 2.82 and 2.30 -> 1.96 ms, ladder term at 128/512/1536 in FP32 24.4 -> 18.6 ms.
+  auto reduce = [&](auto mode) {
+    int kb = (int)(it0 / nkt), kt = (int)(it0 % nkt);
+    const int steps = (int)(it1 - it0);
+    int ahead = 0;  // tile last loaded
+    // the next tile; past the end the last one again (not used), so that no load stands behind a
+    // branch
+    auto advance = [&]() {
+      const bool more = ahead + 1 < steps, wrap = more && kt + 1 == nkt;
+      ahead += more ? 1 : 0;
+      kt = wrap ? 0 : kt + (more ? 1 : 0);
+      kb += wrap ? 1 : 0;
+    };
+    T a0[TM], b0[TN], a1[TM], b1v[TN];
+    load(kb, kt, mode);
+    store(0);
+    advance();
+    load(kb, kt, mode);
+    __syncthreads();
+    frag(0, 0, a0, b0);
+    auto step = [&](auto cur) {
+      constexpr int c = decltype(cur)::value;
+      frag(c, 4, a1, b1v);
+      store(c ^ 1);
+      mma(a0, b0);
+      interleave(std::true_type{}, std::false_type{});
+      advance();
+      frag(c, 8, a0, b0);
+      load(kb, kt, mode);
+      mma(a1, b1v);
+      if constexpr (decltype(mode)::value < 2) interleave(std::false_type{}, std::true_type{});
+      frag(c, 12, a1, b1v);
+      mma(a0, b0);
+      interleave(std::false_type{}, std::false_type{});
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();
+      frag(c ^ 1, 0, a0, b0);
+      mma(a1, b1v);
+      interleave(std::false_type{}, std::false_type{});
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int t = 0; t < steps; t += 2) {
+      step(std::integral_constant<int, 0>{});
+      if (t + 1 < steps) step(std::integral_constant<int, 1>{});
+    }
+  };
+  if (it0 < it1) {
+    if (vec_ok && d.K % BK == 0)
+      reduce(std::integral_constant<int, 0>{});
+    else if (vec_ok && (!(AK || BKC) || d.K % 2 == 0))
+      reduce(std::integral_constant<int, 1>{});
+    else
+      reduce(std::integral_constant<int, 2>{});
   }
 
   const long nbatch = (long)d.nb1 * d.nb2;
@@ -972,16 +1001,27 @@ void launch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T* C, hi
   checked_workgroups<BM, BN, BK>(d);
   const long ntiles = (long)tiles_m * tiles_n;
   // Wave quantisation: when the last of several waves of 128 x 128 tiles would run at
-  // most half full, the trailing tile columns that make up that wave are peeled off and
-  // computed with 64 x 64 tiles (four times the workgroups, a quarter of the work each),
-  // so the tail takes about a quarter of a tile's time.  Every output element is
-  // accumulated over the same sequence of MFMA k steps in both tile shapes, so the result
-  // is bit-identical to the unpeeled GEMM.  The peeled part has its own kernel symbol
-  // (TAG + 2) so that traces tell the two apart.
+  // most half full, the trailing tile columns or tile rows that make up that wave (whichever are
+  // fewer tiles) are peeled off and computed with 64 x 64 tiles (four times the workgroups, a
+  // quarter of the work each), so the tail takes about a quarter of a tile's time.  Every output
+  // element is accumulated over the same sequence of MFMA k steps in both tile shapes, so the
+  // result is bit-identical to the unpeeled GEMM.  The peeled part has its own kernel symbol
+  // (TAG + 2) so that traces tell the two apart.  Measured at 36864 x 2304 x 36864 (288 x 18 tiles,
+  // 64 over ten waves): 1 of 18 columns peeled 87.3 + 7.2 ms, 4 of 288 rows 88.1 + 2.5 ms.
   if constexpr (TAG < 2 && BM == 128 && BN == 128) {
    if (nbatch == 1 && ntiles >= 2 * kResident && d.splitk <= 1 && d.sym < 0) {
     const long rem = ntiles % kResident;
-    const int cols = (int)((rem + tiles_m - 1) / tiles_m);
+    const int cols = (int)((rem + tiles_m - 1) / tiles_m), rows = (int)((rem + tiles_n - 1) / tiles_n);
+    if (rem > 0 && rem <= kResident / 2 && d.cRm == 0 && rows < tiles_m && (long)rows * tiles_n < (long)cols * tiles_m) {
+      const long nmain = (long)(tiles_m - rows) * BM;
+      GemmDesc dm = d, dr = d;
+      dm.M = (int)nmain;
+      dr.M = d.M - (int)nmain;
+      launch<T, BM, BN, BK, AK, BKC, TAG>(dm, alpha, A, B, beta, C, s, Workspace{});
+      launch<T, BM / 2, BN / 2, BK, AK, BKC, TAG + 2>(dr, alpha, A + nmain * (AK ? d.lda : 1), B, beta,
+                                                      C + nmain * d.ldc, s, Workspace{});
+      return;
+    }
     if (rem > 0 && rem <= kResident / 2 && cols < tiles_n) {
       const int nmain = (tiles_n - cols) * BN;
       GemmDesc dm = d, dr = d;

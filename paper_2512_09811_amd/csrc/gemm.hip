@@ -172,10 +172,14 @@ __device__ __forceinline__ void store_mapped(const GemmDesc& d, T alpha, T beta,
     }
 }
 
-template <int BM, int BN>
+// STREAM (whole tiles in m, n in steps of 8 and in k in steps of 32, one batch, no splits): the
+// workgroup computes 'count' tiles, flat, flat + stride, ..., and loads the first k tiles of the
+// next one during the last ones of the present.
+template <int BM, int BN, bool STREAM = false>
 __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, const double* __restrict__ A,
                                               const double* __restrict__ B, double beta, double* __restrict__ C,
-                                              double* __restrict__ W, int splitk, long flat, int split) {
+                                              double* __restrict__ W, int splitk, long flat, int split,
+                                              int count = 1, int stride = 0) {
   constexpr int BK = 16;
   using acc_t = Mfma<double>::acc_t;
   constexpr int WTM = BM / 2, WTN = BN / 2;
@@ -197,7 +201,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   const int batch = (int)(flat / ntiles);
   int tm, tn;
   tile_coords((int)(flat % ntiles), tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
+  int m0 = tm * BM, n0 = tn * BN;
   const int b1 = batch / d.nb2, b2 = batch % d.nb2;
   const double* Atile = A + b1 * d.sA1 + b2 * d.sA2 + (long)m0 * d.lda;
   const double* Btile = B + b1 * d.sB1 + b2 * d.sB2 + (long)n0 * d.ldb;
@@ -215,10 +219,13 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   const bool rows_ok = mrem % 8 == 0 && nrem % 8 == 0 && (d.lda % 2) == 0 && (d.ldb % 2) == 0 && (d.sAk % 2) == 0 &&
                        (d.sBk % 2) == 0 && ((uintptr_t)Atile % 16) == 0 && ((uintptr_t)Btile % 16) == 0;
   long rowA[CA], rowB[CB];
+  auto chunk_rows = [&](int mr, int nr) {
 #pragma unroll
-  for (int c = 0; c < CA; ++c) rowA[c] = (long)min((wave + 4 * c) * 8, mrem - 8) * d.lda;
+    for (int c = 0; c < CA; ++c) rowA[c] = (long)min((wave + 4 * c) * 8, mr - 8) * d.lda;
 #pragma unroll
-  for (int c = 0; c < CB; ++c) rowB[c] = (long)min((wave + 4 * c) * 8, nrem - 8) * d.ldb;
+    for (int c = 0; c < CB; ++c) rowB[c] = (long)min((wave + 4 * c) * 8, nr - 8) * d.ldb;
+  };
+  chunk_rows(mrem, nrem);
   const int kpl = (lane & 7) ^ (4 * (wave & 1) + (lane >> 4));
   const unsigned laneA = 8u * ((unsigned)(lane >> 3) * (unsigned)lda32 + 2u * kpl);
   const unsigned laneB = 8u * ((unsigned)(lane >> 3) * (unsigned)ldb32 + 2u * kpl);
@@ -269,10 +276,13 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   };
 
   acc_t acc[TM][TN];
+  auto clear = [&]() {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+      for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
+  };
+  clear();
   auto frag = [&](const double* Ab, const double* Bb, int kk, double (&a)[TM], double (&b)[TN]) {
     const int kr = kk + (lane >> 4);
 #pragma unroll
@@ -287,6 +297,34 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
       for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<double>::mma(a[i], b[j], acc[i][j]);
   };
 
+  auto finish = [&]() {
+    const long nbatch = (long)d.nb1 * d.nb2;
+    if (!W && (d.cRm | d.cRn)) {
+      store_mapped<double, acc_t, TM, TN, WTM, WTN>(d, alpha, beta, C + b1 * d.sC1 + b2 * d.sC2, m0, n0, wm, wn, lane,
+                                                   acc);
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = m0 + wm * WTM + i * 16 + Mfma<double>::row(lane, r);
+          const int col = n0 + wn * WTN + j * 16 + (lane & 15);
+          if (row < d.M && col < d.N) {
+            const double v = acc[i][j][r];
+            if (W) {
+              W[((long)split * nbatch + batch) * ((long)d.M * d.N) + (long)row * d.N + col] = v;
+            } else {
+              double* cp = C + b1 * d.sC1 + b2 * d.sC2 + (long)row * d.ldc + col;
+              double out = alpha * v;
+              if (beta != 0.0) out += beta * (*cp);
+              *cp = out;
+            }
+          }
+        }
+  };
   // issue order pinned: one k group's MFMAs with the next group's fragment reads, and the loads of
   // a tile where there are any, between them
   auto interleave = [&](auto loads) {
@@ -311,14 +349,27 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   auto reduce = [&](auto whole) {
     int kb = (int)(it0 / nkt), kt = (int)(it0 % nkt);
     const int steps = (int)(it1 - it0);
-    int ahead = 0;  // tile last loaded
+    int ahead = 0;  // tile last loaded (STREAM: output tile whose operands are loaded)
     // the next tile; past the end the last one again, so that no load stands behind a branch, which
     // would keep the MFMAs from hiding its issue (what it brings is not used)
     auto advance = [&]() {
-      const bool more = ahead + 1 < steps, wrap = more && kt + 1 == nkt;
-      ahead += more ? 1 : 0;
-      kt = wrap ? 0 : kt + (more ? 1 : 0);
-      kb += wrap ? 1 : 0;
+      if constexpr (STREAM) {
+        if (kt + 1 < nkt) {
+          ++kt;
+        } else if (ahead + 1 < count) {
+          ++ahead;
+          kt = 0;
+          tile_coords((int)flat + ahead * stride, tiles_m, tiles_n, tm, tn);
+          Atile = A + (long)tm * BM * d.lda;
+          Btile = B + (long)tn * BN * d.ldb;
+          chunk_rows(d.M - tm * BM, d.N - tn * BN);
+        }
+      } else {
+        const bool more = ahead + 1 < steps, wrap = more && kt + 1 == nkt;
+        ahead += more ? 1 : 0;
+        kt = wrap ? 0 : kt + (more ? 1 : 0);
+        kb += wrap ? 1 : 0;
+      }
     };
     double a0[TM], b0[TN], a1[TM], b1v[TN];
     fill(As0, Bs0, kb, kt, whole);
@@ -347,46 +398,36 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
       interleave(whole);
       __builtin_amdgcn_sched_barrier(0);
     };
-    for (int t = 0; t < steps; t += 2) {
-      step(As0, Bs0, As1, Bs1);
-      if (t + 1 < steps) step(As1, Bs1, As0, Bs0);
+    if constexpr (STREAM) {
+      for (int i = 0;;) {
+        for (int t = 0; t < nkt; t += 2) {
+          step(As0, Bs0, As1, Bs1);
+          step(As1, Bs1, As0, Bs0);
+        }
+        if (++i == count) break;
+        finish();
+        m0 = tm * BM;
+        n0 = tn * BN;
+        clear();
+      }
+    } else {
+      for (int t = 0; t < steps; t += 2) {
+        step(As0, Bs0, As1, Bs1);
+        if (t + 1 < steps) step(As1, Bs1, As0, Bs0);
+      }
     }
     __builtin_amdgcn_s_waitcnt(kWaitAll);  // no load may outlive the workgroup's LDS
   };
   // whole k tiles get a loop without the guarded path
-  if (it0 < it1) {
+  if constexpr (STREAM) {
+    reduce(std::true_type{});
+  } else if (it0 < it1) {
     if (rows_ok && d.K % BK == 0)
       reduce(std::true_type{});
     else
       reduce(std::false_type{});
   }
-
-  const long nbatch = (long)d.nb1 * d.nb2;
-  if (!W && (d.cRm | d.cRn)) {
-    store_mapped<double, acc_t, TM, TN, WTM, WTN>(d, alpha, beta, C + b1 * d.sC1 + b2 * d.sC2, m0, n0, wm, wn, lane,
-                                                 acc);
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm * WTM + i * 16 + Mfma<double>::row(lane, r);
-        const int col = n0 + wn * WTN + j * 16 + (lane & 15);
-        if (row < d.M && col < d.N) {
-          const double v = acc[i][j][r];
-          if (W) {
-            W[((long)split * nbatch + batch) * ((long)d.M * d.N) + (long)row * d.N + col] = v;
-          } else {
-            double* cp = C + b1 * d.sC1 + b2 * d.sC2 + (long)row * d.ldc + col;
-            double out = alpha * v;
-            if (beta != 0.0) out += beta * (*cp);
-            *cp = out;
-          }
-        }
-      }
+  finish();
 }
 
 // LDS layouts (chosen per operand at compile time, FP64 64 banks x 4 B):
@@ -720,6 +761,23 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmDesc d, T alpha, 
   gemm_tile<T, BM, BN, BK, AK, BKC, TAG == 4>(d, alpha, A, B, beta, C, W, splitk, flat - split * per, split);
 }
 
+// The k-contiguous FP64 tiles of a short reduction: 512 workgroups that stay, each XCD with its
+// contiguous range of tiles (see gemm_tile_dma).  A workgroup per tile starts with the latency of
+// its first loads and ends with the stores of C, while the one wave per SIMD of its neighbour does
+// not fill the matrix core.  Measured, a workgroup per tile | here, with the share of the cycles
+// that the matrix units are busy: 1536 x 442368 over 384 8080 | 7843 us (85 | 89 %), 1536 x 110592
+// over 384 2012 | 1922 us, 960 x 96000 over 160 567 | 524 us (71 | 77 %).
+template <int TAG>
+__global__ __launch_bounds__(kThreads, 2) void gemm_stream_kernel(GemmDesc d, double alpha, const double* __restrict__ A,
+                                                                  const double* __restrict__ B, double beta,
+                                                                  double* __restrict__ C) {
+  const int ntiles = ((d.M + 127) / 128) * ((d.N + 127) / 128);
+  const int x = (int)blockIdx.x % 8, j = (int)blockIdx.x / 8, per = (int)gridDim.x / 8;
+  const int t0 = (int)((long)ntiles * x / 8), t1 = (int)((long)ntiles * (x + 1) / 8);
+  if (t0 + j >= t1) return;
+  gemm_tile_dma<128, 128, true>(d, alpha, A, B, beta, C, nullptr, 1, t0 + j, 0, (t1 - t0 - j + per - 1) / per, per);
+}
+
 // ---------------------------------------------------------------------------
 // Small FP64 products: the projected matrices and coefficient products of the window solver
 // (M, N <= 512, reductions of 40 .. N) and the contractions of small systems.  They are bound by
@@ -994,6 +1052,16 @@ long checked_workgroups(const GemmDesc& d) {
 constexpr long kCUs = 256;
 constexpr long kResident = 512;  // workgroups resident at once: 256 CUs x 2
 
+// Reductions up to 1024, where starts and ends are 3 % of a tile's time or more (beyond, the one-tile
+// kernel's rounds need no whole pairs of k tiles), and two rounds of tiles at least, so that a
+// workgroup has a next tile.
+inline bool stream_gemm(const GemmDesc& d, const double* A, const double* B) {
+  const long ntiles = (long)((d.M + 127) / 128) * ((d.N + 127) / 128);
+  return d.nb1 == 1 && d.nb2 == 1 && d.KB == 1 && d.sym < 0 && d.M % 8 == 0 && d.N % 8 == 0 && d.K % 32 == 0 &&
+         d.K <= 1024 && ntiles >= 2 * kResident && d.lda % 2 == 0 && d.ldb % 2 == 0 && (uintptr_t)A % 16 == 0 &&
+         (uintptr_t)B % 16 == 0;
+}
+
 template <typename T, int BM, int BN, int BK, bool AK, bool BKC, int TAG>
 void launch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T* C, hipStream_t s, Workspace ws) {
   const int tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
@@ -1066,6 +1134,14 @@ void launch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T* C, hi
     // short accumulating reductions: load C before the reduction (same arithmetic)
     if (splitk == 1 && beta != T(0) && total <= 4 && !(d.cRm | d.cRn)) {
       gemm_kernel<T, BM, BN, BK, AK, BKC, 4><<<grid, kThreads, 0, s>>>(d, alpha, A, B, beta, C, nullptr, 1);
+      PPW_LAUNCH_CHECK();
+      return;
+    }
+  }
+  // whole rounds of short reductions on workgroups that stay
+  if constexpr (std::is_same<T, double>::value && AK && BKC && BM == 128 && TAG < 2) {
+    if (splitk == 1 && stream_gemm(d, A, B)) {
+      gemm_stream_kernel<TAG><<<(unsigned)kResident, kThreads, 0, s>>>(d, alpha, A, B, beta, C);
       PPW_LAUNCH_CHECK();
       return;
     }

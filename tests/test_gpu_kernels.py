@@ -578,3 +578,29 @@ def test_gemm_tiled_edges(B, fp32, M, N, K, KB):
                     got.append(c.cpu())
                 assert torch.isfinite(got[0]).all() and (got[0][:, N] == -7.0).all()
                 assert torch.equal(got[0], got[1]), (tA, tB, ws)
+
+
+@pytest.mark.parametrize("M,N,K", [(4104, 4216, 32), (4096, 4096, 64), (4096, 8192, 96), (3976, 4344, 1024),
+                                   (4096, 4224, 1056)])
+def test_gemm_stream(B, M, N, K):
+    """k-contiguous FP64 products of whole tiles over short reductions (workgroups that stay for
+    several tiles): an odd and an even number of tile rounds, edges of 8 rows and columns, C updated
+    in place and with mapped rows and columns; and the first reduction past the limit.  Every element
+    is summed in the order of the one-tile kernel, which a batch of two takes: equal bit for bit."""
+    torch.manual_seed(K)
+    a = torch.randn(M, K, device="cuda", dtype=torch.float64)
+    b = torch.randn(N, K, device="cuda", dtype=torch.float64)
+    c0 = torch.randn(M, N, device="cuda", dtype=torch.float64)
+    c, c2 = c0.clone(), torch.stack([c0, c0]).contiguous()
+    kw = dict(M=M, N=N, K=K, lda=K, transB=1, ldb=K, ldc=N, alpha=1.25, beta=0.5)
+    B.gemm(a, b, c, **kw)
+    B.gemm(a, torch.stack([b, b]).contiguous(), c2, nbatch=2, sB=N * K, sC=M * N, **kw)
+    assert torch.equal(c2[0], c) and torch.equal(c2[1], c)
+    np.testing.assert_allclose((c[:50, -50:] - 0.5 * c0[:50, -50:]).cpu().numpy(),
+                               1.25 * (a[:50].cpu() @ b[-50:].cpu().T).numpy(), atol=1e-12, rtol=0)
+    # rows (q, j) of R = 8 at stride S apart, columns (p, d) of 8
+    plain, mapped = torch.empty(M, N, device="cuda", dtype=torch.float64), torch.zeros(N * M, device="cuda",
+                                                                                      dtype=torch.float64)
+    B.gemm(a, b, plain, M=M, N=N, K=K, lda=K, transB=1, ldb=K, ldc=N)
+    B.gemm_cmap(a, b, mapped, M=M, N=N, K=K, lda=K, transB=1, ldb=K, ldc=8, cRm=8, cSm=8 * N, cRn=8, cSn=64)
+    assert torch.equal(mapped.reshape(M // 8, N // 8, 8, 8).permute(0, 2, 1, 3).reshape(M, N), plain)

@@ -419,3 +419,26 @@ def test_window_strong_metric(P, scale):
     with P.Handle.from_system(sys, order=2) as h:
         e, vec, f, info = h.window_solve(w0, 4)
     _check_window(sys, 2, w0, 4, e, vec, f, info)
+
+
+@pytest.mark.parametrize("o,v,naux", [(16, 33, 100), (17, 21, 100), (30, 16, 100), (33, 17, 100), (45, 20, 70),
+                                      (48, 12, 70), (49, 12, 70)])
+def test_products_of_many_auxiliary_functions(P, o, v, naux):
+    """Enough auxiliary functions and vectors that the o x o by o x v updates of G take the kernel that
+    keeps the small factor in registers: one, two and three row tiles, ragged and full, and the first
+    size past it.  Tolerances as for the other FP64 and FP32 products here."""
+    torch = pytest.importorskip("torch")
+    sys = gen(17, o, v, naux, b_scale=0.3)
+    V = torch.tensor(np.random.default_rng(o).standard_normal((8, o * v)), device="cuda")
+    outs = [torch.empty_like(V) for _ in range(6)]
+    A, B, S = dense.assemble(sys, 2)
+    with P.Handle.from_system(sys, order=2, precision=P.PP_FP32) as h:
+        h.products(V, outs[0], outs[1], outs[2], fp32=False)
+        h.products(V, outs[3], outs[4], outs[5], fp32=True)
+    Vh = V.cpu().numpy()
+    ref = [(A @ Vh.T).T, (B @ Vh.T).T, (S @ Vh.T).T]
+    for j in range(3):
+        np.testing.assert_allclose(outs[j].cpu().numpy(), ref[j], rtol=0, atol=1e-12 * np.abs(ref[j]).max())
+        corr = ref[j] - (Vh * np.diag(A if j == 0 else (B if j == 1 else S))) if j < 2 else ref[j] - Vh
+        err = np.abs(outs[3 + j].cpu().numpy() - ref[j]).max()
+        assert err <= 2e-6 * np.abs(corr).max() + 1e-14, (j, err, np.abs(corr).max())

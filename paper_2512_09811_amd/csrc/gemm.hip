@@ -248,9 +248,8 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
                                          (__attribute__((address_space(3))) void*)(Bb + (wave + 4 * c) * 128), 16, 0,
                                          0);
     } else {
-      // element-wise guarded loads, zero outside the operand (unrolled only by two: their addresses
-      // would not fit the registers)
-#pragma unroll 2
+      // element-wise guarded loads, zero outside the operand
+#pragma unroll
       for (int i = 0; i < SA / 2 / kThreads; ++i) {
         const int pr = i * kThreads + tid, m = pr >> 3, kp = pr & 7;
         pair_t v;
@@ -261,7 +260,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
         }
         *reinterpret_cast<pair_t*>(Ab + 2 * swz16(m, kp)) = v;
       }
-#pragma unroll 2
+#pragma unroll
       for (int i = 0; i < SB / 2 / kThreads; ++i) {
         const int pr = i * kThreads + tid, nn = pr >> 3, kp = pr & 7;
         pair_t v;
@@ -1088,7 +1087,19 @@ __global__ void splitk_reduce_kernel(GemmDesc d, T alpha, T beta, const T* __res
     const long rc = idx % per;
     const int row = (int)(rc / d.N), col = (int)(rc % d.N);
     T s = T(0);
-    for (int k = 0; k < splitk; ++k) s += W[((long)k * nbatch + batch) * per + rc];
+    // (the order of the sum is that of the splits; the loads of eight go out together: one at a time,
+    // 64 splits of a 13 x 37 product over four vectors took 18 us)
+    const T* w = W + batch * per + rc;
+    const long step = nbatch * per;
+    int k = 0;
+    for (; k + 8 <= splitk; k += 8) {
+      T v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = w[(k + u) * step];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; k < splitk; ++k) s += w[k * step];
     const int b1 = (int)(batch / d.nb2), b2 = (int)(batch % d.nb2);
     T* cp = C + b1 * d.sC1 + b2 * d.sC2 + c_index(row, d.cRm, d.cSm, d.ldc) + c_index(d.cRn ? col + d.cBn : col, d.cRn, d.cSn, 1);
     T out = alpha * s;
@@ -1607,7 +1618,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
   // the tile, both waves of a SIMD read 12 fragments each with the matrix cores idle (768 cycles
   // of LDS time in every 3100 of MFMA time).  Measured on the amplitude contraction at
   // 128/512/1536 (33792 x 24576 x 65536): matrix units busy 60 -> 80 % of the active cycles and
-  // 259 -> 242 ms a launch (420 -> 450 TF/s).  The clock falls from 1.97 to 1.65 GHz as they fill
+  // 259 -> 236 ms a launch (420 -> 461 TF/s).  The clock falls from 1.97 to 1.65 GHz as they fill
   // (2.4 nominal): the launch is bound by power, as the library's bf16 product is (1323 TF/s at
   // 16384^3, 441 per three products).
   constexpr int kWaitAll = 0x0F70;  // vmcnt(0), other counters left alone (gfx9 s_waitcnt encoding)

@@ -719,7 +719,7 @@ def product_main(args):
         "fp64_steps": fsteps,
         "reduced_over_fp64": value / fp64_tflops if fp64_tflops else None,
         "roofline": {"bound": "mfma",
-                     "kernel": "gemm_sbf16_kernel<256,256,4,2,2,1> (H = tau G of one amplitude strip: split-BF16, "
+                     "kernel": "gemm_sbf16_kernel<256,256,4,2,1,1> (H = tau G of one amplitude strip: split-BF16, "
                                "three BF16 MFMAs per FP32-equivalent product), priced against the BF16 peak / 3",
                      "achieved": achieved, "peak": PEAK_SPLIT_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_SPLIT_BF16_TFLOPS,

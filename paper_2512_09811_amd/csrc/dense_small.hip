@@ -617,7 +617,7 @@ void tridiagonalize(int n, const double* A, double* ex, double* d, double* e, do
 // and per triangular solve, so its time is (steps in sequence) x (latency of a step), and the
 // two kernels below shorten both.  Measured on MI355X at n = 240..480, p = 28: 1.4 ms in one
 // workgroup (one thread per eigenvalue bisecting with a division per Sturm step, then one
-// thread per vector with its arrays in global memory); now both kernels together 0.17 ms.
+// thread per vector with its arrays in global memory); now both kernels together 0.16 ms.
 
 // Scale of the tridiagonal: a power of two that brings its Gershgorin interval [gl, gu]
 // into [-1, 1], so that a Sturm sequence grows by at most a factor 4 per step.
@@ -962,7 +962,8 @@ __global__ void tridiag_apply_kernel(int n, int p, const double* __restrict__ d,
 
 // Z[r][j] = (H_0 ... H_{n-3} v_j)[r], one wave per vector with the vector in registers (8 per
 // lane up to n = 512): a reflector costs one wave sum and no barrier, and the next one's
-// elements are loaded meanwhile.  At n = 480: 60 us against 150 us with a workgroup per vector.
+// elements are loaded meanwhile.  In four windows with bases up to
+// 430: 74 us on average, 150 us with a workgroup per vector.
 __global__ __launch_bounds__(64) void backtransform_kernel(int n, int p, const double* __restrict__ Hh,
                                                            const double* __restrict__ V, double* __restrict__ Z) {
   constexpr int S = kMaxN / 64;

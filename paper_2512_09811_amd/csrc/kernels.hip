@@ -415,7 +415,7 @@ dim3 tau_grid(int o, int v, int ib) {
 }
 }  // namespace
 
-// One FP64 strip at 96/384/1152 (the whole 36864^2 matrix): 3.6 ms against 6.05 ms when every
+// One FP64 strip at 96/384/1152 (the whole 36864^2 matrix): 4.4 ms against 7.2 ms when every
 // tile read its transpose as well and S was complete.
 void tau_strip(const double* S, int o, int v, int k0, int ib, const double* eps_o, const double* eps_v, double* tau,
                double* t, double* tEv, double* tEo, double* partial, hipStream_t s) {
@@ -425,7 +425,7 @@ void tau_strip(const double* S, int o, int v, int k0, int ib, const double* eps_
 }
 
 // split: tau in the chunk layout of split_sbf16, written by this kernel where v is a multiple of
-// 8 (the strip is then not read and written once more: 12.2 -> 4 ms a strip at 128/512/1536),
+// 8 (the strip is then not read and written once more: 13 -> 6.6 ms a strip at 128/512/1536),
 // else by a pass over the finished rows.
 void tau_strip_f32(const float* S, int o, int v, int k0, int ib, const double* eps_o, const double* eps_v, float* tau,
                    long ld, bool split, hipStream_t s) {

@@ -53,7 +53,7 @@ inline int gridn(long n) { return (int)std::max<long>(1, std::min<long>((n + kB 
 // a few microseconds each, 9-16 us apart in a trace, so a cycle's time is mostly the number of
 // launches.  The kernels below therefore each take a whole step of that chain (a norm and its
 // scaling, a product's three combinations, all coefficients of a block, the six sums, alpha and
-// the update of a Jacobi step): 8/24/64 first order 180 -> 100 launches and 50 -> 12 copies a cycle.
+// the update of a Jacobi step): 8/24/64 first order 180 -> 90 launches and 50 -> 19 copies a cycle.
 
 // rows X[q][N] to unit length, their norms (1 for a zero row) in nrm; one workgroup per row
 __global__ __launch_bounds__(kB) void unit_rows_kernel(double* __restrict__ X, long N, double* __restrict__ nrm) {

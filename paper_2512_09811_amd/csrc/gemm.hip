@@ -1305,6 +1305,18 @@ void gemm_dispatch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T
     launch<T, BMv, BNv, 16, AKv, BKv, TAG>(d, alpha, A, B, beta, C, s, ws);         \
     return;                                                                         \
   }
+  if constexpr (TAG == 0) {
+    // Rows of tiles of 96 where as many of them do as of 128 (96 rows in one, 129 .. 192 in two,
+    // 257 .. 288 in three): a quarter less work for the same workgroups and reduction splits.  K_A
+    // at 96/384/1152 (96 x 384 over 96 x 1152, 16 vectors): 2.82 ms with 128 rows, 2.17 with 96.
+    if (big && d.sym < 0 && (d.M + 95) / 96 == (d.M + 127) / 128) {
+      checked_workgroups<128, 128, 16>(d);
+      PPW_GEMM_CASE(96, 128, true, true)
+      PPW_GEMM_CASE(96, 128, true, false)
+      PPW_GEMM_CASE(96, 128, false, true)
+      PPW_GEMM_CASE(96, 128, false, false)
+    }
+  }
   if (big) {
     PPW_GEMM_CASE(128, 128, true, true)
     PPW_GEMM_CASE(128, 128, true, false)

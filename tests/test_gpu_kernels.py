@@ -604,3 +604,29 @@ def test_gemm_stream(B, M, N, K):
     B.gemm(a, b, plain, M=M, N=N, K=K, lda=K, transB=1, ldb=K, ldc=N)
     B.gemm_cmap(a, b, mapped, M=M, N=N, K=K, lda=K, transB=1, ldb=K, ldc=8, cRm=8, cSm=8 * N, cRn=8, cSn=64)
     assert torch.equal(mapped.reshape(M // 8, N // 8, 8, 8).permute(0, 2, 1, 3).reshape(M, N), plain)
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("M", [96, 97, 129, 192, 193, 257, 288, 289])
+def test_gemm_rows_96(B, fp32, M):
+    """Tiles of 96 rows (96, 129 .. 192 and 257 .. 288 rows of C) and of 128 beside them, for all
+    operand layouts, with and without reduction splits.  Every element is summed in the order of the
+    128-row tiles, which a grouped launch takes: equal bit for bit."""
+    torch.manual_seed(M)
+    N, K = 4200, 330
+    dt = torch.float32 if fp32 else torch.float64
+    a, b = torch.randn(M, K, device="cuda", dtype=dt), torch.randn(N, K, device="cuda", dtype=dt)
+    for tA in (0, 1):
+        for tB in (0, 1):
+            x, y = (a.T if tA else a).contiguous(), (b if tB else b.T).contiguous()
+            kw = dict(M=M, N=N, K=K, transA=tA, transB=tB, lda=x.shape[1], ldb=y.shape[1], ldc=N)
+            one, split = (torch.empty(M, N, device="cuda", dtype=dt) for _ in range(2))
+            B.gemm(x, y, one, fp32=fp32, **kw)
+            B.gemm(x, y, split, fp32=fp32, ws_bytes=1 << 28, **kw)
+            members = [dict(A=x, B=y, C=torch.empty(M, N, device="cuda", dtype=dt), alpha=1.0, beta=0.0, **kw)
+                       for _ in range(16)]
+            assert B.gemm_group(members, fp32=fp32) >= 1
+            assert torch.equal(members[0]["C"], one) and torch.equal(members[15]["C"], one)
+            ref = a.double() @ b.double().T
+            tol = (1.2e-7 if fp32 else 2.3e-16) * K
+            assert (split.double() - ref).abs().max() <= tol * a.abs().max().item() * b.abs().max().item()

@@ -12,6 +12,11 @@ namespace ppw {
 // 8-value chunks, plus 64 values (256 B) when that would start the rows a multiple of
 // 4 KiB apart.  Rows 1 MiB apart (n = 262144) all start on the same memory channels and
 // a 256-row GEMM tile of them ran 6% slower than with the 256 B offset.
+// Row stride of the FP64 G and of rebuilt amplitude strips: rows a multiple of 256 KiB apart start
+// on the same memory channels (the amplitude contraction with rows 2 MiB apart: 62.9 TF/s, with 32
+// values between them 72.2; 512 KiB apart 69.7 and 71.4).
+inline long padded_stride64(long n) { return n % 32768 == 0 ? n + 32 : n; }
+
 inline long padded_stride(long n) {
   const long p = (n + 7) / 8 * 8;
   return (p * 4) % 4096 == 0 ? p + 64 : p;
@@ -276,6 +281,7 @@ class EventLog {
 struct Context {
   int o = 0, v = 0, naux = 0, order = 0;
   long N = 0;
+  long ld64 = 0;  // row stride of the FP64 G and amplitude strips (padded_stride64(N))
   long N8 = 0;  // row stride of the FP32 / split-BF16 G and amplitude rows (padded_stride(N))
   int X8 = 0;   // naux rounded up to a multiple of 8
   int device = 0;

@@ -16,9 +16,9 @@ void permute3(const double* in, double* out, int d0, int d1, int d2, const int p
 //   t   = S / D
 //   tEv = t * (e_k + e_l - e_y)
 //   tEo = t * (e_k - e_x - e_y)
-// and per-block partial sums of tau * S into partial[] (one per block, see tau_blocks()).
+// (tau in rows of ld >= o v values) and per-block partial sums of tau * S into partial[] (one per block, see tau_blocks()).
 void tau_strip(const double* S, int o, int v, int k0, int ib, const double* eps_o, const double* eps_v,
-               double* tau, double* t, double* tEv, double* tEo, double* partial, hipStream_t s);
+               double* tau, long ld, double* t, double* tEv, double* tEo, double* partial, hipStream_t s);
 long tau_blocks(int o, int v, int ib);
 // Same strip built in FP32 (for the reduced-precision product path): tau only, rows of
 // ld >= o v values (columns o v .. ld - 1 are not written, or with split left as they are:

@@ -418,8 +418,8 @@ dim3 tau_grid(int o, int v, int ib) {
 // One FP64 strip at 96/384/1152 (the whole 36864^2 matrix): 4.4 ms against 7.2 ms when every
 // tile read its transpose as well and S was complete.
 void tau_strip(const double* S, int o, int v, int k0, int ib, const double* eps_o, const double* eps_v, double* tau,
-               double* t, double* tEv, double* tEo, double* partial, hipStream_t s) {
-  tau_strip_kernel<double, false><<<tau_grid(o, v, ib), kBlock, 0, s>>>(S, o, v, k0, ib, eps_o, eps_v, tau, (long)o * v,
+               long ld, double* t, double* tEv, double* tEo, double* partial, hipStream_t s) {
+  tau_strip_kernel<double, false><<<tau_grid(o, v, ib), kBlock, 0, s>>>(S, o, v, k0, ib, eps_o, eps_v, tau, ld,
                                                                         t, tEv, tEo, partial);
   PPW_LAUNCH_CHECK();
 }

@@ -131,6 +131,7 @@ Context* setup_context(const SetupParams& p) {
     c->order = p.order;
     c->split_bf16 = p.split_bf16 && p.want_f32;
     c->N = (long)p.o * p.v;
+    c->ld64 = padded_stride64(c->N);
     c->N8 = padded_stride(c->N);
     c->X8 = (p.naux + 7) / 8 * 8;
     c->device = p.device;
@@ -224,7 +225,7 @@ Context* setup_context(const SetupParams& p) {
         GemmDesc d = gd(nb * v, (int)N, X, 1, N, 0, N, N);
         d.sym = (long)k0 * v;
         gemm_f64(d, 1.0, c->Bov + (size_t)k0 * v, c->Bov, 0.0, S, s, c->ws);
-        tau_strip(S, o, v, k0, nb, c->eps_o, c->eps_v, tau_b, t, tEv, tEo, partial + pofs, s);
+        tau_strip(S, o, v, k0, nb, c->eps_o, c->eps_v, tau_b, N, t, tEv, tEo, partial + pofs, s);
         pofs += tau_blocks(o, v, nb);
         // Gv[a][b] += sum_k sum_(l,y) tau[(k,a)][(l,y)] t[(k,b)][(l,y)]
         GemmDesc g = gd(v, v, (int)N, 0, N, 1, N, v);
@@ -383,14 +384,14 @@ void grow_workspace(Context& c, int k) {
   Grow g(c);
   c.kcap = 0;
   g.add(c.w_c, (size_t)X * k, "ws c");
-  g.add(c.w_G, (size_t)k * X * N, "ws G");
+  g.add(c.w_G, (size_t)k * X * c.ld64, "ws G");
   g.add(c.w_U, (size_t)k * o * c.ns * X * o, "ws U");
   if (c.order >= 2) {
     const int ib = c.tau ? o : c.strip_rows;
     g.add(c.w_H, (size_t)ib * v * k * X, "ws H");
     if (!c.tau) {
       g.add(c.w_S, (size_t)c.strip_rows * v * N, "ws strip S");
-      g.add(c.w_tau, (size_t)c.strip_rows * v * N, "ws strip tau");
+      g.add(c.w_tau, (size_t)c.strip_rows * v * c.ld64, "ws strip tau");
     }
   }
   g.done(c.kcap, k);
@@ -462,8 +463,8 @@ void gemm_hhat_t<float>(const GemmDesc& d, float a, const float* A, const float*
   gemm_f32_hhat(d, a, A, B, b, C, s, ws);
 }
 inline void tau_strip_t(const double* S, int o, int v, int k0, int ib, const double* eo, const double* ev, double* tau,
-                        long, bool, hipStream_t s) {
-  tau_strip(S, o, v, k0, ib, eo, ev, tau, nullptr, nullptr, nullptr, nullptr, s);
+                        long ld, bool, hipStream_t s) {
+  tau_strip(S, o, v, k0, ib, eo, ev, tau, ld, nullptr, nullptr, nullptr, nullptr, s);
 }
 inline void tau_strip_t(const float* S, int o, int v, int k0, int ib, const double* eo, const double* ev, float* tau,
                         long ld, bool split, hipStream_t s) {
@@ -486,7 +487,7 @@ struct Ops {
 
 Ops<double> ops64(Context& c) {
   return Ops<double>{c.Bov, c.BovLam, c.Boo, c.Bvv, c.Boo_t, c.R, c.tau, c.Gv, c.Ev, c.Go, c.Eo,
-                     c.w_c, c.w_G, c.w_U, c.w_H, c.w_S, c.w_tau, c.N, c.N, c.N, false, nullptr};
+                     c.w_c, c.w_G, c.w_U, c.w_H, c.w_S, c.w_tau, c.ld64, c.N, c.ld64, false, nullptr};
 }
 Ops<float> ops32(Context& c) {
   const bool sbf = c.split_bf16 && c.order >= 2;
@@ -759,7 +760,7 @@ Footprint context_footprint(int o, int v, int X, int order, bool dip, bool store
   auto r = [](size_t bytes) { return ((bytes + 255) / 256) * 256; };
   const size_t D = sizeof(double), F = sizeof(float);
   const size_t N = (size_t)o * v, K = (size_t)k;
-  const size_t N8 = (size_t)padded_stride((long)N), X8 = ((size_t)X + 7) / 8 * 8;
+  const size_t ld64 = (size_t)padded_stride64((long)N), N8 = (size_t)padded_stride((long)N), X8 = ((size_t)X + 7) / 8 * 8;
   const size_t ns = order >= 2 ? 2 : 1;
   const int ib = order >= 2 ? std::max(1, std::min(strip_rows > 0 ? strip_rows : o, o)) : 0;
   size_t keep = r(o * D) + r(v * D) + r(X * (size_t)o * o * D) + r(X * (size_t)v * v * D) + r(ns * X * N * D);
@@ -788,11 +789,11 @@ Footprint context_footprint(int o, int v, int X, int order, bool dip, bool store
   size_t ws = 0;
   if (order >= 1) {
     ws += r(K * N * D) + r(4 * K * N * D);
-    ws += r(X * K * D) + r(K * X * N * D) + r(K * o * ns * X * o * D);
+    ws += r(X * K * D) + r(K * X * ld64 * D) + r(K * o * ns * X * o * D);
     const size_t ibw = store ? (size_t)o : (size_t)ib;
     if (order >= 2) {
       ws += r(ibw * v * K * X * D);
-      if (!store) ws += 2 * r((size_t)ib * v * N * D);
+      if (!store) ws += r((size_t)ib * v * N * D) + r((size_t)ib * v * ld64 * D);
     }
     if (want_f32) {
       ws += 4 * r(K * N * F) + r(4 * K * N * F);
@@ -840,11 +841,12 @@ size_t sigma_reserve_bytes(const Context& c, int k, int precision) {
   } else {
     const size_t ib = c.tau ? o : (size_t)c.strip_rows;
     t += grow(c.kcap, [&](size_t q) {
-      size_t b = r(X * q, D) + r(q * X * N, D) + r(q * o * ns * X * o, D);
+      size_t b = r(X * q, D) + r(q * X * (size_t)c.ld64, D) + r(q * o * ns * X * o, D);
       if (c.order >= 2) b += r(ib * v * q * X, D);
       return b;
     });
-    if (c.kcap == 0 && c.order >= 2 && !c.tau) t += 2 * r((size_t)c.strip_rows * v * N, D);
+    if (c.kcap == 0 && c.order >= 2 && !c.tau)
+      t += r((size_t)c.strip_rows * v * N, D) + r((size_t)c.strip_rows * v * (size_t)c.ld64, D);
   }
   return t;
 }

@@ -76,10 +76,6 @@ void to_f64(long n, const float* x, double* y, hipStream_t s);
 void response_on_grid(int n, const double* e, const double* f, int n_omega, const double* omega, double eta,
                       double* re, double* im, double* lor, hipStream_t s);
 
-// Column statistics of k column-vectors of length n stored [k][n] (row-major per vector):
-// out[c] = sum_r x[c][r] * y[c][r] (wavefront-level reductions, deterministic order).
-void column_dots(const double* x, const double* y, long n, int k, double* out, hipStream_t s);
-
 }  // namespace ppw
 
 namespace ppw {

@@ -358,18 +358,6 @@ __global__ void to_f64_kernel(long n, const float* __restrict__ x, double* __res
     y[i] = (double)x[i];
 }
 
-// one block per column; fixed reduction order
-__global__ void column_dots_kernel(const double* __restrict__ x, const double* __restrict__ y, long n,
-                                   double* __restrict__ out) {
-  const int c = blockIdx.x;
-  const double* xc = x + (long)c * n;
-  const double* yc = y + (long)c * n;
-  double acc = 0.0;
-  for (long i = threadIdx.x; i < n; i += blockDim.x) acc += xc[i] * yc[i];
-  const double s = block_sum(acc);
-  if (threadIdx.x == 0) out[c] = s;
-}
-
 __global__ void combine_pairs_kernel(long N, int m, const double* __restrict__ AV, const double* __restrict__ BV,
                                      const double* __restrict__ SV, int metric, double* __restrict__ out) {
   const long n = 2 * N * m;
@@ -529,12 +517,6 @@ void exciton_dos(int o, int v, const double* eo, const double* ev, const double*
 
 void to_f64(long n, const float* x, double* y, hipStream_t s) {
   to_f64_kernel<<<grid_for(n), kBlock, 0, s>>>(n, x, y);
-  PPW_LAUNCH_CHECK();
-}
-
-void column_dots(const double* x, const double* y, long n, int k, double* out, hipStream_t s) {
-  if (k <= 0) return;
-  column_dots_kernel<<<k, kBlock, 0, s>>>(x, y, n, out);
   PPW_LAUNCH_CHECK();
 }
 

@@ -119,8 +119,13 @@ long sym_tiles(const GemmDesc& d) {
 // doubles is 8 slots of 16 B; (row r, pair kp) lives in slot r * 8 + (kp ^ ((r >> 1) & 7)),
 // which puts the 16 rows of an MFMA fragment read in 16 different 16-byte bank groups.
 // Lanes choose their source element so that each wave's 64 slots (8 rows) are filled in
-// one instruction.  Ragged tiles (an edge in m, n or k, or rows not 16-byte aligned) are
-// loaded through registers into the same layout.  The two LDS buffers are separate
+// one instruction.  Rows past an edge in m or n repeat the last one (their results are not
+// stored); in a ragged k tile the pairs past K repeat the last one and are overwritten by zeros
+// once they have landed.  Operands whose rows are not all 16-byte aligned, or of an odd K, go
+// through registers into the same layout.  Measured, with element-wise guarded loads of every k
+// tile as soon as M, N or K was not a multiple of 8, 8 or 16 | here: 672 x 499100 over 434 8107 |
+// 5351 us, 2250 x 1320 over 2250 463 | 289, 5889 x 3760 over 5889 (odd rows) 7381 | 4611; a launch
+// of whole tiles is as fast as before (6400 x 7200 over 6400 9.3 ms).  The two LDS buffers are separate
 // arrays and the loop is unrolled by two, so a buffer being filled and the buffer being
 // read are distinct objects to the compiler.  MFMA operands and their order are those of
 // the register-staged path, so results are bit-identical to it.
@@ -212,66 +217,93 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   const long it1 = min(total, it0 + chunk);
   const int lda32 = (int)d.lda, ldb32 = (int)d.ldb;
   const int mrem = d.M - m0, nrem = d.N - n0;
-  // A chunk is 8 rows, (wave + 4 c) 8 on; chunks past the edge repeat the last one (their results
-  // are not stored), so an edge has to lie between chunks.  The first row of a chunk is the same
-  // for the whole wave and the lanes' offsets from it are those of every chunk, so that a load
-  // takes its address from scalar registers and one vector register.
-  const bool rows_ok = mrem % 8 == 0 && nrem % 8 == 0 && (d.lda % 2) == 0 && (d.ldb % 2) == 0 && (d.sAk % 2) == 0 &&
-                       (d.sBk % 2) == 0 && ((uintptr_t)Atile % 16) == 0 && ((uintptr_t)Btile % 16) == 0;
+  // A chunk is 8 rows, (wave + 4 c) 8 on; chunks past the edge repeat the last one and rows past it
+  // within a chunk the last row.  The first row of a chunk is the same for the whole wave, and the
+  // lanes' offsets from it are those of every chunk but the one at an edge, so that a load takes its
+  // address from scalar registers and one vector register.
+  const bool dma = (d.lda % 2) == 0 && (d.ldb % 2) == 0 && (d.sAk % 2) == 0 && (d.sBk % 2) == 0 &&
+                   ((uintptr_t)Atile % 16) == 0 && ((uintptr_t)Btile % 16) == 0 && d.K % 2 == 0;
+  const int kpl = (lane & 7) ^ (4 * (wave & 1) + (lane >> 4));
   long rowA[CA], rowB[CB];
+  unsigned laneA[CA], laneB[CB];
   auto chunk_rows = [&](int mr, int nr) {
+    // (a stream's edges lie between chunks)
+    const int ma = (mr - 1) & ~7, nb = (nr - 1) & ~7;
+    const int la = lane >> 3, ea = STREAM ? la : min(la, (mr - 1) & 7), eb = STREAM ? la : min(la, (nr - 1) & 7);
 #pragma unroll
-    for (int c = 0; c < CA; ++c) rowA[c] = (long)min((wave + 4 * c) * 8, mr - 8) * d.lda;
+    for (int c = 0; c < CA; ++c) {
+      const int r = (wave + 4 * c) * 8;
+      rowA[c] = (long)min(r, ma) * d.lda;
+      laneA[c] = 8u * ((unsigned)(r < ma ? la : ea) * (unsigned)lda32 + 2u * kpl);
+    }
 #pragma unroll
-    for (int c = 0; c < CB; ++c) rowB[c] = (long)min((wave + 4 * c) * 8, nr - 8) * d.ldb;
+    for (int c = 0; c < CB; ++c) {
+      const int r = (wave + 4 * c) * 8;
+      rowB[c] = (long)min(r, nb) * d.ldb;
+      laneB[c] = 8u * ((unsigned)(r < nb ? la : eb) * (unsigned)ldb32 + 2u * kpl);
+    }
   };
   chunk_rows(mrem, nrem);
-  const int kpl = (lane & 7) ^ (4 * (wave & 1) + (lane >> 4));
-  const unsigned laneA = 8u * ((unsigned)(lane >> 3) * (unsigned)lda32 + 2u * kpl);
-  const unsigned laneB = 8u * ((unsigned)(lane >> 3) * (unsigned)ldb32 + 2u * kpl);
+  // the pairs of the ragged k tile that lie past K: how far back (bytes) the last one is from this lane's
+  const int kpast = kpl - ((d.K % BK) / 2 - 1);
+  const unsigned back = kpast > 0 ? 16u * kpast : 0u;
+  // k tile (kb, kt) straight into buffer (Ab, Bb)
+  auto fill = [&](double* Ab, double* Bb, int kb, int kt, auto rag) {
+    const double* Ak = Atile + kb * d.sAk + kt * BK;
+    const double* Bk = Btile + kb * d.sBk + kt * BK;
+    const unsigned off = decltype(rag)::value && kt + 1 == nkt ? back : 0u;
+#pragma unroll
+    for (int c = 0; c < CA; ++c)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)((const char*)(Ak + rowA[c]) + (laneA[c] - off)),
+          (__attribute__((address_space(3))) void*)(Ab + (wave + 4 * c) * 128), 16, 0, 0);
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)((const char*)(Bk + rowB[c]) + (laneB[c] - off)),
+          (__attribute__((address_space(3))) void*)(Bb + (wave + 4 * c) * 128), 16, 0, 0);
+  };
+  // zeros past K in a ragged tile: the slots that this lane's own loads (landed) filled
   typedef double pair_t __attribute__((ext_vector_type(2)));
-  // fill buffer (Ab, Bb) with the k tile (kb, kt)
-  auto fill = [&](double* Ab, double* Bb, int kb, int kt, auto whole) {
-    const int k0 = kt * BK;
-    const double* Ak = Atile + kb * d.sAk + k0;
-    const double* Bk = Btile + kb * d.sBk + k0;
-    const int krem = d.K - k0;
-    if (decltype(whole)::value || (rows_ok && krem >= BK)) {
+  auto cut = [&](double* Ab, double* Bb) {
+    if (kpast <= 0) return;
 #pragma unroll
-      for (int c = 0; c < CA; ++c)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)(Ak + rowA[c]) + laneA),
-                                         (__attribute__((address_space(3))) void*)(Ab + (wave + 4 * c) * 128), 16, 0,
-                                         0);
+    for (int c = 0; c < CA; ++c) *reinterpret_cast<pair_t*>(Ab + (wave + 4 * c) * 128 + 2 * lane) = pair_t{0.0, 0.0};
 #pragma unroll
-      for (int c = 0; c < CB; ++c)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)(Bk + rowB[c]) + laneB),
-                                         (__attribute__((address_space(3))) void*)(Bb + (wave + 4 * c) * 128), 16, 0,
-                                         0);
-    } else {
-      // element-wise guarded loads, zero outside the operand
+    for (int c = 0; c < CB; ++c) *reinterpret_cast<pair_t*>(Bb + (wave + 4 * c) * 128 + 2 * lane) = pair_t{0.0, 0.0};
+  };
+  // k tile (kb, kt) through registers: pairs of row r0 + 32 i from element 2 kp on.  A pair past the
+  // end of K is read from the last two values of its row (never past them; K is 2 at least) and put
+  // right, with zeros past K, when it is stored.  Offsets are worked out anew for every tile (the
+  // thread's number is hidden from the compiler, which would otherwise keep them all in registers
+  // that the accumulators need).
+  typedef double pair8_t __attribute__((ext_vector_type(2), aligned(8)));
+  auto hidden = [](int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  pair_t sa[CA], sb[CB];
+  auto load_regs = [&](int kb, int kt) {
+    const double* Ak = Atile + kb * d.sAk + kt * BK;
+    const double* Bk = Btile + kb * d.sBk + kt * BK;
+    const int id = hidden(tid), r0 = id >> 3, kc = min(2 * (id & 7), d.K - kt * BK - 2);
 #pragma unroll
-      for (int i = 0; i < SA / 2 / kThreads; ++i) {
-        const int pr = i * kThreads + tid, m = pr >> 3, kp = pr & 7;
-        pair_t v;
+    for (int i = 0; i < CA; ++i)
+      sa[i] = *reinterpret_cast<const pair8_t*>(Ak + (min(r0 + 32 * i, mrem - 1) * lda32 + kc));
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int kk = 2 * kp + h;
-          v[h] = (m < mrem && kk < krem) ? Ak[m * lda32 + kk] : 0.0;
-        }
-        *reinterpret_cast<pair_t*>(Ab + 2 * swz16(m, kp)) = v;
-      }
+    for (int i = 0; i < CB; ++i)
+      sb[i] = *reinterpret_cast<const pair8_t*>(Bk + (min(r0 + 32 * i, nrem - 1) * ldb32 + kc));
+  };
+  auto store_regs = [&](double* Ab, double* Bb, int kt) {
+    const int id = hidden(tid), r0 = id >> 3, kp = id & 7;
+    const int left = d.K - kt * BK - 2 * kp;  // values of K from the pair's first on
+    auto put = [&](double* p, pair_t v) {
+      *reinterpret_cast<pair_t*>(p) = pair_t{left >= 2 ? v[0] : (left == 1 ? v[1] : 0.0), left >= 2 ? v[1] : 0.0};
+    };
 #pragma unroll
-      for (int i = 0; i < SB / 2 / kThreads; ++i) {
-        const int pr = i * kThreads + tid, nn = pr >> 3, kp = pr & 7;
-        pair_t v;
+    for (int i = 0; i < CA; ++i) put(Ab + 2 * swz16(r0 + 32 * i, kp), sa[i]);
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int kk = 2 * kp + h;
-          v[h] = (nn < nrem && kk < krem) ? Bk[nn * ldb32 + kk] : 0.0;
-        }
-        *reinterpret_cast<pair_t*>(Bb + 2 * swz16(nn, kp)) = v;
-      }
-    }
+    for (int i = 0; i < CB; ++i) put(Bb + 2 * swz16(r0 + 32 * i, kp), sb[i]);
   };
 
   acc_t acc[TM][TN];
@@ -345,39 +377,50 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   // 6400 x 14336 x 6400: 68.5 TF/s with the barrier at the end of the tile, 69.7 with it here,
   // 72.4 with the loads spread (the library's product: 71.1); matrix units busy 88 -> 93 %.
   constexpr int kWaitAll = 0x0F70;  // vmcnt(0): this wave's loads into LDS have landed
-  auto reduce = [&](auto whole) {
-    int kb = (int)(it0 / nkt), kt = (int)(it0 % nkt);
-    const int steps = (int)(it1 - it0);
-    int ahead = 0;  // tile last loaded (STREAM: output tile whose operands are loaded)
-    // the next tile; past the end the last one again, so that no load stands behind a branch, which
-    // would keep the MFMAs from hiding its issue (what it brings is not used)
-    auto advance = [&]() {
-      if constexpr (STREAM) {
-        if (kt + 1 < nkt) {
-          ++kt;
-        } else if (ahead + 1 < count) {
-          ++ahead;
-          kt = 0;
-          tile_coords((int)flat + ahead * stride, tiles_m, tiles_n, tm, tn);
-          Atile = A + (long)tm * BM * d.lda;
-          Btile = B + (long)tn * BN * d.ldb;
-          chunk_rows(d.M - tm * BM, d.N - tn * BN);
+  const int steps = (int)(it1 - it0);
+  // the k tile to load next; past the end the last one again, so that no load stands behind a branch,
+  // which would keep the MFMAs from hiding its issue (what it brings is not used)
+  int kb = (int)(it0 / nkt), kt = (int)(it0 % nkt);
+  int ahead = 0;  // tile last loaded (STREAM: output tile whose operands are loaded)
+  auto advance = [&]() {
+    if constexpr (STREAM) {
+      if (kt + 1 < nkt) {
+        ++kt;
+      } else if (ahead + 1 < count) {
+        ++ahead;
+        kt = 0;
+        tile_coords((int)flat + ahead * stride, tiles_m, tiles_n, tm, tn);
+        Atile = A + (long)tm * BM * d.lda;
+        Btile = B + (long)tn * BN * d.ldb;
+        chunk_rows(d.M - tm * BM, d.N - tn * BN);
+      }
+    } else {
+      const bool more = ahead + 1 < steps, wrap = more && kt + 1 == nkt;
+      ahead += more ? 1 : 0;
+      kt = wrap ? 0 : kt + (more ? 1 : 0);
+      kb += wrap ? 1 : 0;
+    }
+  };
+  double a0[TM], b0[TN], a1[TM], b1v[TN];
+  // straight into LDS (rag: the last k tile of each outer block is ragged)
+  auto reduce = [&](auto rag) {
+    // a tile that has landed, behind the barrier: ragged, it is cut, and the barrier waited for again
+    auto landed = [&](double* Ab, double* Bb) {
+      if constexpr (decltype(rag)::value) {
+        if (kt + 1 == nkt) {
+          cut(Ab, Bb);
+          __syncthreads();
         }
-      } else {
-        const bool more = ahead + 1 < steps, wrap = more && kt + 1 == nkt;
-        ahead += more ? 1 : 0;
-        kt = wrap ? 0 : kt + (more ? 1 : 0);
-        kb += wrap ? 1 : 0;
       }
     };
-    double a0[TM], b0[TN], a1[TM], b1v[TN];
-    fill(As0, Bs0, kb, kt, whole);
+    fill(As0, Bs0, kb, kt, rag);
     __builtin_amdgcn_s_waitcnt(kWaitAll);
     __syncthreads();
+    landed(As0, Bs0);
     advance();
-    fill(As1, Bs1, kb, kt, whole);
+    fill(As1, Bs1, kb, kt, rag);
     frag(As0, Bs0, 0, a0, b0);
-    auto step = [&](double* Ac, double* Bc, const double* An, const double* Bn) {
+    auto step = [&](double* Ac, double* Bc, double* An, double* Bn) {
       frag(Ac, Bc, 4, a1, b1v);
       mma(a0, b0);
       interleave(std::false_type{});
@@ -390,11 +433,12 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_waitcnt(kWaitAll);
       __syncthreads();
+      landed(An, Bn);
       advance();
-      fill(Ac, Bc, kb, kt, whole);
+      fill(Ac, Bc, kb, kt, rag);
       frag(An, Bn, 0, a0, b0);
       mma(a1, b1v);
-      interleave(whole);
+      interleave(std::true_type{});
       __builtin_amdgcn_sched_barrier(0);
     };
     if constexpr (STREAM) {
@@ -417,14 +461,49 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
     }
     __builtin_amdgcn_s_waitcnt(kWaitAll);  // no load may outlive the workgroup's LDS
   };
-  // whole k tiles get a loop without the guarded path
+  // through registers, which go to the free buffer during the first k group and take the next tile
+  // during the second
+  auto reduce_regs = [&]() {
+    load_regs(kb, kt);
+    store_regs(As0, Bs0, kt);
+    advance();
+    load_regs(kb, kt);
+    __syncthreads();
+    frag(As0, Bs0, 0, a0, b0);
+    auto step = [&](const double* Ac, const double* Bc, double* An, double* Bn) {
+      frag(Ac, Bc, 4, a1, b1v);
+      store_regs(An, Bn, kt);
+      mma(a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+      advance();
+      frag(Ac, Bc, 8, a0, b0);
+      load_regs(kb, kt);
+      mma(a1, b1v);
+      __builtin_amdgcn_sched_barrier(0);
+      frag(Ac, Bc, 12, a1, b1v);
+      mma(a0, b0);
+      interleave(std::false_type{});
+      __builtin_amdgcn_sched_barrier(0);
+      __syncthreads();
+      frag(An, Bn, 0, a0, b0);
+      mma(a1, b1v);
+      interleave(std::false_type{});
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int t = 0; t < steps; t += 2) {
+      step(As0, Bs0, As1, Bs1);
+      if (t + 1 < steps) step(As1, Bs1, As0, Bs0);
+    }
+  };
   if constexpr (STREAM) {
-    reduce(std::true_type{});
-  } else if (it0 < it1) {
-    if (rows_ok && d.K % BK == 0)
-      reduce(std::true_type{});
-    else
+    reduce(std::false_type{});
+  } else if (steps > 0) {
+    if (!dma)
+      reduce_regs();
+    else if (d.K % BK == 0)
       reduce(std::false_type{});
+    else
+      reduce(std::true_type{});
   }
   finish();
 }
@@ -1035,6 +1114,7 @@ inline int small_waves(const GemmDesc& d) {
   return tiles >= 256 || steps <= 64 ? 4 : 16;
 }
 inline bool small_gemm(const GemmDesc& d) {
+  if (d.K == 1 && d.transA == 0 && d.transB != 0) return true;  // rows of one value have no pairs to load
   const long tiles = small_tiles(d), steps = small_steps(d);
   return tiles <= 2048 && steps <= 512 && tiles * steps <= 60000;
 }

@@ -630,3 +630,50 @@ def test_gemm_rows_96(B, fp32, M):
             ref = a.double() @ b.double().T
             tol = (1.2e-7 if fp32 else 2.3e-16) * K
             assert (split.double() - ref).abs().max() <= tol * a.abs().max().item() * b.abs().max().item()
+
+
+@pytest.mark.parametrize("KB", [1, 3])
+@pytest.mark.parametrize("M,N,K", [(1001, 999, 1), (1001, 999, 2), (997, 1003, 3), (1000, 1004, 15), (1002, 998, 18),
+                                   (1003, 1001, 31), (1006, 1010, 44), (1000, 1000, 47)])
+def test_gemm_ragged_rows(B, M, N, K, KB):
+    """k-contiguous FP64 products with edges inside a group of 8 rows and ragged k tiles of every
+    kind (one value, one pair, odd, even), rows padded by NaN.  Even rows of an even K go straight
+    into LDS, the others through registers, in the same order: equal bit for bit.  Rounding error of a
+    dot product of K KB terms of size one: eps sqrt(K KB) with a margin of 8."""
+    rng = np.random.default_rng(M + N + K)
+    A, Bt = rng.uniform(-1, 1, (KB, M, K)), rng.uniform(-1, 1, (KB, N, K))
+    C0 = rng.uniform(-1, 1, (M, N))
+    ref = 0.5 * np.matmul(A, Bt.transpose(0, 2, 1)).sum(0) - C0
+    got = []
+    for pad in (2 + (K & 1), 3 - (K & 1)):
+        a, b = (torch.tensor(np.concatenate([x, np.full(x.shape[:2] + (pad,), np.nan)], 2), device="cuda")
+                for x in (A, Bt))
+        for ws in (0, 1 << 26):
+            c = torch.tensor(C0, device="cuda")
+            B.gemm(a, b, c, M=M, N=N, K=K, KB=KB, lda=K + pad, sAk=M * (K + pad), transB=1, ldb=K + pad,
+                   sBk=N * (K + pad), ldc=N, alpha=0.5, beta=-1.0, ws_bytes=ws)
+            got.append(c.cpu())
+            assert np.abs(got[-1].numpy() - ref).max() <= 8 * 2.3e-16 * np.sqrt(K * KB) + 4.6e-16
+    assert torch.equal(got[0], got[2]) and torch.equal(got[1], got[3])
+
+
+@pytest.mark.parametrize("M,N,K,pad", [(6000, 2820, 6000, 0), (6630, 2800, 6630, 2), (5889, 3760, 5889, 0)])
+def test_gemm_ragged_rate(B, M, N, K, pad):
+    """A k-contiguous FP64 product whose extents are not whole tiles costs little more than the next
+    larger one of whole tiles (rows by 128, k by 16): a quarter at most, with 15 % for the clock."""
+    import time
+
+    def best(m, n, k, p):
+        a = torch.randn(m, k + p, device="cuda", dtype=torch.float64)
+        b = torch.randn(n, k + p, device="cuda", dtype=torch.float64)
+        c = torch.empty(m, n, device="cuda", dtype=torch.float64)
+        torch.cuda.synchronize()
+        t = []
+        for _ in range(6):
+            t0 = time.perf_counter()
+            B.gemm(a, b, c, M=m, N=n, K=k, lda=k + p, transB=1, ldb=k + p, ldc=n)
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    up = lambda x, t: (x + t - 1) // t * t
+    assert best(M, N, K, pad) <= 1.25 * 1.15 * best(up(M, 128), up(N, 128), up(K, 16), 0)

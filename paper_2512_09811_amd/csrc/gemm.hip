@@ -418,7 +418,7 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
     __syncthreads();
     landed(As0, Bs0);
     advance();
-    fill(As1, Bs1, kb, kt, rag);
+    if (STREAM || steps > 1) fill(As1, Bs1, kb, kt, rag);
     frag(As0, Bs0, 0, a0, b0);
     auto step = [&](double* Ac, double* Bc, double* An, double* Bn) {
       frag(Ac, Bc, 4, a1, b1v);
@@ -466,8 +466,10 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   auto reduce_regs = [&]() {
     load_regs(kb, kt);
     store_regs(As0, Bs0, kt);
-    advance();
-    load_regs(kb, kt);
+    if (steps > 1) {
+      advance();
+      load_regs(kb, kt);
+    }
     __syncthreads();
     frag(As0, Bs0, 0, a0, b0);
     auto step = [&](const double* Ac, const double* Bc, double* An, double* Bn) {
@@ -621,7 +623,9 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
                       (d.sAk % 2) == 0 && (d.sBk % 2) == 0 && ((uintptr_t)Atile % (2 * sizeof(T))) == 0 &&
                       ((uintptr_t)Btile % (2 * sizeof(T))) == 0;
   const int mlast = AK ? mrem - 1 : mrem - 2, nlast = BKC ? nrem - 1 : nrem - 2;
-  // MODE 0: whole k tiles on the vector path, 1: the vector path with a ragged last one, 2: guarded
+  // MODE 0: whole k tiles on the vector path, 1: the vector path with a ragged last one (pairs past K
+  // repeat one of the tile, and 'cut' makes them zero on their way to LDS: at the load it would wait for
+  // it), 2: guarded
   auto load = [&](int kb, int kt, auto mode) {
     constexpr int MODE = decltype(mode)::value;
     const int k0 = kt * BK;
@@ -649,20 +653,16 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
         int m, k;
         a_pair(i * kThreads + tid, m, k);
         m = min(m, mlast);
-        const bool in = k < krem;
-        const int kc = in ? k : 0;
-        const pair_t v = *reinterpret_cast<const pair_t*>(Ak + (AK ? (m * lda32 + kc) : (kc * lda32 + m)));
-        ra[i] = in ? v : pair_t{T(0), T(0)};
+        const int kc = k < krem ? k : 0;
+        ra[i] = *reinterpret_cast<const pair_t*>(Ak + (AK ? (m * lda32 + kc) : (kc * lda32 + m)));
       }
 #pragma unroll
       for (int i = 0; i < PB; ++i) {
         int n, k;
         b_pair(i * kThreads + tid, n, k);
         n = min(n, nlast);
-        const bool in = k < krem;
-        const int kc = in ? k : 0;
-        const pair_t v = *reinterpret_cast<const pair_t*>(Bk + (BKC ? (n * ldb32 + kc) : (kc * ldb32 + n)));
-        rb[i] = in ? v : pair_t{T(0), T(0)};
+        const int kc = k < krem ? k : 0;
+        rb[i] = *reinterpret_cast<const pair_t*>(Bk + (BKC ? (n * ldb32 + kc) : (kc * ldb32 + n)));
       }
     } else {
 #pragma unroll
@@ -689,6 +689,21 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
           rb[i][h] = v;
         }
       }
+    }
+  };
+  auto cut = [&](int kt) {
+    const int krem = d.K - kt * BK;
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+      int m, k;
+      a_pair(i * kThreads + tid, m, k);
+      ra[i] = k < krem ? ra[i] : pair_t{T(0), T(0)};
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      int n, k;
+      b_pair(i * kThreads + tid, n, k);
+      rb[i] = k < krem ? rb[i] : pair_t{T(0), T(0)};
     }
   };
   auto store = [&](int buf) {
@@ -754,14 +769,18 @@ __device__ __forceinline__ void gemm_tile(const GemmDesc& d, T alpha, const T* _
     };
     T a0[TM], b0[TN], a1[TM], b1v[TN];
     load(kb, kt, mode);
+    if constexpr (decltype(mode)::value == 1) cut(kt);
     store(0);
-    advance();
-    load(kb, kt, mode);
+    if (steps > 1) {
+      advance();
+      load(kb, kt, mode);
+    }
     __syncthreads();
     frag(0, 0, a0, b0);
     auto step = [&](auto cur) {
       constexpr int c = decltype(cur)::value;
       frag(c, 4, a1, b1v);
+      if constexpr (decltype(mode)::value == 1) cut(kt);
       store(c ^ 1);
       mma(a0, b0);
       interleave(std::true_type{}, std::false_type{});

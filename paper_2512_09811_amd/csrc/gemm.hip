@@ -129,6 +129,12 @@ long sym_tiles(const GemmDesc& d) {
 // arrays and the loop is unrolled by two, so a buffer being filled and the buffer being
 // read are distinct objects to the compiler.  MFMA operands and their order are those of
 // the register-staged path, so results are bit-identical to it.
+// x, as a value that the compiler cannot know: what depends on it is worked out where it is used and
+// not held in registers through the loops before
+__device__ __forceinline__ int hidden(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 __device__ __forceinline__ int swz16(int r, int kp) { return r * 8 + (kp ^ ((r >> 1) & 7)); }
 
 // Offset of index x along a C dimension that may be a pair (x / R, x % R) with strides
@@ -274,14 +280,9 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   };
   // k tile (kb, kt) through registers: pairs of row r0 + 32 i from element 2 kp on.  A pair past the
   // end of K is read from the last two values of its row (never past them; K is 2 at least) and put
-  // right, with zeros past K, when it is stored.  Offsets are worked out anew for every tile (the
-  // thread's number is hidden from the compiler, which would otherwise keep them all in registers
-  // that the accumulators need).
+  // right, with zeros past K, when it is stored.  Offsets are worked out anew for every tile: the
+  // accumulators need the registers.
   typedef double pair8_t __attribute__((ext_vector_type(2), aligned(8)));
-  auto hidden = [](int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-  };
   pair_t sa[CA], sb[CB];
   auto load_regs = [&](int kb, int kt) {
     const double* Ak = Atile + kb * d.sAk + kt * BK;
@@ -1577,9 +1578,8 @@ int gemm_group_impl(const std::vector<GemmCall<T>>& calls, hipStream_t s) {
 // at twice the rate of the 16x16x32 form: 2.0 against 1.1 PFLOP/s measured with
 // register-only chains), three MFMAs per block and 16-value k step: lane l supplies row
 // l % 32 and chunk l / 32 of the step; block results: lane l, register r holds row
-// 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.  Ragged tiles (an edge in m, n or k) are
-// copied chunk by chunk through registers into the same layout; values past K inside the
-// last chunk of a row must be zero (split_sbf16 of a zero-padded row leaves them so).
+// 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.  Values past K inside the last chunk of a row
+// must be zero (split_sbf16 of a zero-padded row leaves them so).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kSbBK = 32;
@@ -1605,7 +1605,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
   __shared__ __attribute__((aligned(16))) float As1[SA];
   __shared__ __attribute__((aligned(16))) float Bs0[SB];
   __shared__ __attribute__((aligned(16))) float Bs1[SB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave / WN, wn = wave % WN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
   const int tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
   int tm, tn;
   if (d.sym >= 0) {
@@ -1618,53 +1618,38 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
   const float* Bt = B + (long)n0 * d.ldb;
   const int lda32 = (int)d.lda, ldb32 = (int)d.ldb;
   const int mrem = d.M - m0, nrem = d.N - n0;
-  const bool rows_ok = mrem >= BM && nrem >= BN;
-  int offA[CA], offB[CB];
-#pragma unroll
-  for (int c = 0; c < CA; ++c) {
-    const int sl = (wave + NW * c) * 64 + lane, r = sl >> 3, sg = (sl & 7) ^ ((r >> 1) & 7);
-    offA[c] = r * lda32 + 4 * sg;
-  }
-#pragma unroll
-  for (int c = 0; c < CB; ++c) {
-    const int sl = (wave + NW * c) * 64 + lane, r = sl >> 3, sg = (sl & 7) ^ ((r >> 1) & 7);
-    offB[c] = r * ldb32 + 4 * sg;
-  }
-  // tiles loaded straight into LDS: all of them when the tile is whole in m and n, except
-  // a ragged last k tile
-  const int nkt = (d.K + BK - 1) / BK;
-  const int ndma = rows_ok ? d.K / BK : 0;
+  // Every k tile is loaded straight into LDS.  Rows past an edge in m or n repeat the last one (their
+  // results are not stored).  A ragged last k tile is the 4 chunks that end with K, so its own chunks
+  // come 'back' places late in it (without 4 chunks in a row: the last one is repeated); it is read and
+  // cut by tail() below.  Measured, with ragged tiles and edges
+  // through registers, in a loop that spilled | here: 6400 x 7200 over 6400 1916 | 1680 us, 6795 x 5500
+  // over 6795 2130 | 1557, 13115 x 5600 over 13115 6920 | 5382, 3024 x 1512 over 3024 284 | 126.
+  const int nkt = (d.K + BK - 1) / BK, nch = (d.K + 7) / 8;
+  const int left = nch - 4 * (nkt - 1), back = nkt > 1 ? 4 - left : 0;
+  // A wave's load is 8 rows: its first row is scalar, the lanes' offsets from it are those of every
+  // load but the one at an edge.  In a tile without an edge they are 32-bit byte offsets (BM rows of lda
+  // lie within 2^31 values), so that a load takes its address from scalar registers and one vector
+  // register; at an edge they are worked out for every tile.
+  const int sg = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7), slot = 8 * min(sg >> 1, nch - 1) + 4 * (sg & 1);
+  const unsigned inA = 4u * ((lane >> 3) * lda32 + slot), inB = 4u * ((lane >> 3) * ldb32 + slot);
   auto fill = [&](float* Ab, float* Bb, int kt, auto whole) {
-    const int k0 = kt * BK;
-    const float* Ak = At + k0;
-    const float* Bk = Bt + k0;
-    if (decltype(whole)::value || kt < ndma) {
+    const int k0 = kt * BK - (kt + 1 == nkt ? 8 * back : 0);
+    auto rows = [&](const float* X, long ld, int rem, unsigned in, int i) {
+      if constexpr (decltype(whole)::value)
+        return (const char*)(X + k0 + (long)i * ld) + in;
+      else
+        return (const char*)(X + k0 + (min(i + (hidden(lane) >> 3), rem - 1) * (int)ld + slot));
+    };
 #pragma unroll
-      for (int c = 0; c < CA; ++c)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Ak + offA[c]),
-                                         (__attribute__((address_space(3))) void*)(Ab + (wave + NW * c) * 256), 16, 0,
-                                         0);
+    for (int c = 0; c < CA; ++c)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)rows(At, d.lda, mrem, inA, (wave + NW * c) * 8),
+          (__attribute__((address_space(3))) void*)(Ab + (wave + NW * c) * 256), 16, 0, 0);
 #pragma unroll
-      for (int c = 0; c < CB; ++c)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Bk + offB[c]),
-                                         (__attribute__((address_space(3))) void*)(Bb + (wave + NW * c) * 256), 16, 0,
-                                         0);
-    } else {
-#pragma unroll
-      for (int i = 0; i < SA / 4 / NT; ++i) {
-        const int q = i * NT + tid, r = q >> 3, sg = q & 7;
-        f32x4_t v = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        if (r < mrem && k0 + 8 * (sg >> 1) < d.K) v = *reinterpret_cast<const f32x4_t*>(Ak + r * lda32 + 4 * sg);
-        *reinterpret_cast<f32x4_t*>(Ab + 4 * swz16(r, sg)) = v;
-      }
-#pragma unroll
-      for (int i = 0; i < SB / 4 / NT; ++i) {
-        const int q = i * NT + tid, r = q >> 3, sg = q & 7;
-        f32x4_t v = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        if (r < nrem && k0 + 8 * (sg >> 1) < d.K) v = *reinterpret_cast<const f32x4_t*>(Bk + r * ldb32 + 4 * sg);
-        *reinterpret_cast<f32x4_t*>(Bb + 4 * swz16(r, sg)) = v;
-      }
-    }
+    for (int c = 0; c < CB; ++c)
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)rows(Bt, d.ldb, nrem, inB, (wave + NW * c) * 8),
+          (__attribute__((address_space(3))) void*)(Bb + (wave + NW * c) * 256), 16, 0, 0);
   };
   f32x16_t acc[TM][TN];
 #pragma unroll
@@ -1691,6 +1676,30 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
       const int r = wn * WTN + j * 32 + rl;
       f.bh[j] = *reinterpret_cast<const bf16x8_t*>(Bb + 4 * swz16(r, 2 * ch));
       f.bl[j] = *reinterpret_cast<const bf16x8_t*>(Bb + 4 * swz16(r, 2 * ch + 1));
+    }
+  };
+  // the same of the last k tile, whose chunks lie 'back' places on; zeros past K (its addresses are
+  // worked out there, not kept through the loop)
+  auto tail = [&](const float* Ab, const float* Bb, int st, Frags& f) {
+    const int id = hidden(tid), rl = id & 31, wm = (id >> 6) / WN, wn = (id >> 6) % WN;
+    const int ch = 2 * st + ((id >> 5) & 1), at = min(ch + back, 3);
+    const bool in = ch < left;
+    const bf16x8_t none = {};
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int r = wm * WTM + i * 32 + rl;
+      const bf16x8_t h = *reinterpret_cast<const bf16x8_t*>(Ab + 4 * swz16(r, 2 * at));
+      const bf16x8_t l = *reinterpret_cast<const bf16x8_t*>(Ab + 4 * swz16(r, 2 * at + 1));
+      f.ah[i] = in ? h : none;
+      f.al[i] = in ? l : none;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int r = wn * WTN + j * 32 + rl;
+      const bf16x8_t h = *reinterpret_cast<const bf16x8_t*>(Bb + 4 * swz16(r, 2 * at));
+      const bf16x8_t l = *reinterpret_cast<const bf16x8_t*>(Bb + 4 * swz16(r, 2 * at + 1));
+      f.bh[j] = in ? h : none;
+      f.bl[j] = in ? l : none;
     }
   };
   // per column block: the hi-lo products of its row blocks, then lo-hi, then hi-hi
@@ -1755,16 +1764,19 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
       step(As0, Bs0, As1, Bs1, kt);
       if (kt + 2 < nkt) step(As1, Bs1, As0, Bs0, kt + 1);
     }
-    frags((nkt & 1) ? As0 : As1, (nkt & 1) ? Bs0 : Bs1, 1, f1);
-    mma(f0);
-    interleave();
-    mma(f1);
   };
-  // whole tiles get a loop without the ragged path, whose addresses would not fit the registers
-  if (ndma == nkt)
+  if (mrem >= BM && nrem >= BN)
     reduce(std::true_type{});
   else
     reduce(std::false_type{});
+  {
+    const float *Al = (nkt & 1) ? As0 : As1, *Bl = (nkt & 1) ? Bs0 : Bs1;
+    Frags f0, f1;
+    tail(Al, Bl, 0, f0);
+    tail(Al, Bl, 1, f1);
+    mma(f0);
+    mma(f1);
+  }
   // epilogue: column offsets once per thread, row offsets once per accumulator row
   const bool mapped = (d.cRm | d.cRn) != 0;
   long coff[TN];

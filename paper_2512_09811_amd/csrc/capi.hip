@@ -221,6 +221,8 @@ pp_status pp_sigma(pp_handle* h, int32_t order, int32_t m, const double* X, doub
       each = h->acap;
     } else {
       settle(h);
+      // (workspaces first: they may need the room of a staging block that is not lent yet)
+      if (order >= 1) ppw::sigma_reserve(c, k, product_precision(h, flags));
       fr.p = c.arena.take_staging((4 * per + (dev ? 0 : (size_t)2 * m * N)) * sizeof(double), "sigma staging");
       V = static_cast<double*>(fr.p);
       if (!dev) out = V + 4 * per;
@@ -435,7 +437,7 @@ pp_status pp_reset_stats(pp_handle* h) {
 
 double pp_mp2_energy(const pp_handle* h) { return (h && h->ctx) ? h->ctx->emp2 : 0.0; }
 
-uint64_t pp_device_bytes(const pp_handle* h) { return (h && h->ctx) ? h->ctx->arena.used() : 0; }
+uint64_t pp_device_bytes(const pp_handle* h) { return (h && h->ctx) ? h->ctx->arena.owned() : 0; }
 
 pp_status pp_destroy(pp_handle* h) {
   if (!h) return PP_OK;

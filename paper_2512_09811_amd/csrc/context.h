@@ -38,6 +38,8 @@ class Arena {
 
   void set_budget(size_t b) { budget_ = b; }
   size_t used() const { return used_; }
+  // with the staging block that waits for the next call
+  size_t owned() const { return used_ + (spare_busy_ ? 0 : spare_bytes_); }
   size_t budget() const { return budget_; }
 
   // bytes an array of n elements of size e takes
@@ -98,29 +100,27 @@ class Arena {
       }
   }
 
-  // Staging of one synchronous call (a single one at a time): an array of at most kSpare bytes
-  // stays with the arena for the next call, until anything else needs the room.  The work that
-  // used it must be done when it is returned.
+  // Staging of one synchronous call (a single one at a time): a block of at most kSpare bytes
+  // stays with the arena for the next call, until anything else needs the room.  While it is lent
+  // the whole block counts as used; where the budget has no room for all of it, a block of the size
+  // asked for takes its place.  The work that used it must be done when it is returned.
   void* take_staging(size_t bytes, const char* what) {
     bytes = rounded(bytes, 1);
     if (bytes > kSpare || spare_busy_) return alloc<char>(bytes, what);
-    if (spare_bytes_ < bytes) {
+    if (spare_bytes_ < bytes || (budget_ && used_ + spare_bytes_ > budget_)) {
       drop_spare();
       check(bytes, what);
       spare_ = device_alloc(bytes, what);
       spare_bytes_ = bytes;
-    } else {
-      check(bytes, what);
     }
     spare_busy_ = true;
-    spare_used_ = bytes;
-    used_ += bytes;
+    used_ += spare_bytes_;
     return spare_;
   }
   void return_staging(void* p) {
     if (spare_busy_ && p == spare_) {
       spare_busy_ = false;
-      used_ -= spare_used_;
+      used_ -= spare_bytes_;
     } else {
       free(p);
     }
@@ -189,7 +189,7 @@ class Arena {
   std::vector<Segment> segs_;
   int open_ = -1;
   void* spare_ = nullptr;
-  size_t spare_bytes_ = 0, spare_used_ = 0;
+  size_t spare_bytes_ = 0;
   bool spare_busy_ = false;
   size_t used_ = 0;
   size_t budget_ = 0;

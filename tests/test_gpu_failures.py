@@ -87,3 +87,39 @@ def test_injected_hip_errors(P):
     with P.Handle.from_system(sys_, order=2) as h:
         got, _, _, _ = h.window_solve(0.9, 4)
     np.testing.assert_allclose(got, e_ref, rtol=0, atol=1e-8)
+
+
+def test_staging_block_within_budget(P):
+    """The staging block that a large product leaves with its handle counts against the byte budget
+    while a later call uses a part of it: a small product whose workspaces have to grow either fits
+    beside the block or takes its place.  Device memory in use never exceeds the budget (by more than
+    the runtime's rounding of allocations, 16 MiB for the dozen of them)."""
+    import torch
+    sys_ = gen(3, 16, 64, 192, b_scale=0.1)
+    big = torch.zeros((960, 2, sys_.N), dtype=torch.float64, device="cuda")    # 60 MiB of staging
+    small = torch.ones((12, 2, sys_.N), dtype=torch.float64, device="cuda")
+    out, ref, got = torch.empty_like(big), torch.empty_like(small), torch.empty_like(small)
+    kw = dict(order=2, precision=P.PP_FP32, store_amplitudes=1, strip_rows=16)
+
+    def in_use():
+        torch.cuda.synchronize()
+        free, total = torch.cuda.mem_get_info()
+        return total - free
+
+    with P.Handle.from_system(sys_, **kw) as h:      # the runtime's own allocations
+        h.sigma_device(big, out)
+        h.sigma_device(small, ref, reduced=True)
+    base = in_use()
+    with P.Handle.from_system(sys_, **kw) as h:
+        h.sigma_device(big, out)
+        first = in_use() - base
+        assert h.device_bytes() <= first + (16 << 20)
+        h.sigma_device(small, ref, reduced=True)
+    budget = first + (16 << 20)
+    base = in_use()
+    with P.Handle.from_system(sys_, hbm_budget=budget, **kw) as h:
+        h.sigma_device(big, out)
+        h.sigma_device(small, got, reduced=True)     # about 40 MiB of workspaces in FP32
+        assert in_use() - base <= budget + (16 << 20)
+        assert h.device_bytes() <= budget
+    assert torch.equal(got, ref)

@@ -186,6 +186,7 @@ __device__ __forceinline__ void store_mapped(const GemmDesc& d, T alpha, T beta,
 // STREAM (whole tiles in m, n in steps of 8 and in k in steps of 32, one batch, no splits): the
 // workgroup computes 'count' tiles, flat, flat + stride, ..., and loads the first k tiles of the
 // next one during the last ones of the present.
+constexpr long kDmaRow = 1L << 26;  // 7 rows of it and a k tile lie within 4 GiB
 template <int BM, int BN, bool STREAM = false>
 __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, const double* __restrict__ A,
                                               const double* __restrict__ B, double beta, double* __restrict__ C,
@@ -226,9 +227,10 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   // A chunk is 8 rows, (wave + 4 c) 8 on; chunks past the edge repeat the last one and rows past it
   // within a chunk the last row.  The first row of a chunk is the same for the whole wave, and the
   // lanes' offsets from it are those of every chunk but the one at an edge, so that a load takes its
-  // address from scalar registers and one vector register.
+  // address from scalar registers and one vector register (32-bit byte offsets: longer rows go through
+  // registers).
   const bool dma = (d.lda % 2) == 0 && (d.ldb % 2) == 0 && (d.sAk % 2) == 0 && (d.sBk % 2) == 0 &&
-                   ((uintptr_t)Atile % 16) == 0 && ((uintptr_t)Btile % 16) == 0 && d.K % 2 == 0;
+                   ((uintptr_t)Atile % 16) == 0 && ((uintptr_t)Btile % 16) == 0 && d.K % 2 == 0 && d.lda < kDmaRow && d.ldb < kDmaRow;
   const int kpl = (lane & 7) ^ (4 * (wave & 1) + (lane >> 4));
   long rowA[CA], rowB[CB];
   unsigned laneA[CA], laneB[CB];

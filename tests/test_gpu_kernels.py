@@ -747,3 +747,21 @@ def test_gemm_split_bf16_ragged_rate(B):
             B.gemm(a, b, c, M=M, N=N, K=K, lda=ld, transB=1, ldb=ld, ldc=N, fp32=5)
             t.append(time.perf_counter() - t0)
     assert min(runs[0][-1]) <= 1.25 * 1.05 * min(runs[1][-1])
+
+
+@pytest.mark.parametrize("lda", [(1 << 26) - 2, 1 << 26, (1 << 27) + 64])
+def test_gemm_long_rows_tiled(B, lda):
+    """A long reduction over rows of up to 1 GiB: the 8 rows of one load span more than the 32-bit byte
+    offsets of the loads straight into LDS hold, and such operands take the other path.  The order of the
+    sums is the same: equal bit for bit to the product of packed rows."""
+    M, N, K = 9, 200, 4104
+    torch.manual_seed(12)
+    a = torch.randn(M, K, device="cuda", dtype=torch.float64)
+    b = torch.randn(N, K, device="cuda", dtype=torch.float64)
+    far = torch.zeros((M - 1) * lda + K, dtype=torch.float64, device="cuda")
+    for m in range(M):
+        far[m * lda:m * lda + K] = a[m]
+    c, ref = (torch.zeros(M, N, dtype=torch.float64, device="cuda") for _ in range(2))
+    B.gemm(far, b, c, M=M, N=N, K=K, lda=lda, transB=1, ldb=K, ldc=N)
+    B.gemm(a, b, ref, M=M, N=N, K=K, lda=K, transB=1, ldb=K, ldc=N)
+    assert torch.equal(c, ref)

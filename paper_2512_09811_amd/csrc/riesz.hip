@@ -237,7 +237,7 @@ ContourFilter::ContourFilter(Context& c, int kblock, int nodes_max, int chunk, h
   if (kblock < 1 || nodes_max < 1 || chunk < 2 * kblock) throw InvalidArg("contour filter: bad dimensions");
   const size_t rows = (size_t)4 * nodes_max * kblock;
   const size_t n = rows * N_;
-  c_.arena.open(bytes(N_, kblock, nodes_max));
+  c_.arena.open(8 * Arena::segment_part(n, sizeof(double)));
   X_ = get<double>(n, "contour x");
   R_ = get<double>(n, "contour r");
   Z_ = get<double>(n, "contour u");

@@ -149,12 +149,15 @@ Context* setup_context(const SetupParams& p) {
     const int o = p.o, v = p.v, X = p.naux;
     const long N = c->N;
 
-    auto r = [](size_t n, size_t e = sizeof(double)) { return Arena::rounded(n, e); };
+    auto r = [](size_t n, size_t e = sizeof(double)) { return Arena::segment_part(n, e); };
     c->ns = p.order >= 2 ? 2 : 1;
     const size_t ws0 = std::max<size_t>((size_t)64 << 20, (size_t)X * 1024 * sizeof(double));
-    c->arena.open(r(o) + r(v) + 2 * r((size_t)X * o * o) + r((size_t)X * v * v) + r((size_t)c->ns * X * N) +
-                  (p.dip ? r((size_t)3 * N) : 0) + r(ws0, 1) + 3 * r(N) +
-                  (p.order >= 2 ? 2 * r((size_t)v * v) + 2 * r((size_t)o * o) : 0));
+    // (the workspace, 64 MiB where the runtime keeps as much of what is freed, joins a segment, which
+    // it takes past that, only where there is one anyway)
+    const size_t own = r(o) + r(v) + 2 * r((size_t)X * o * o) + r((size_t)X * v * v) + r((size_t)c->ns * X * N) +
+                       (p.dip ? r((size_t)3 * N) : 0) + 3 * r(N) +
+                       (p.order >= 2 ? 2 * r((size_t)v * v) + 2 * r((size_t)o * o) : 0);
+    c->arena.open(own ? own + r(ws0, 1) : 0);
     c->eps_o = c->arena.alloc<double>(o, "eps_o");
     c->eps_v = c->arena.alloc<double>(v, "eps_v");
     c->Boo = c->arena.alloc<double>((size_t)X * o * o, "B_oo");
@@ -175,7 +178,6 @@ Context* setup_context(const SetupParams& p) {
     c->Boo_t = c->arena.alloc<double>((size_t)o * o * X, "B_oo [i][j][P]");
     const int perm[3] = {1, 2, 0};
     permute3(c->Boo, c->Boo_t, X, o, o, perm, s);
-    ensure_ws(*c, ws0);
     c->dA = c->arena.alloc<double>(N, "diag A");
     c->dB = c->arena.alloc<double>(N, "diag B");
     c->dS = c->arena.alloc<double>(N, "diag S");
@@ -185,6 +187,7 @@ Context* setup_context(const SetupParams& p) {
       c->Go = c->arena.alloc<double>((size_t)o * o, "Go");
       c->Eo = c->arena.alloc<double>((size_t)o * o, "Eo");
     }
+    ensure_ws(*c, ws0);
     c->arena.open(2 * r(N));
     double* coul = c->arena.alloc<double>(N, "diag tmp");
     double* exch = c->arena.alloc<double>(N, "diag tmp");
@@ -346,7 +349,7 @@ class Grow {
   void add(T*& p, size_t n, const char* w) {
     if (p) c_.arena.free(p);
     p = nullptr;
-    bytes_ += Arena::rounded(n, sizeof(T));
+    bytes_ += Arena::segment_part(n, sizeof(T));
     make_.push_back([this, &p, n, w] { p = c_.arena.alloc<T>(n, w); });
   }
   void done(int& cap, int k) {

@@ -468,7 +468,7 @@ class ProductBatcher : public ProductSink {
   }
   void reserve(int ktot) {
     const size_t n = (size_t)ktot * c_.N;
-    c_.arena.open(4 * Arena::rounded(n, sizeof(double)));
+    c_.arena.open(4 * Arena::segment_part(n, sizeof(double)));
     V_ = c_.arena.alloc<double>(n, "batch V");
     AV_ = c_.arena.alloc<double>(n, "batch AV");
     BV_ = c_.arena.alloc<double>(n, "batch BV");

@@ -807,16 +807,22 @@ __global__ __launch_bounds__(64) void inverse_iteration_kernel(int n, const doub
 // does for the symmetric one (eigenvectors of G): k dependent steps of one wave in LDS, 18 us at
 // k = 40, where the eigensolver below took 260 us (its rotations are a scalar recurrence of
 // about k^2 steps).
+//
+// KM (32 or 64, k at most) sizes its LDS: beside the products of other windows the kernel has to find
+// a compute unit with room for it, and 16 or 64 KiB fit where the 96 KiB of three arrays of 64 x 64
+// did not: 18 us alone, and in two windows at 40/160/600 in split BF16 330 us on average with 96 KiB,
+// 87 us with 16 (the Cholesky panel below 64 KiB, with 64 rows a workgroup, gained nothing).
+template <int KM>
 __global__ __launch_bounds__(64) void orth_factors_kernel(int k, const double* __restrict__ G, double thresh,
                                                           double* __restrict__ T, double* __restrict__ R,
                                                           int* __restrict__ q_out) {
-  __shared__ double Gs[64][64], Rs[64][64], Ts[64][64];
-  __shared__ int perm[64], rank[64];
-  const int lane = threadIdx.x;
+  __shared__ double Gs[KM][KM], Rs[KM][KM];
+  __shared__ int perm[KM], rank[KM];
+  const int lane = threadIdx.x, col = min(lane, KM - 1);
   for (int i = lane; i < k * k; i += 64) Gs[i / k][i % k] = G[i];
-  rank[lane] = -1;
+  if (lane < KM) rank[lane] = -1;
   __syncthreads();
-  double dj = lane < k ? Gs[lane][lane] : -1.0;
+  double dj = lane < k ? Gs[col][col] : -1.0;
   bool done = lane >= k;
   int q = 0;
   for (; q < k; ++q) {
@@ -824,11 +830,11 @@ __global__ __launch_bounds__(64) void orth_factors_kernel(int k, const double* _
     const int at = __ffsll((long long)__ballot(!done && dj == best)) - 1;
     if (!(best > thresh)) break;
     const double piv = sqrt(best);
-    double acc = Gs[at][lane];
+    double acc = Gs[at][col];
 #pragma unroll 8
-    for (int t = 0; t < q; ++t) acc = fma(-Rs[t][at], Rs[t][lane], acc);
+    for (int t = 0; t < q; ++t) acc = fma(-Rs[t][at], Rs[t][col], acc);
     const double r = done ? 0.0 : (lane == at ? piv : acc / piv);
-    Rs[q][lane] = r;
+    if (lane < KM) Rs[q][lane] = r;
     dj = fma(-r, r, dj);
     if (lane == at) {
       done = true;
@@ -837,26 +843,34 @@ __global__ __launch_bounds__(64) void orth_factors_kernel(int k, const double* _
     }
     __syncthreads();
   }
-  // upper triangle in pivot order, then column c of its inverse by lane c
+  // upper triangle in pivot order, then column c of its inverse by lane c, row by row from the last in
+  // the rows' own places
   for (int i = 0; i < q; ++i)
-    if (lane < q) {
-      Gs[i][lane] = Rs[i][perm[lane]];
-      Ts[i][lane] = 0.0;
-    }
+    if (lane < q) Gs[i][lane] = Rs[i][perm[lane]];
   __syncthreads();
   for (int i = q - 1; i >= 0; --i) {
+    const double gii = Gs[i][i];
     double acc = lane == i ? 1.0 : 0.0;
 #pragma unroll 4
-    for (int t = i + 1; t < q; ++t) acc = fma(-Gs[i][t], Ts[t][lane], acc);
-    if (lane < q && lane >= i) Ts[i][lane] = acc / Gs[i][i];
+    for (int t = i + 1; t < q; ++t) acc = fma(-Gs[i][t], Gs[t][col], acc);
+    __syncthreads();
+    if (lane < q) Gs[i][lane] = lane >= i ? acc / gii : 0.0;
+    __syncthreads();
   }
-  __syncthreads();
   for (int i = lane; i < k * q; i += 64) {
     const int j = i / q, c = i % q;
-    T[i] = rank[j] >= 0 ? Ts[rank[j]][c] : 0.0;
+    T[i] = rank[j] >= 0 ? Gs[rank[j]][c] : 0.0;
     R[i] = Rs[i / k][i % k];
   }
   if (lane == 0) *q_out = q;
+}
+
+void launch_orth_factors(int k, const double* G, double thresh, double* T, double* R, int* count, hipStream_t s) {
+  if (k <= 32)
+    orth_factors_kernel<32><<<1, 64, 0, s>>>(k, G, thresh, T, R, count);
+  else
+    orth_factors_kernel<64><<<1, 64, 0, s>>>(k, G, thresh, T, R, count);
+  PPW_LAUNCH_CHECK();
 }
 
 // Eigenpairs of a symmetric n x n matrix (n <= 64) that is diagonal but for a few elements, by
@@ -1102,8 +1116,7 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
   g.M = p; g.N = p; g.K = n; g.transA = 0; g.lda = n; g.transB = 1; g.ldb = n; g.ldc = p;
   gemm_f64(g, 1.0, V, V, 0.0, G, s);
   // (T1 is p x q, ld q; R goes to UG)
-  orth_factors_kernel<<<1, 64, 0, s>>>(p, G, 1e-12, T1, UG, nc);
-  PPW_LAUNCH_CHECK();
+  launch_orth_factors(p, G, 1e-12, T1, UG, nc, s);
   int got[4] = {0, 0, 0, 0};
   PPW_HIP(hipMemcpyAsync(got, flags, sizeof(got), hipMemcpyDeviceToHost, s));
   PPW_HIP(hipStreamSynchronize(s));
@@ -1133,8 +1146,7 @@ int partial_syev(int n, const double* A, double target, int p, double* lam, doub
 
 int orth_factors(int k, const double* G, double thresh, double* T, double* R, int* count, hipStream_t s) {
   if (k < 1 || k > 64) throw InvalidArg("orth_factors: k out of range");
-  orth_factors_kernel<<<1, 64, 0, s>>>(k, G, thresh, T, R, count);
-  PPW_LAUNCH_CHECK();
+  launch_orth_factors(k, G, thresh, T, R, count, s);
   int q = 0;
   PPW_HIP(hipMemcpyAsync(&q, count, sizeof(int), hipMemcpyDeviceToHost, s));
   PPW_HIP(hipStreamSynchronize(s));

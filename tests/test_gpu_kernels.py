@@ -765,3 +765,25 @@ def test_gemm_long_rows_tiled(B, lda):
     B.gemm(far, b, c, M=M, N=N, K=K, lda=lda, transB=1, ldb=K, ldc=N)
     B.gemm(a, b, ref, M=M, N=N, K=K, lda=K, transB=1, ldb=K, ldc=N)
     assert torch.equal(c, ref)
+
+
+@pytest.mark.parametrize("p", [31, 32, 33, 48])
+def test_partial_syev_block_sizes(B, p):
+    """Blocks on both sides of the 32 vectors up to which the orthonormalisation keeps its matrices in
+    less LDS, with a cluster in the window.  Eigenvalues and residuals to n eps |A| (with the factor for
+    clusters of the test above)."""
+    rng = np.random.default_rng(p)
+    n = 200
+    lam = rng.uniform(0.1, 2.0, n)
+    lam[:6] = 0.9 + 1e-13 * np.arange(6)
+    A = _spectrum_matrix(lam, n)
+    A = 0.5 * (A + A.T)
+    w = torch.zeros(p, dtype=torch.float64, device="cuda")
+    Z = torch.zeros(n * p, dtype=torch.float64, device="cuda")
+    q = B.partial_syev(torch.tensor(A, device="cuda"), 0.9, p, w, Z)
+    assert q == p
+    wh, Zh = w.cpu().numpy(), Z.cpu().numpy().reshape(n, p)
+    nearest = np.sort(np.sort(lam)[np.argsort(np.abs(np.sort(lam) - 0.9), kind="stable")[:p]])
+    np.testing.assert_allclose(np.sort(wh), nearest, rtol=0, atol=1e-12 * np.abs(lam).max())
+    assert np.linalg.norm(A @ Zh - Zh * wh, axis=0).max() < 1e-11 * np.abs(lam).max()
+    np.testing.assert_allclose(Zh.T @ Zh, np.eye(p), atol=1e-11)

@@ -435,9 +435,12 @@ __global__ __launch_bounds__(kT) void trinv_kernel(int n, const double* __restri
 //
 // Every wait ends: the waves take 16 slots of one workgroup each, all waves that a wait depends
 // on are in the same grid, other kernels' workgroups end by themselves, and a wave that has
-// polled kPolls times (seconds) reports in *err and leaves.
+// polled kPolls times in one step (half a microsecond or more each, the time of a load that passes
+// the L2: 17 s at least) reports in *err and leaves; the solve then ends with the device error that
+// partial_syev raises (PP_EDEVICE).  (The device's clock in this loop instead of a count costs the
+// compiler half as many registers again, and spills at n > 448.)
 constexpr unsigned long long kUnset = ~0ull;
-constexpr int kPolls = 1 << 22;
+constexpr int kPolls = 1 << 25;
 constexpr int kTriWaves = 64;
 
 __global__ void exchange_fill_kernel(long n, unsigned long long* __restrict__ x, int* __restrict__ err) {

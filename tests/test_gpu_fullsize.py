@@ -171,3 +171,42 @@ def test_fullsize_fp32_products(P):
         a, b = o64[j].cpu().numpy(), o32[j].cpu().numpy()
         err = np.abs(a - b).max()
         assert err <= 2e-6 * np.abs(a).max(), (j, err, np.abs(a).max())
+
+
+def test_projected_problem_beside_long_products(P):
+    """The tridiagonalization, whose 16 workgroups wait for one another, while products on another
+    stream keep every compute unit busy (amplitude launches of 0.1 s each): it finds its places, and its
+    eigenpairs are those of an idle device, bit for bit."""
+    from paper_2512_09811_amd import binding
+    from synth.device_gen import gen_device
+    o, v, X, n, p = 64, 256, 768, 448, 28
+    t = gen_device(9, o, v, X)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    V = torch.randn((8, 2, o * v), generator=g, device="cuda", dtype=torch.float64)
+    out = torch.empty_like(V)
+    A = torch.randn((n, n), generator=g, device="cuda", dtype=torch.float64)
+    A = (A + A.T).contiguous()
+
+    def pairs():
+        w = torch.zeros(p, dtype=torch.float64, device="cuda")
+        Z = torch.zeros(n * p, dtype=torch.float64, device="cuda")
+        t0 = time.time()
+        assert binding.partial_syev(A, 0.3, p, w, Z) == p      # waits for the device
+        return w, Z, time.time() - t0
+
+    torch.cuda.synchronize()
+    with P.Handle(t["eps"], t["B_oo"], t["B_ov"], t["B_vv"], t["dip"], order=2, device_ptrs=True,
+                  store_amplitudes=0, strip_rows=o) as h:
+        h.sigma_device(V, out)
+        ref = out.clone()
+        w0, Z0, alone = pairs()
+        for _ in range(3):
+            for _ in range(4):
+                h.sigma_device(V, out, async_=True)
+            w, Z, beside = pairs()
+            h.sync()
+            print(f"[fullsize] eigenpairs alone {1e3 * alone:.1f} ms, with four products {1e3 * beside:.1f} ms",
+                  flush=True)
+            assert beside > 4 * alone                          # the products did run meanwhile
+            assert torch.equal(w, w0) and torch.equal(Z, Z0)
+            assert torch.equal(out, ref)

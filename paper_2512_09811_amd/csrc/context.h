@@ -337,7 +337,7 @@ struct Context {
   float *w32_V = nullptr, *w32_c = nullptr, *w32_J = nullptr, *w32_G = nullptr, *w32_U = nullptr,
         *w32_H = nullptr, *w32_S = nullptr, *w32_tau = nullptr, *w32_P = nullptr, *w32_AV = nullptr,
         *w32_BV = nullptr;
-  std::vector<hipStream_t> solver_streams;  // one per concurrent window, kept between solves
+  std::vector<hipStream_t> solver_streams;  // one per concurrent window, some kept between solves
   Workspace ws;      // split-K workspace
   size_t ws_bytes = 0;
 

@@ -1321,6 +1321,10 @@ void Solver::run(double* energies, double* vectors, double* osc, pp_solve_info* 
 
 }  // namespace
 
+// Streams of concurrent windows that a context keeps between solves (one costs 0.12 ms to make; a
+// spectrum of more windows than this makes the others anew).
+constexpr size_t kKeptStreams = 8;
+
 void window_solve_many(Context& c, const SolveOptions& opt, int nw, const double* omega0, int n_roots,
                        double* energies, double* vectors, double* osc, pp_solve_info* info) {
   PPW_HIP(hipSetDevice(c.device));
@@ -1339,9 +1343,19 @@ void window_solve_many(Context& c, const SolveOptions& opt, int nw, const double
     for (int w = g; w < nw; w += ngroups) ++members;
     pbs.emplace_back(new ProductBatcher(c, members, opt.precision, &enqueue, opt.pass_vectors));
   }
-  std::vector<std::unique_ptr<Solver>> sv;
+  struct Trim {
+    Context& c;
+    ~Trim() {
+      while (c.solver_streams.size() > kKeptStreams) {
+        (void)hipStreamDestroy(c.solver_streams.back());
+        c.solver_streams.pop_back();
+      }
+    }
+  } trim{c};
+  std::vector<std::unique_ptr<Solver>> sv;  // (gone before its streams)
   std::vector<int> ktot(ngroups, 0);
-  // one window takes turns with its products, so it shares their stream; several have one each
+  // one window takes turns with its products, so it shares their stream; several have one each, of
+  // which kKeptStreams stay with the context
   while (nw > 1 && (int)c.solver_streams.size() < nw) {
     hipStream_t q = nullptr;
     PPW_HIP(hipStreamCreateWithFlags(&q, hipStreamNonBlocking));

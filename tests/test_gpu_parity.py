@@ -442,3 +442,20 @@ def test_products_of_many_auxiliary_functions(P, o, v, naux):
         corr = ref[j] - (Vh * np.diag(A if j == 0 else (B if j == 1 else S))) if j < 2 else ref[j] - Vh
         err = np.abs(outs[3 + j].cpu().numpy() - ref[j]).max()
         assert err <= 2e-6 * np.abs(corr).max() + 1e-14, (j, err, np.abs(corr).max())
+
+
+def test_more_windows_than_kept_streams(P):
+    """Eleven windows in one call, more than a handle keeps streams for, and again after the spare ones
+    have been given back: the same roots bit for bit, those of the dense oracle, and one window after them."""
+    sys_ = gen(7, 8, 24, 64, b_scale=0.3)
+    A, B, S = dense.assemble(sys_, 1)
+    omegas = [float(w) for w in np.linspace(0.35, 1.35, 11)]
+    with P.Handle.from_system(sys_, order=1) as h:
+        e1, _, f1, _ = h.window_solve_batch(omegas, 3, vectors=False)
+        e2, _, f2, _ = h.window_solve_batch(omegas, 3, vectors=False)
+        assert np.array_equal(e1, e2) and np.array_equal(f1, f2)
+        for w, e in zip(omegas, e1):
+            ref = pencil.window_solve(A, B, S, sys_.dip, w, 3)[0]
+            np.testing.assert_allclose(e, ref, rtol=0, atol=1e-8)
+        one, _, _, _ = h.window_solve(omegas[4], 3)
+        np.testing.assert_allclose(one, e1[4], rtol=0, atol=1e-9)

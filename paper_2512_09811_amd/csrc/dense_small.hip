@@ -311,9 +311,8 @@ __global__ __launch_bounds__(kCholNB + kCholRows) void chol_panel_kernel(int n, 
                                                                          int* __restrict__ info) {
   __shared__ double Ds[kCholNB][kCholNB];    // [column][row] of the diagonal block
   __shared__ double Os[kCholNB][kCholRows];  // [column][row] of this workgroup's rows below it
-  __shared__ int bad;
+  __shared__ int bad, failed;
   const int tid = threadIdx.x, nt = kCholNB + kCholRows;
-  if (info && j0 > 0 && *info != 0) return;
   const int j1 = j0 + jb, r0 = j1 + (int)blockIdx.x * kCholRows;
   const int nown = max(0, min(kCholRows, n - r0));
   for (int i = tid; i < jb * jb; i += nt) {
@@ -324,8 +323,13 @@ __global__ __launch_bounds__(kCholNB + kCholRows) void chol_panel_kernel(int n, 
     const int r = i / jb, k = i % jb;
     Os[k][r] = W[(long)(r0 + r) * n + j0 + k];
   }
-  if (tid == 0) bad = 0;
+  if (tid == 0) {
+    bad = 0;
+    // (read once: workgroup 0 may be writing its own failure while another starts)
+    failed = info && j0 > 0 && *info != 0;
+  }
   __syncthreads();
+  if (failed) return;
   const bool diag = tid < kCholNB;
   const int row = diag ? tid : tid - kCholNB;
   const bool live = diag ? row < jb : row < nown;

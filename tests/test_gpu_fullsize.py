@@ -210,3 +210,33 @@ def test_projected_problem_beside_long_products(P):
             assert beside > 4 * alone                          # the products did run meanwhile
             assert torch.equal(w, w0) and torch.equal(Z, Z0)
             assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("o,v,X,rows", [(40, 72, 100, 5), (40, 72, 100, 9), (44, 53, 90, 7), (50, 120, 100, 17)])
+def test_strips_off_the_tiles(P, o, v, X, rows):
+    """Amplitudes rebuilt in strips of several tile rows whose offsets in the symmetric matrix of
+    integrals are not whole tiles (128 rows in FP64, 128 and 256 in split BF16), the last strip shorter:
+    tiles below a strip's diagonal are left out, and none that the amplitudes read may be (it would hold
+    the integrals of the strip before).  The second-order part of B V against that of stored amplitudes:
+    1e-9 of its scale in FP64, in split BF16 2^-16 of the products' scale with a margin of 8."""
+    from synth.device_gen import gen_device
+    t = gen_device(o + rows, o, v, X)
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    U = torch.randn((3, o * v), generator=g, device="cuda", dtype=torch.float64)
+
+    def second(precision, **kw):
+        with P.Handle(t["eps"], t["B_oo"], t["B_ov"], t["B_vv"], t["dip"], order=2, device_ptrs=True,
+                      precision=precision, **kw) as h:
+            got = {}
+            for order in (1, 2):
+                for fp32 in ((False,) if precision == P.PP_FP64 else (False, True)):
+                    a, b, s = (torch.empty_like(U) for _ in range(3))
+                    h.products(U, a, b, s, order=order, fp32=fp32)
+                    got[order, fp32] = b
+            return {f: got[2, f] - got[1, f] for o_, f in got if o_ == 2}
+
+    ref = second(P.PP_FP64, store_amplitudes=1)[False]
+    scale = ref.abs().max()
+    strips = second(P.PP_SPLIT_BF16, store_amplitudes=0, strip_rows=rows)
+    assert (strips[False] - ref).abs().max() <= 1e-9 * scale
+    assert (strips[True] - ref).abs().max() <= 8 * 2.0 ** -16 * scale

@@ -12,15 +12,16 @@ namespace ppw {
 // 8-value chunks, plus 64 values (256 B) when that would start the rows a multiple of
 // 4 KiB apart.  Rows 1 MiB apart (n = 262144) all start on the same memory channels and
 // a 256-row GEMM tile of them ran 6% slower than with the 256 B offset.
-// Row stride of the FP64 G and of rebuilt amplitude strips: rows a multiple of 256 KiB apart start
-// on the same memory channels (the amplitude contraction with rows 2 MiB apart: 62.9 TF/s, with 32
-// values between them 72.2; 512 KiB apart 69.7 and 71.4).
-inline long padded_stride64(long n) { return n % 32768 == 0 ? n + 32 : n; }
-
 inline long padded_stride(long n) {
   const long p = (n + 7) / 8 * 8;
   return (p * 4) % 4096 == 0 ? p + 64 : p;
 }
+
+// Row stride of the FP64 G and of rebuilt amplitude strips: rows a multiple of 1 MiB apart start on
+// the same memory channels.  Measured, as they are | with 32 values between them: 2 MiB apart 68.0 |
+// 72.9 TF/s (2048 x 2048 over 262144), 1 MiB apart 72.3 | 73.7 (8192 x 8192 over 131072); 256 and
+// 512 KiB apart 73.7 either way.
+inline long padded_stride64(long n) { return n % 131072 == 0 ? n + 32 : n; }
 
 // Device allocations with a byte budget.  Every allocation of a handle goes
 // through its arena, so the footprint is known and bounded.

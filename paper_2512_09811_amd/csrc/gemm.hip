@@ -8,10 +8,10 @@
 // Design (gfx950):
 //  * 256 threads = 4 wave64, arranged 2x2; each wave owns a (BM/2)x(BN/2) block of
 //    C made of 16x16 MFMA tiles (v_mfma_f64_16x16x4f64 / v_mfma_f32_16x16x4f32).
-//  * A and B tiles (BK deep) are staged through LDS in k-major layout
-//    ([BK][BM+pad]) so that one MFMA operand fragment is a 16-lane contiguous
-//    read; two LDS buffers and a register prefetch of the next tile overlap global
-//    loads with matrix-core work (one barrier per BK step).
+//  * A and B tiles (BK deep) go through two LDS buffers, with one barrier per BK step
+//    that stands before the step's last quarter.  FP64 operands contiguous along k (and
+//    split-BF16 ones) are loaded straight into LDS, the other layouts through registers
+//    that hold the next tile; either way a load has a whole tile's time to arrive.
 //  * Workgroup ids are remapped so that the tiles an XCD runs are contiguous in a
 //    grouped (row-band) order: tiles sharing A rows or B columns hit the same L2.
 //  * Split-K (over the flattened outer x inner reduction) writes per-split partial
@@ -1409,8 +1409,10 @@ void gemm_dispatch(const GemmDesc& d, T alpha, const T* A, const T* B, T beta, T
   }
   if constexpr (TAG == 0) {
     // Rows of tiles of 96 where as many of them do as of 128 (96 rows in one, 129 .. 192 in two,
-    // 257 .. 288 in three): a quarter less work for the same workgroups and reduction splits.  K_A
-    // at 96/384/1152 (96 x 384 over 96 x 1152, 16 vectors): 2.82 ms with 128 rows, 2.17 with 96.
+    // 257 .. 288 in three): a quarter less work for the same workgroups and reduction splits.  128
+    // rows | 96, FP64: 96 x 512 over 96 x 1500, 8 vectors, 2.70 | 2.21 ms, 130 (130 x 1500) 7.10 | 5.49,
+    // 192 (192 x 1500) 10.3 | 8.7, 288 (288 x 1500) 21.9 | 18.8; between 1.16 and 1.42 times as fast at
+    // 96, 130, 160, 192, 260 and 288 rows, in FP64 and FP32, over operands of all layouts.
     if (big && d.sym < 0 && (d.M + 95) / 96 == (d.M + 127) / 128) {
       checked_workgroups<128, 128, 16>(d);
       PPW_GEMM_CASE(96, 128, true, true)

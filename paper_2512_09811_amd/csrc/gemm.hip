@@ -230,7 +230,8 @@ __device__ __forceinline__ void gemm_tile_dma(const GemmDesc& d, double alpha, c
   // address from scalar registers and one vector register (32-bit byte offsets: longer rows go through
   // registers).
   const bool dma = (d.lda % 2) == 0 && (d.ldb % 2) == 0 && (d.sAk % 2) == 0 && (d.sBk % 2) == 0 &&
-                   ((uintptr_t)Atile % 16) == 0 && ((uintptr_t)Btile % 16) == 0 && d.K % 2 == 0 && d.lda < kDmaRow && d.ldb < kDmaRow;
+                   ((uintptr_t)Atile % 16) == 0 && ((uintptr_t)Btile % 16) == 0 && d.K % 2 == 0 &&
+                   d.lda < kDmaRow && d.ldb < kDmaRow;
   const int kpl = (lane & 7) ^ (4 * (wave & 1) + (lane >> 4));
   long rowA[CA], rowB[CB];
   unsigned laneA[CA], laneB[CB];
@@ -1609,7 +1610,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_sbf16_kernel(
   __shared__ __attribute__((aligned(16))) float As1[SA];
   __shared__ __attribute__((aligned(16))) float Bs0[SB];
   __shared__ __attribute__((aligned(16))) float Bs1[SB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
   const int tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
   int tm, tn;
   if (d.sym >= 0) {

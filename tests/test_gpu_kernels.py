@@ -634,7 +634,8 @@ def test_gemm_rows_96(B, fp32, M):
 
 @pytest.mark.parametrize("KB", [1, 3])
 @pytest.mark.parametrize("M,N,K", [(1001, 999, 1), (1001, 999, 2), (997, 1003, 3), (1000, 1004, 15), (1002, 998, 18),
-                                   (1003, 1001, 31), (1006, 1010, 44), (1000, 1000, 47)])
+                                   (1003, 1001, 31), (1006, 1010, 44), (1000, 1000, 47), (1001, 1003, 17),
+                                   (999, 1002, 33)])
 def test_gemm_ragged_rows(B, M, N, K, KB):
     """k-contiguous FP64 products with edges inside a group of 8 rows and ragged k tiles of every
     kind (one value, one pair, odd, even), rows padded by NaN.  Even rows of an even K go straight

@@ -77,9 +77,9 @@ def hhat_traffic(flops_per_launch, precision):
 # KiB per dispatch) scaled by what the same counters read for a plain 1 GiB device copy
 # in the same runs (--copy-calibration); valid for the GEMM source with this digest and
 # launches of this size only (else null).
-PRODUCT_TRAFFIC = {"gemm_sha256_16": "e57879e29ca9be4a", "flops_per_launch": 281474976710656.0,
-                   "fetch_kib": 403022119.7, "write_kib": 2310144.0,
-                   "copy_fetch_kib": 524302.2, "copy_write_kib": 1048576.0}
+PRODUCT_TRAFFIC = {"gemm_sha256_16": "3150dfdd34cb7edb", "flops_per_launch": 281474976710656.0,
+                   "fetch_kib": 402669770.5, "write_kib": 2097152.0,
+                   "copy_fetch_kib": 524302.5, "copy_write_kib": 1048576.0}
 
 
 def product_traffic(flops_per_launch):
